@@ -334,3 +334,34 @@ def test_lidar_at_benchmark_scale_sampled(R):
     got = R.render_lidar(R.add_synth_scene(scene), [rot, grid, ros], vmt, pt)
     got = [(r.cpu().numpy(), h.cpu().numpy()) for r, h in got]
     _sampled_compare(R, scene, batch, [rot, grid, ros], got, 24, "benchmark scale")
+
+
+@pytest.mark.parametrize("ts", [8, 16])
+@pytest.mark.parametrize("shape", ["needle", "disc", "tiny"])
+def test_ellipsoid_culling_matches_oracle(ts, shape):
+    """Long, flat and very small Gaussians at all distances, grids off the ray
+    tiles' sides: a wave drops a Gaussian by its ellipsoid only where no ray
+    takes it."""
+    _torch()
+    from paper_2604_25459_amd import gsr
+    rng = np.random.default_rng({"needle": 1, "disc": 2, "tiny": 3}[shape])
+    n, E = 1500, 2
+    sc = {"needle": [0.6, 0.012, 0.012], "disc": [0.3, 0.3, 0.004], "tiny": [0.012, 0.009, 0.006]}[shape]
+    means = rng.uniform(-2.5, 2.5, (n, 3)) * (rng.uniform(0.05, 1.0, (n, 1)) if shape == "tiny" else 1.0)
+    scales = np.asarray(sc)[None] * np.exp(0.4 * rng.standard_normal((n, 3)))
+    quats = rng.standard_normal((n, 4))
+    scene = scene_from(means, scales, quats=quats, opac=rng.uniform(0.05, 0.999, n), degree=0)
+    lids = [synth.rotating_lidar(13, 100, -35, 40), synth.height_grid(19, 37, 0.06 if shape != "tiny" else 0.02),
+            synth.rosette_lidar(17, 45, 40.0, s0=2.0)]
+    vm = np.stack([synth.sensor_viewmats(rng, E, 0.0, 0.8, z) for z in (0.1, 0.9, 0.2)])
+    batch = synth.LidarBatch(cams=lids, viewmats=vm, poses=np.zeros((E, 0, 7), np.float32))
+    r = gsr.Renderer(0, tile_size=ts)
+    sid = r.add_synth_scene(scene)
+    vm_t, poses_t = _tensors(batch)
+    out = r.render_lidar(sid, lids, vm_t, poses_t)
+    for l in range(3):
+        for e in range(E):
+            ref = lidar_ref(scene, batch, l, e)
+            _compare(out[l][0][e].cpu().numpy(), out[l][1][e].cpu().numpy(), ref, f"{shape} ts {ts} slot {l} env {e}",
+                     scene, batch, l, e, min_hits=1)
+    r.close()
