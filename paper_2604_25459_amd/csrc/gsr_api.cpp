@@ -276,6 +276,8 @@ ChunkPlan plan_chunks(const gsr_ctx* ctx, const SceneRes* sc, const std::vector<
         c = (imgs.size() + n_chunks - 1) / n_chunks;
         p.chunk = (int)std::min<size_t>(c, imgs.size());
     }
+    p.tile_items = tile_items_for((uint64_t)n, (uint64_t)p.chunk, p.tx_max, p.ty_max);
+    p.tile_blocks = (int)std::max<int64_t>(1, (n + p.tile_items - 1) / p.tile_items);
     return p;
 }
 
@@ -387,6 +389,7 @@ ChunkDev chunk_view(Workspace& ws, const SceneRes* sc, const ChunkPlan& p, int i
     c.rect4 = rect4_format(tx_max, ty_max);
     c.sort_blocks = p.sort_blocks;
     c.tile_blocks = p.tile_blocks;
+    c.tile_items = p.tile_items;
     c.img = ws.img.as<ImageInfo>() + i0;
     c.xform = ws.xform.as<float>();
     c.keyz = ws.keyz.as<uint32_t>();
@@ -517,7 +520,7 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
                                  (uint64_t)(uintptr_t)s.body_off, (uint64_t)job.lidar,
                                  (uint64_t)(uintptr_t)c.img, (uint64_t)n_img,
                                  (uint64_t)c.t_max, (uint64_t)c.tx_max, (uint64_t)c.ty_max, (uint64_t)c.sort_blocks,
-                                 (uint64_t)c.tile_blocks, (uint64_t)tu.ts, (uint64_t)tu.batch, (uint64_t)tu.ipt,
+                                 (uint64_t)c.tile_blocks, (uint64_t)c.tile_items, (uint64_t)tu.ts, (uint64_t)tu.batch, (uint64_t)tu.ipt,
                                  (uint64_t)tu.persistent, (uint64_t)(uintptr_t)job.viewmats,
                                  (uint64_t)(uintptr_t)job.poses, (uint64_t)(uintptr_t)ws.h_total,
                                  (uint64_t)(ctx->opt.cutoff * 1.0e6f), (uint64_t)tu.bin, (uint64_t)async_lists,
@@ -586,9 +589,14 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
         *pairs_total = total;
         // segments per tile-row list: enough level-2 waves for the launch, none shorter than kRowSegEntries
         const uint64_t per_row = n_rows ? row_total / n_rows : 0;
-        const uint64_t by_len = std::max<uint64_t>(1, per_row / kRowSegEntries);
-        const uint64_t by_waves = n_rows ? ((uint64_t)kLevel2Waves + n_rows - 1) / n_rows : 1;
-        n_seg = (int)std::min<uint64_t>(32, std::min(by_len, by_waves));
+        uint64_t by_len = std::max<uint64_t>(1, per_row / kRowSegEntries), most = 32;
+        uint64_t by_waves = n_rows ? ((uint64_t)kLevel2Waves + n_rows - 1) / n_rows : 1;
+        if (n_rows * std::min(by_len, most) < (uint64_t)kLevel2FewWaves) {
+            by_len = std::max<uint64_t>(1, per_row / kRowSegEntriesFew);
+            by_waves = n_rows ? ((uint64_t)kLevel2FewWaves + n_rows - 1) / n_rows : 1;
+            most = kMaxRowSegs;
+        }
+        n_seg = (int)std::min<uint64_t>(most, std::min(by_len, by_waves));
         if ((int)ws.nseg_hint.size() <= chunk_idx) ws.nseg_hint.resize((size_t)chunk_idx + 1, 1);
         ws.nseg_hint[chunk_idx] = n_seg;
     }

@@ -128,7 +128,8 @@ struct ChunkDev {
     int n_img;
     int t_max;                 // largest tile count of an image in the chunk
     int sort_blocks;           // depth-sort blocks per image (pass 0: ceil(n / kSortItems))
-    int tile_blocks;           // tile-pass blocks per image (ceil(n / kTileGauss))
+    int tile_blocks;           // tile-pass blocks per image (ceil(n / tile_items))
+    int tile_items;            // depth-ordered Gaussians per tile-pass block (level 1: one wave each)
     const ImageInfo* img;      // [n_img]
     float* xform;              // [n_img][n_bodies + 1][16]
     uint32_t* keyz;            // [n_img][n] depth bits or kInvalidKey
@@ -180,15 +181,38 @@ constexpr int kKmmStride = 2;
 constexpr int kSortBlock = 256;
 constexpr int kSortIpt = 16;
 constexpr int kSortItems = kSortBlock * kSortIpt;   // 4096 items per block
-// Tile pass geometry: one wave per block, kTileGauss depth-ordered Gaussians per block.
+// Tile pass geometry: k_tile_hist counts kTileGauss depth-ordered Gaussians per
+// block; level 1 places `tile_items` of them per wave (tile_items_for).
 constexpr int kTileGauss = 4096;
+constexpr int kTileItemsMin = 256;
+constexpr int kLevel1Waves = 8192;
+// Items per level-1 wave: a wave walks its items in dependent groups of 64, so
+// a launch of few images is cut into more, shorter waves until it has about
+// kLevel1Waves of them (a single 640x480 image of 300k Gaussians: one wave per
+// 4096 items took 201 us with 74 waves on the chip, 256 items 29 us).  Large
+// launches keep 4096: every block starts and ends its row lists with partial
+// lines, and the scan of block offsets grows with the blocks.  The rows counted
+// per block also have to fit the LDS of k_tile_hist beside its tile counts.
+inline int tile_items_for(uint64_t n, uint64_t n_img, int tx_max, int ty_max)
+{
+    int items = kTileGauss;
+    while (items > kTileItemsMin && n * n_img / (uint64_t)items < (uint64_t)kLevel1Waves &&
+           ((size_t)(tx_max + 1) * (ty_max + 1) + (size_t)(2 * kTileGauss / items) * (ty_max + 1)) * 4 <= 60 * 1024)
+        items /= 2;
+    return items;
+}
 // Level 2 runs one wave per (image, tile row, segment).  Tile-row lists are
 // cut into segments only as far as the launch needs to have about
 // kLevel2Waves waves, and never into segments shorter than kRowSegEntries:
 // every extra segment costs a per-segment count pass over its entries, and
-// many short waves crowd out a rasteriser running beside them.
+// many short waves crowd out a rasteriser running beside them.  A launch that
+// would stay below kLevel2FewWaves waves that way takes segments of down to
+// kRowSegEntriesFew entries instead: there the longest wave is what it waits for.
 constexpr int kRowSegEntries = 1024;
+constexpr int kRowSegEntriesFew = 256;
 constexpr int kLevel2Waves = 16384;
+constexpr int kLevel2FewWaves = 4096;
+constexpr int kMaxRowSegs = 128;
 
 // ------------------------------------------------------------ launchers
 // All launchers enqueue on `stream` and return hipGetLastError().

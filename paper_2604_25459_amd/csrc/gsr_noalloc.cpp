@@ -61,6 +61,14 @@ size_t chunk_fixed_bytes(const SceneRes* sc, const ChunkPlan& plan)
     return b;
 }
 
+// The plan with the fewest tile-pass blocks (the smallest block counts).
+ChunkPlan coarse_blocks(const SceneRes* sc, ChunkPlan plan)
+{
+    plan.tile_items = kTileGauss;
+    plan.tile_blocks = (int)std::max<int64_t>(1, (sc->dev.n + kTileGauss - 1) / kTileGauss);
+    return plan;
+}
+
 // Points the workspace's per-chunk buffers into the scratch from `base` on;
 // the tile lists get what is left up to `end`.
 void carve(Workspace& ws, const SceneRes* sc, const ChunkPlan& plan, char* base, char* end)
@@ -130,7 +138,8 @@ int render_noalloc(gsr_ctx* ctx, NoallocDev& nd, SceneRes* sc, const gsr_render_
     ChunkPlan plan = plan_chunks(ctx, sc, job.imgs, false, 0, 48, (int64_t)budget);
     int chunk = std::max(1, std::min(plan.chunk, n_img));
     plan.chunk = 1;
-    const size_t one = chunk_fixed_bytes(sc, plan);
+    const ChunkPlan coarse = coarse_blocks(sc, plan);
+    const size_t one = chunk_fixed_bytes(sc, coarse);
     if (one + kAlign > budget) {
         char msg[256];
         std::snprintf(msg, sizeof msg,
@@ -145,6 +154,8 @@ int render_noalloc(gsr_ctx* ctx, NoallocDev& nd, SceneRes* sc, const gsr_render_
         if (chunk_fixed_bytes(sc, plan) + (size_t)chunk * kAlign * 4 <= budget) break;
         chunk = (chunk + 1) / 2;
     }
+    plan.chunk = chunk;
+    if (chunk_fixed_bytes(sc, plan) + kAlign > budget) plan = coarse;
 
     // work of the previous call (on any stream) has finished with the scratch
     // before this call's first write to it
@@ -166,8 +177,9 @@ int render_noalloc(gsr_ctx* ctx, NoallocDev& nd, SceneRes* sc, const gsr_render_
         carve(nd.ws, sc, plan, nd.ptr + img_bytes, nd.ptr + kScratchBytes);
         uint64_t total = 0;
         rc = run_chunk(ctx, nd.ws, sc, job, plan, i0, m, chunk_idx, st, Mode::kRender, false, &total);
-        if (rc == GSR_E_OVERFLOW && m > 1) {
-            chunk = m / 2;             // the same images again in smaller chunks
+        if (rc == GSR_E_OVERFLOW && (m > 1 || plan.tile_items != coarse.tile_items)) {
+            chunk = std::max(1, m / 2);             // the same images again in smaller chunks
+            if (m == 1) plan = coarse;              // the last room: the block counts' share
             rc = GSR_OK;
             continue;
         }

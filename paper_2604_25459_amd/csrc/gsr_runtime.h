@@ -133,6 +133,7 @@ struct ChunkPlan {
     int t_max;          // max tiles of any image
     int tx_max, ty_max; // max tile columns / rows of any image
     int sort_blocks, tile_blocks;
+    int tile_items;     // depth-ordered Gaussians per tile-pass block
 };
 
 // Debug stop of a render sequence: the job ends after the chunk that holds

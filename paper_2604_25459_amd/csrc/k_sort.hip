@@ -150,14 +150,18 @@ __global__ __launch_bounds__(256) void k_sort_hist(const uint32_t* __restrict__ 
 }
 
 // Per image: digit-major, block-minor exclusive offsets (in place).  Pass 0
-// also records the number of visible Gaussians.
-template <bool FIRST>
-__global__ __launch_bounds__(256) void k_sort_scan(uint32_t* __restrict__ hist, int blocks, uint32_t* __restrict__ counts,
-                                                   uint32_t* __restrict__ kmm, uint64_t n, int pass,
-                                                   const uint32_t* __restrict__ kblk)
+// also records the number of visible Gaussians.  SEGS = 1: 256 threads, thread
+// d owning digits d and d + 256.  SEGS = 4 (launches of few images, where the
+// walk over one image's blocks is what the launch waits for): each of four
+// groups of 256 threads takes a quarter of the blocks.
+template <bool FIRST, int SEGS>
+__global__ __launch_bounds__(256 * SEGS) void k_sort_scan(uint32_t* __restrict__ hist, int blocks,
+                                                          uint32_t* __restrict__ counts, uint32_t* __restrict__ kmm,
+                                                          uint64_t n, int pass, const uint32_t* __restrict__ kblk)
 {
-    __shared__ uint32_t lds8[8], red[8];
-    const int i = blockIdx.x, d = threadIdx.x;
+    __shared__ uint32_t lds8[8], red[8 * SEGS];
+    __shared__ uint32_t seg_sum[SEGS][kRadix];
+    const int i = blockIdx.x, d = threadIdx.x & 255, sg = threadIdx.x >> 8;
     if (pass == 3 && !wide_image(kmm, i)) return;
     const uint64_t cnt = FIRST ? n : counts[i];
     const int nb = (int)((cnt + kSortItems - 1) / kSortItems);
@@ -165,54 +169,104 @@ __global__ __launch_bounds__(256) void k_sort_scan(uint32_t* __restrict__ hist, 
         // the image's key range from its blocks' ranges; the smallest key is
         // kept rounded down to a multiple of 512 (see k_sort_hist)
         uint32_t kmin = 0xFFFFFFFFu, kmax = 0u;
-        for (int b = d; b < nb; b += 256) {
+        for (int b = threadIdx.x; b < nb; b += 256 * SEGS) {
             kmin = min(kmin, kblk[((size_t)i * blocks + b) * 2]);
             kmax = max(kmax, kblk[((size_t)i * blocks + b) * 2 + 1]);
         }
         const uint32_t hi = wave_last(wave_incl_max(kmax)), lo = ~wave_last(wave_incl_max(~kmin));
         if (__lane_id() == 0) {
-            red[2 * (d >> 6)] = lo;
-            red[2 * (d >> 6) + 1] = hi;
+            red[2 * (threadIdx.x >> 6)] = lo;
+            red[2 * (threadIdx.x >> 6) + 1] = hi;
         }
         __syncthreads();
-        if (d == 0) {
-            const uint32_t l = min(min(red[0], red[2]), min(red[4], red[6]));
-            kmm[kKmmStride * i] = l <= max(max(red[1], red[3]), max(red[5], red[7])) ? (l & ~kDigitMask) : l;
-            kmm[kKmmStride * i + 1] = max(max(red[1], red[3]), max(red[5], red[7]));
+        if (threadIdx.x == 0) {
+            uint32_t l = red[0], h = red[1];
+            for (int k = 1; k < 4 * SEGS; ++k) {
+                l = min(l, red[2 * k]);
+                h = max(h, red[2 * k + 1]);
+            }
+            kmm[kKmmStride * i] = l <= h ? (l & ~kDigitMask) : l;
+            kmm[kKmmStride * i + 1] = h;
         }
     }
     uint32_t* H = hist + (size_t)i * blocks * kRadix;
+    const int b_lo = nb * sg / SEGS, b_hi = nb * (sg + 1) / SEGS;
     // thread d owns digits d and d + 256: the scan runs over the first half,
     // then over the second half after the first half's total
     uint32_t tot[kDpt] = {};
-    for (int b = 0; b < nb; ++b)
+    for (int b0 = b_lo; b0 < b_hi; b0 += 8) {
+        uint32_t v[8][kDpt];
 #pragma unroll
-        for (int q = 0; q < kDpt; ++q) tot[q] += H[(size_t)b * kRadix + d + 256 * q];
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int r = 0; r < kDpt; ++r) v[q][r] = b0 + q < b_hi ? H[(size_t)(b0 + q) * kRadix + d + 256 * r] : 0u;
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+            for (int r = 0; r < kDpt; ++r) tot[r] += v[q][r];
+    }
+    uint32_t below[kDpt] = {};
+    if (SEGS > 1) {
+#pragma unroll
+        for (int r = 0; r < kDpt; ++r) seg_sum[sg][d + 256 * r] = tot[r];
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kDpt; ++r) {
+            tot[r] = 0u;
+#pragma unroll
+            for (int k = 0; k < SEGS; ++k) {
+                const uint32_t v = seg_sum[k][d + 256 * r];
+                below[r] += k < sg ? v : 0u;
+                tot[r] += v;
+            }
+        }
+    }
+    // every group scans the same 512 totals (its own four waves' partial sums)
     uint32_t run[kDpt], all = 0;
 #pragma unroll
     for (int q = 0; q < kDpt; ++q) {
-        uint32_t total;
-        run[q] = all + block_excl_scan256(tot[q], &total, lds8);
+        const uint32_t x = wave_incl_sum(tot[q]);
+        if (sg == 0 && __lane_id() == 63) lds8[d >> 6] = x;
+        __syncthreads();
+        uint32_t pre = 0, total = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            pre += k < (d >> 6) ? lds8[k] : 0u;
+            total += lds8[k];
+        }
+        __syncthreads();
+        run[q] = all + pre + x - tot[q] + below[q];
         all += total;
     }
-    if (FIRST && d == 0) counts[i] = all;
+    if (FIRST && threadIdx.x == 0) counts[i] = all;
     // offsets in place, 16 blocks at a time: the loads of a group are all
     // complete (one wait) before its stores
-    for (int b0 = 0; b0 < nb; b0 += 16) {
+    for (int b0 = b_lo; b0 < b_hi; b0 += 16) {
         uint32_t v[16][kDpt];
 #pragma unroll
         for (int q = 0; q < 16; ++q)
 #pragma unroll
-            for (int r = 0; r < kDpt; ++r) v[q][r] = b0 + q < nb ? H[(size_t)(b0 + q) * kRadix + d + 256 * r] : 0u;
+            for (int r = 0; r < kDpt; ++r) v[q][r] = b0 + q < b_hi ? H[(size_t)(b0 + q) * kRadix + d + 256 * r] : 0u;
         __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
 #pragma unroll
         for (int q = 0; q < 16; ++q)
 #pragma unroll
             for (int r = 0; r < kDpt; ++r) {
-                if (b0 + q < nb) H[(size_t)(b0 + q) * kRadix + d + 256 * r] = run[r];
+                if (b0 + q < b_hi) H[(size_t)(b0 + q) * kRadix + d + 256 * r] = run[r];
                 run[r] += v[q][r];
             }
     }
+}
+
+template <bool FIRST>
+void launch_scan(const ChunkDev& c, uint64_t n, int pass, hipStream_t stream)
+{
+    if (c.n_img < 256)
+        hipLaunchKernelGGL((k_sort_scan<FIRST, 4>), dim3(c.n_img), dim3(1024), 0, stream, c.sort_hist, c.sort_blocks,
+                           c.vis_count, c.kmm, n, pass, (const uint32_t*)c.kblk);
+    else
+        hipLaunchKernelGGL((k_sort_scan<FIRST, 1>), dim3(c.n_img), dim3(256), 0, stream, c.sort_hist, c.sort_blocks,
+                           c.vis_count, c.kmm, n, pass, (const uint32_t*)c.kblk);
 }
 
 template <typename R>
@@ -383,8 +437,7 @@ hipError_t launch_depth_sort(const SceneDev& s, const ChunkDev& c, hipStream_t s
     // pass 0: dense keys (index order) -> compacted keys relative to the image's smallest, digit 0
     hipLaunchKernelGGL(k_sort_hist<true>, grid, dim3(256), 0, stream, c.keyz, (const uint32_t*)nullptr, c.vis_count,
                        c.kmm, n, 0, c.sort_hist, c.sort_blocks, c.kblk);
-    hipLaunchKernelGGL(k_sort_scan<true>, dim3(c.n_img), dim3(256), 0, stream, c.sort_hist, c.sort_blocks,
-                       c.vis_count, c.kmm, n, 0, (const uint32_t*)c.kblk);
+    launch_scan<true>(c, n, 0, stream);
     hipLaunchKernelGGL(k_sort_scatter<true>, grid, dim3(256), 0, stream, c.keyz, c.sk[0], c.sk[1], c.sv[0], c.sv[1],
                        c.vis_count, c.kmm, n, 0, c.sort_hist, c.sort_blocks, c.rect, c.srect, c.rect4, c.err);
     // passes 1, 2 and (for images whose keys span 2^27 or more) 3; the blocks of
@@ -392,8 +445,7 @@ hipError_t launch_depth_sort(const SceneDev& s, const ChunkDev& c, hipStream_t s
     for (int pass = 1; pass < 4; ++pass) {
         hipLaunchKernelGGL(k_sort_hist<false>, grid, dim3(256), 0, stream, c.sk[0], c.sk[1], c.vis_count, c.kmm, n,
                            pass, c.sort_hist, c.sort_blocks, c.kblk);
-        hipLaunchKernelGGL(k_sort_scan<false>, dim3(c.n_img), dim3(256), 0, stream, c.sort_hist, c.sort_blocks,
-                           c.vis_count, c.kmm, n, pass, (const uint32_t*)c.kblk);
+        launch_scan<false>(c, n, pass, stream);
         hipLaunchKernelGGL(k_sort_scatter<false>, grid, dim3(256), 0, stream, (const uint32_t*)nullptr, c.sk[0],
                            c.sk[1], c.sv[0], c.sv[1], c.vis_count, c.kmm, n, pass, c.sort_hist, c.sort_blocks, c.rect,
                            c.srect, c.rect4, c.err);

@@ -12,7 +12,7 @@
 // tile of the image; scattering straight into ~10^3 tile lists leaves as many
 // partially written cache lines open per block):
 //   level 1  depth-ordered Gaussians -> one list per tile row (a Gaussian
-//            appears in each row its rectangle spans), blocks of kTileGauss
+//            appears in each row its rectangle spans), blocks of tile_items
 //            Gaussians, one output stream per tile row;
 //   level 2  one wave per segment of an (image, tile row) list walks it in
 //            order and expands each entry into the tiles of that row, one
@@ -144,6 +144,8 @@ __global__ __launch_bounds__(256) void k_zero_diff(int32_t* __restrict__ d, uint
     if (i < n) d[i] = 0;
 }
 
+// One block per kTileGauss depth-ordered Gaussians: the image's tile counts (2D
+// differences) and, for each of its sub-blocks of tile_items, the row counts.
 __global__ __launch_bounds__(256) void k_tile_hist(ChunkDev c, uint64_t n)
 {
     extern __shared__ int32_t lds_i[];
@@ -156,10 +158,10 @@ __global__ __launch_bounds__(256) void k_tile_hist(ChunkDev c, uint64_t n)
     const ImageInfo im = c.img[i];
     const int P1 = im.tiles_x + 1, Q1 = im.tiles_y + 1;
     const int D = P1 * Q1;
+    const int subs = kTileGauss / c.tile_items, sub_shift = __builtin_ctz((unsigned)c.tile_items);
     int32_t* diff = lds_i;              // [Q1][P1]
-    int32_t* rdiff = lds_i + D;         // [Q1]
-    for (int t = tid; t < D; t += 256) diff[t] = 0;
-    for (int y = tid; y < Q1; y += 256) rdiff[y] = 0;
+    int32_t* rdiff = lds_i + D;         // [subs][Q1]
+    for (int t = tid; t < D + subs * Q1; t += 256) diff[t] = 0;
     __syncthreads();
     // all of the thread's rectangle loads first, then the LDS atomics
     constexpr int kPer = kTileGauss / 256;
@@ -178,8 +180,9 @@ __global__ __launch_bounds__(256) void k_tile_hist(ChunkDev c, uint64_t n)
             atomicAdd(&diff[y0 * P1 + x1], -1);
             atomicAdd(&diff[y1 * P1 + x0], -1);
             atomicAdd(&diff[y1 * P1 + x1], 1);
-            atomicAdd(&rdiff[y0], 1);
-            atomicAdd(&rdiff[y1], -1);
+            int32_t* rd = rdiff + ((tid + 256 * q) >> sub_shift) * Q1;
+            atomicAdd(&rd[y0], 1);
+            atomicAdd(&rd[y1], -1);
         }
     }
     __syncthreads();
@@ -188,27 +191,30 @@ __global__ __launch_bounds__(256) void k_tile_hist(ChunkDev c, uint64_t n)
         const int32_t v = diff[t];
         if (v) atomicAdd(&gd[t], v);
     }
-    if (tid == 0) {                     // per-block row counts: prefix of the row differences
-        uint32_t* rout = c.row_hist + ((size_t)i * c.tile_blocks + b) * c.ty_max;
+    // per-block row counts: prefix of the row differences, one thread per sub-block
+    if (tid < subs && b * subs + tid < c.tile_blocks) {
+        uint32_t* rout = c.row_hist + ((size_t)i * c.tile_blocks + b * subs + tid) * c.ty_max;
         int32_t run = 0;
         for (int y = 0; y < im.tiles_y; ++y) {
-            run += rdiff[y];
+            run += rdiff[tid * Q1 + y];
             rout[y] = (uint32_t)run;
         }
     }
 }
 
-__device__ __forceinline__ uint32_t block_excl_scan256(uint32_t v, uint32_t* total, uint32_t* lds8)
+// Exclusive scan over the NT threads of a block; returns the block total.
+template <int NT>
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* total, uint32_t* lds16)
 {
     const int lane = __lane_id();
     const int w = threadIdx.x >> 6;
     const uint32_t x = wave_incl_sum(v);
-    if (lane == 63) lds8[w] = x;
+    if (lane == 63) lds16[w] = x;
     __syncthreads();
     uint32_t pre = 0, tot = 0;
 #pragma unroll
-    for (int k = 0; k < 4; ++k) {
-        const uint32_t s = lds8[k];
+    for (int k = 0; k < NT / 64; ++k) {
+        const uint32_t s = lds16[k];
         if (k < w) pre += s;
         tot += s;
     }
@@ -217,57 +223,88 @@ __device__ __forceinline__ uint32_t block_excl_scan256(uint32_t v, uint32_t* tot
     return pre + x - v;
 }
 
-// Per image (256 threads): bins summed over the image's blocks, exclusive scan
-// over bins -> [start, end) per bin; optionally per-block offsets in place.
-__device__ uint32_t scan_bins(uint32_t* H, int nb, int stride, int nbins, uint32_t* range, bool block_offsets,
-                              uint32_t* lds8)
+// Row lists of one image: every block's row counts become its first positions
+// (in place), and each row's [start, end) is written.  Thread (segment sg, row
+// r): the segment's blocks are summed, the sums turned into the segment's first
+// position per row, then the blocks' offsets follow, sixteen loads at a time
+// (one wait before the stores).  Returns the image's row entries.
+template <int NT>
+__device__ uint32_t scan_rows(uint32_t* H, int nb, int stride, int rows, uint32_t* range, uint32_t* part,
+                              uint32_t* lds16)
 {
     const int tid = threadIdx.x;
-    uint32_t run = 0;
-    for (int t0 = 0; t0 < nbins; t0 += 256) {
-        const int t = t0 + tid;
-        uint32_t tot = 0;
-        if (t < nbins)
-            for (int b = 0; b < nb; ++b) tot += H[(size_t)b * stride + t];
-        uint32_t chunk_total;
-        const uint32_t start = run + block_excl_scan256(tot, &chunk_total, lds8);
-        if (t < nbins) {
-            range[2 * t] = start;
-            range[2 * t + 1] = start + tot;
-            if (block_offsets) {
-                // 16 blocks at a time: a group's loads all complete (one
-                // wait) before its stores
-                uint32_t o = start;
-                for (int b0 = 0; b0 < nb; b0 += 16) {
-                    uint32_t v[16];
+    uint32_t done = 0;
+    for (int r0 = 0; r0 < rows; r0 += NT) {
+        const int m = min(rows - r0, NT);               // rows of this round
+        const int segs = NT / m;                        // >= 1
+        const int sg = tid / m, r = tid - sg * m;
+        const bool on = sg < segs;
+        const int b0 = on ? (int)((int64_t)nb * sg / segs) : 0, b1 = on ? (int)((int64_t)nb * (sg + 1) / segs) : 0;
+        uint32_t* col = H + r0 + r;
+        uint32_t sum = 0;
+        for (int b = b0; b < b1; b += 8) {
+            uint32_t v[8];
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) v[q] = b0 + q < nb ? H[(size_t)(b0 + q) * stride + t] : 0u;
-                    __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
+            for (int q = 0; q < 8; ++q) v[q] = b + q < b1 ? col[(size_t)(b + q) * stride] : 0u;
 #pragma unroll
-                    for (int q = 0; q < 16; ++q) {
-                        if (b0 + q < nb) H[(size_t)(b0 + q) * stride + t] = o;
-                        o += v[q];
-                    }
-                }
+            for (int q = 0; q < 8; ++q) sum += v[q];
+        }
+        if (on) part[sg * m + r] = sum;
+        __syncthreads();
+        uint32_t below = 0, tot = 0;
+        for (int k = 0; k < segs; ++k) {
+            const uint32_t v = on ? part[k * m + r] : 0u;
+            below += k < sg ? v : 0u;
+            tot += v;
+        }
+        // row starts: a scan over the first segment's threads (rows in order)
+        uint32_t total;
+        const uint32_t start = done + block_excl_scan<NT>(sg == 0 ? tot : 0u, &total, lds16);
+        __syncthreads();
+        if (sg == 0) {
+            part[r] = start;
+            range[2 * (r0 + r)] = start;
+            range[2 * (r0 + r) + 1] = start + tot;
+        }
+        __syncthreads();
+        uint32_t o = (on ? part[r] : 0u) + below;
+        for (int b = b0; b < b1; b += 16) {
+            uint32_t v[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[q] = b + q < b1 ? col[(size_t)(b + q) * stride] : 0u;
+            __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                if (b + q < b1) col[(size_t)(b + q) * stride] = o;
+                o += v[q];
             }
         }
-        run += chunk_total;
+        done += total;
+        __syncthreads();
     }
-    return run;
+    return done;
 }
 
-__global__ __launch_bounds__(256) void k_tile_scan(ChunkDev c)
+// Per image: the tile ranges from the 2D prefix sums of its difference array
+// (taken into LDS once: the prefix sums' steps depend on each other, and in
+// memory each of them would wait for the one before), and the row lists.
+// Launches of few images use 1024 threads per image (the blocks' counts are
+// then summed by more segments), others 256.
+template <int NT>
+__global__ __launch_bounds__(NT) void k_tile_scan(ChunkDev c)
 {
-    __shared__ uint32_t lds8[8];
+    extern __shared__ int32_t gd[];     // [TY][P1]
+    __shared__ uint32_t lds16[16];
+    __shared__ uint32_t part[NT];
     const int i = blockIdx.x;
     const uint32_t V = c.n ? c.vis_count[i] : 0u;
-    const int nb = (int)((V + kTileGauss - 1) / kTileGauss);
+    const int nb = (int)((V + (uint32_t)c.tile_items - 1u) / (uint32_t)c.tile_items);
     const ImageInfo im = c.img[i];
     const int TX = im.tiles_x, TY = im.tiles_y, P1 = TX + 1;
-    // 2D prefix of the image's difference array (rows, then columns) gives
-    // the tile counts, in place; then the tile ranges by a scan in tile order
-    int32_t* gd = c.tile_hist + (size_t)i * (size_t)(c.tx_max + 1) * (c.ty_max + 1);
-    for (int y = threadIdx.x; y < TY; y += 256) {
+    const int32_t* hist = c.tile_hist + (size_t)i * (size_t)(c.tx_max + 1) * (c.ty_max + 1);
+    for (int t = threadIdx.x; t < TY * P1; t += NT) gd[t] = hist[t];
+    __syncthreads();
+    for (int y = threadIdx.x; y < TY; y += NT) {
         int32_t run = 0;
         for (int x = 0; x < TX; ++x) {
             run += gd[y * P1 + x];
@@ -275,7 +312,7 @@ __global__ __launch_bounds__(256) void k_tile_scan(ChunkDev c)
         }
     }
     __syncthreads();
-    for (int x = threadIdx.x; x < TX; x += 256) {
+    for (int x = threadIdx.x; x < TX; x += NT) {
         int32_t run = 0;
         for (int y = 0; y < TY; ++y) {
             run += gd[y * P1 + x];
@@ -285,19 +322,19 @@ __global__ __launch_bounds__(256) void k_tile_scan(ChunkDev c)
     __syncthreads();
     uint32_t* range = c.tile_range + (size_t)i * c.t_max * 2;
     uint32_t P = 0;
-    for (int t0 = 0; t0 < TX * TY; t0 += 256) {
+    for (int t0 = 0; t0 < TX * TY; t0 += NT) {
         const int t = t0 + threadIdx.x;
         const uint32_t cnt = t < TX * TY ? (uint32_t)gd[(t / TX) * P1 + (t % TX)] : 0u;
         uint32_t chunk_total;
-        const uint32_t start = P + block_excl_scan256(cnt, &chunk_total, lds8);
+        const uint32_t start = P + block_excl_scan<NT>(cnt, &chunk_total, lds16);
         if (t < TX * TY) {
             range[2 * t] = start;
             range[2 * t + 1] = start + cnt;
         }
         P += chunk_total;
     }
-    const uint32_t Rn = scan_bins(c.row_hist + (size_t)i * c.tile_blocks * c.ty_max, nb, c.ty_max, im.tiles_y,
-                                  c.row_range + (size_t)i * c.ty_max * 2, true, lds8);
+    const uint32_t Rn = scan_rows<NT>(c.row_hist + (size_t)i * c.tile_blocks * c.ty_max, nb, c.ty_max, TY,
+                                      c.row_range + (size_t)i * c.ty_max * 2, part, lds16);
     if (threadIdx.x == 0) {
         c.pair_count[i] = P;
         c.row_count[i] = Rn;
@@ -387,9 +424,9 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_row_scatter(ChunkDev c,
     const uint32_t L = xcd_remap(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y);
     const int i = (int)(L / gridDim.x), b = (int)(L - (uint32_t)i * gridDim.x) * kWavesPerBlock + wv;
     const uint32_t V = c.n ? c.vis_count[i] : 0u;
-    const uint32_t j0 = (uint32_t)b * kTileGauss;
+    const uint32_t j0 = (uint32_t)b * (uint32_t)c.tile_items;
     if (b >= c.tile_blocks || j0 >= V) return;     // wave-uniform; the waves of a block never wait on each other
-    const uint32_t j1 = min(j0 + (uint32_t)kTileGauss, V);
+    const uint32_t j1 = min(j0 + (uint32_t)c.tile_items, V);
     const ImageInfo im = c.img[i];
     const uint32_t TY = (uint32_t)im.tiles_y;
     const uint32_t* off = c.row_hist + ((size_t)i * c.tile_blocks + b) * c.ty_max;
@@ -516,11 +553,17 @@ __global__ __launch_bounds__(64) void k_rowseg_scan(ChunkDev c, int n_seg, uint3
     uint32_t* base = seg_off + ((size_t)i * c.ty_max + y) * n_seg * c.tx_max;
     for (int x = lane; x < TX; x += 64) {
         uint32_t run = tr[2 * x];
-        for (int sg = 0; sg < n_seg; ++sg) {
-            uint32_t* q = base + (size_t)sg * c.tx_max + x;
-            const uint32_t v = *q;
-            *q = run;
-            run += v;
+        // sixteen segments at a time: their loads all complete (one wait) before the stores
+        for (int s0 = 0; s0 < n_seg; s0 += 16) {
+            uint32_t v[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) v[q] = s0 + q < n_seg ? base[(size_t)(s0 + q) * c.tx_max + x] : 0u;
+            __builtin_amdgcn_s_waitcnt(0x0F70);     // vmcnt(0)
+#pragma unroll
+            for (int q = 0; q < 16; ++q) {
+                if (s0 + q < n_seg) base[(size_t)(s0 + q) * c.tx_max + x] = run;
+                run += v[q];
+            }
         }
     }
 }
@@ -789,7 +832,7 @@ __device__ __forceinline__ void line_finish(const LineLists<T>& L, uint32_t cur,
 __host__ __device__ constexpr size_t line_lds_bytes(int buckets) { return 1024 + 128 * (size_t)buckets; }
 
 // Level 1, schedule 1.  Block (gx, i), wave wv: task gx * kWavesPerBlock + wv
-// over (kTileGauss block b of image i's depth-ordered Gaussians, window of 64
+// over (block b of tile_items of image i's depth-ordered Gaussians, window of 64
 // tile rows); the block's rows start at its per-block row offsets.
 __global__ __launch_bounds__(64 * kWavesPerBlock) void k_row_rank(ChunkDev c, uint64_t n, int n_rw, int nb)
 {
@@ -801,9 +844,9 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_row_rank(ChunkDev c, ui
     const int i = (int)(L / gridDim.x), task = (int)(L - (uint32_t)i * gridDim.x) * kWavesPerBlock + wv;
     const int b = task / n_rw, rw = task - b * n_rw;
     const uint32_t V = c.n ? c.vis_count[i] : 0u;
-    const uint32_t j0 = (uint32_t)b * kTileGauss;
+    const uint32_t j0 = (uint32_t)b * (uint32_t)c.tile_items;
     if (b >= c.tile_blocks || j0 >= V) return;     // wave-uniform; the waves of a block never wait on each other
-    const uint32_t j1 = min(j0 + (uint32_t)kTileGauss, V);
+    const uint32_t j1 = min(j0 + (uint32_t)c.tile_items, V);
     const ImageInfo im = c.img[i];
     const uint32_t TY = (uint32_t)im.tiles_y, TX = (uint32_t)im.tiles_x;
     const uint32_t rbase = (uint32_t)rw * 64u;
@@ -938,11 +981,16 @@ hipError_t launch_tile_count(const SceneDev& s, const ChunkDev& c, hipStream_t s
     const uint64_t nd = (uint64_t)c.n_img * (uint64_t)(c.tx_max + 1) * (uint64_t)(c.ty_max + 1);
     hipLaunchKernelGGL(k_zero_diff, dim3((unsigned)((nd + 255) / 256)), dim3(256), 0, stream, c.tile_hist, nd);
     if (n > 0) {
-        const size_t lds = (size_t)((c.tx_max + 1) * (c.ty_max + 1) + c.ty_max + 1) * 4;
-        hipLaunchKernelGGL(k_tile_hist, dim3((unsigned)c.tile_blocks, (unsigned)c.n_img), dim3(256), lds, stream, c,
-                           n);
+        const size_t subs = (size_t)(kTileGauss / c.tile_items);
+        const size_t lds = ((size_t)(c.tx_max + 1) * (c.ty_max + 1) + subs * (c.ty_max + 1)) * 4;
+        hipLaunchKernelGGL(k_tile_hist, dim3((unsigned)((n + kTileGauss - 1) / kTileGauss), (unsigned)c.n_img),
+                           dim3(256), lds, stream, c, n);
     }
-    hipLaunchKernelGGL(k_tile_scan, dim3((unsigned)c.n_img), dim3(256), 0, stream, c);
+    const size_t scan_lds = (size_t)(c.tx_max + 1) * c.ty_max * 4;
+    if (c.n_img < 128)
+        hipLaunchKernelGGL(k_tile_scan<1024>, dim3((unsigned)c.n_img), dim3(1024), scan_lds, stream, c);
+    else
+        hipLaunchKernelGGL(k_tile_scan<256>, dim3((unsigned)c.n_img), dim3(256), scan_lds, stream, c);
     hipLaunchKernelGGL(k_image_scan, dim3(1), dim3(256), 0, stream, c);
     return hipGetLastError();
 }

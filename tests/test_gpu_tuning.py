@@ -285,3 +285,31 @@ def test_list_overflow_falls_back_with_identical_bits():
         for a, b in zip(ref, (rgb, depth, alpha, work)):
             assert torch.equal(a, b), f"render {k}"
     R.close()
+
+
+@pytest.mark.parametrize("n,envs,w,h,ts", [(255, 1, 100, 75, 16), (4097, 1, 100, 75, 16), (40_000, 1, 333, 47, 16),
+                                           (70_000, 3, 640, 200, 16), (600, 300, 64, 48, 16), (2_000, 1, 24, 8000, 8),
+                                           (1_500, 1, 112, 8192, 8)])
+def test_lists_at_every_launch_size(n, envs, w, h, ts):
+    """Tile lists against the specification where the list kernels change shape
+    with the launch: block lengths from one short block to many, one image and
+    hundreds, row counts beyond a scan's threads, and the tallest tile grids."""
+    _torch()
+    from oracle import bin_ref
+    from paper_2604_25459_amd import gsr
+    scene = synth.make_scene(n + h, n, 0, 0, sh_degree=0, half_box=2.0)
+    vm = synth.orbit_viewmats(np.random.default_rng(n), envs, 3.0, 5.0)
+    batch = synth.Batch(cams=[synth.pinhole(w, h, 60.0)], viewmats=vm[None], poses=np.zeros((envs, 0, 7), np.float32))
+    r = gsr.Renderer(0, tile_size=ts)
+    sid = r.add_synth_scene(scene)
+    cams, vm_t, poses = gsr.batch_tensors(batch)
+    for schedule in (0, 1):
+        r.set_tuning(sid, cams, vm_t, poses, bin_schedule=schedule)
+        for e in sorted({0, envs - 1}):
+            got = r.debug_bins(sid, cams, vm_t, poses, e)
+            ref = bin_ref(scene, batch, 0, e, ts)
+            assert got["n_visible"] == int(ref.visible.sum())
+            np.testing.assert_array_equal(got["keys"], ref.keys)
+            np.testing.assert_array_equal(got["values"], ref.values)
+            np.testing.assert_array_equal(got["ranges"], ref.ranges)
+    r.close()
