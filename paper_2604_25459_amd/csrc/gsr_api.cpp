@@ -92,7 +92,7 @@ Workspace::~Workspace()
     if (!fixed)
         for (DevBuf* b : {&img, &xform, &keyz, &rect, &srect, &rec, &sk0, &sk1, &sv0, &sv1, &sort_hist, &kmm, &vis_count,
                       &tile_hist, &tile_range, &pair_count, &pair_base, &pairs, &row_hist, &row_range, &row_count,
-                          &row_base, &rows, &debug, &stage_vm, &stage_pose, &stage_elev, &seg_off, &counter,
+                          &row_base, &rows, &debug, &stage_elev, &seg_off, &counter,
                           &ovf, &counter2})
             b->release();
     if (h_total) (void)hipHostFree(h_total);
@@ -190,8 +190,8 @@ void fill_images(const gsr_render_desc* d, int ts, int n_bodies, ImageInfo* v)
             im.guard_x = 1.3f * ((0.5f * (float)cam.width) / cam.fx);
             im.guard_y = 1.3f * ((0.5f * (float)cam.height) / cam.fy);
             im.key_tile_base = (uint32_t)tile_base;
-            im.vm_off = (uint32_t)(((size_t)c * E + e) * 12);
-            im.pose_off = (uint32_t)((size_t)e * n_bodies * 7);
+            im.viewmat = d->viewmats + ((size_t)c * E + e) * 12;
+            im.poses = n_bodies > 0 ? d->body_poses + (size_t)e * n_bodies * 7 : nullptr;
             im.bg[0] = d->bg[0];
             im.bg[1] = d->bg[1];
             im.bg[2] = d->bg[2];
@@ -313,6 +313,18 @@ WorkspaceSizes workspace_sizes(const SceneRes* sc, const ChunkPlan& p, size_t n_
     return z;
 }
 
+hipError_t alloc_totals(Workspace& ws)
+{
+    if (ws.h_total) return hipSuccess;
+    hipError_t e = hipHostMalloc((void**)&ws.h_total, 64, hipHostMallocDefault);
+    if (e != hipSuccess) {
+        ws.h_total = nullptr;
+        return e;
+    }
+    std::memset(ws.h_total, 0, 64);
+    return hipHostGetDevicePointer((void**)&ws.d_total, ws.h_total, 0);
+}
+
 hipError_t ensure_workspace(Workspace& ws, const SceneRes* sc, const ChunkPlan& p, size_t n_images_total,
                             size_t rec_bytes)
 {
@@ -320,9 +332,7 @@ hipError_t ensure_workspace(Workspace& ws, const SceneRes* sc, const ChunkPlan& 
     const WorkspaceSizes z = workspace_sizes(sc, p, n_images_total, rec_bytes);
     for (int k = 0; k < z.count; ++k)
         if ((e = (ws.*(z.b[k].buf)).ensure(z.b[k].bytes)) != hipSuccess) return e;
-    if (!ws.h_total) {
-        if ((e = hipHostMalloc((void**)&ws.h_total, 64, hipHostMallocDefault)) != hipSuccess) return e;
-    }
+    if ((e = alloc_totals(ws)) != hipSuccess) return e;
     if (ws.h_img_cap < n_images_total) {
         if (ws.h_img) (void)hipHostFree(ws.h_img);
         ws.h_img = nullptr;
@@ -417,6 +427,8 @@ ChunkDev chunk_view(Workspace& ws, const SceneRes* sc, const ChunkPlan& p, int i
     return c;
 }
 
+constexpr int kWholeChunk = 5;      // run_stage: all stages of an asynchronous chunk as one graph
+
 // One pipeline stage, launched eagerly or as a captured graph.  Graphs are
 // captured on the workspace's private stream (capture executes nothing) and
 // launched on the chunk's stream; a graph is re-captured when anything its
@@ -456,6 +468,41 @@ int run_stage(Workspace& ws, bool graph, int chunk_idx, int stage, uint64_t scen
     return GSR_OK;
 }
 
+// Launch parameters of the rasteriser for images [i0, i0 + n_img) of a job.
+int raster_params(gsr_ctx* ctx, Workspace& ws, const RenderJob& job, int i0, int n_img, RasterParams* out)
+{
+    const Tuning& tu = job.tune;
+    RasterParams& rp = *out;
+    rp = RasterParams{};
+    rp.ts = tu.ts;
+    rp.batch = tu.batch;
+    rp.persistent = tu.persistent;
+    rp.count_work = 0;
+    for (int k = 0; k < n_img; ++k) rp.count_work |= job.imgs[i0 + k].out_work != nullptr;
+    rp.persistent_blocks = ctx->cu_count * (tu.ts == 8 ? 16 : 4);
+    if (tu.persistent) {
+        if (!ws.fixed) GSR_HIP_TRY(ws.counter.ensure(256));
+        rp.counter = ws.counter.as<uint32_t>();
+    }
+    uint32_t blocks = 0;
+    const std::vector<ImageInfo>& imgs = job.imgs;
+    for (int k = 0; k < n_img;) {
+        const ImageInfo& a = imgs[i0 + k];
+        int m = k;
+        while (m < n_img && imgs[i0 + m].width == a.width && imgs[i0 + m].height == a.height) ++m;
+        if (rp.n_segs >= kMaxSegs) return fail(GSR_E_INVALID, "more than 8 image sizes in one chunk");
+        RasterSeg& sg = rp.segs[rp.n_segs++];
+        sg.first_tile = blocks;
+        sg.first_image = (uint32_t)k;
+        sg.n_images = (uint32_t)(m - k);
+        sg.tiles_per_image = (uint32_t)(a.tiles_x * a.tiles_y);
+        blocks += sg.n_images * sg.tiles_per_image;
+        k = m;
+    }
+    rp.n_blocks = blocks;
+    return GSR_OK;
+}
+
 }  // namespace
 
 // Enqueue the pipeline of images [i0, i0 + n_img) of `job` (image descriptions
@@ -469,6 +516,9 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
     c.ovf_count = ctx->d_err + 1;
     c.acc = reinterpret_cast<unsigned long long*>(ctx->d_err + 16);
     c.ovf = ws.ovf.as<uint32_t>();
+    c.host_totals = async_lists ? nullptr : ws.d_total;
+    c.host_ovf = reinterpret_cast<uint32_t*>(ws.d_total + 5);
+    c.fallback_counter = async_lists ? ws.counter2.as<uint32_t>() : nullptr;
     // synchronous lists: the host sizes the buffers from the totals, nothing overflows
     c.cap_pairs = async_lists ? ws.pairs.bytes / 4 : ~0ull;
     c.cap_rows = async_lists ? ws.rows.bytes / 8 : ~0ull;
@@ -521,8 +571,7 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
                                  (uint64_t)(uintptr_t)c.img, (uint64_t)n_img,
                                  (uint64_t)c.t_max, (uint64_t)c.tx_max, (uint64_t)c.ty_max, (uint64_t)c.sort_blocks,
                                  (uint64_t)c.tile_blocks, (uint64_t)c.tile_items, (uint64_t)tu.ts, (uint64_t)tu.batch, (uint64_t)tu.ipt,
-                                 (uint64_t)tu.persistent, (uint64_t)(uintptr_t)job.viewmats,
-                                 (uint64_t)(uintptr_t)job.poses, (uint64_t)(uintptr_t)ws.h_total,
+                                 (uint64_t)tu.persistent, (uint64_t)(uintptr_t)ws.d_total,
                                  (uint64_t)(ctx->opt.cutoff * 1.0e6f), (uint64_t)tu.bin, (uint64_t)async_lists,
                                  c.cap_pairs, c.cap_rows};
     if (graph) {
@@ -536,8 +585,37 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
             key.push_back(((uint64_t)job.imgs[i0 + k].width << 32) | (uint64_t)job.imgs[i0 + k].height);
     }
 
+    if (graph && async_lists && !prof && mode == Mode::kRender) {
+        // nothing of this chunk waits for the host: its stages are one graph
+        const int n_seg = ws.nseg_hint[chunk_idx];
+        const size_t seg_bytes =
+            n_seg > 1 ? (size_t)((uint64_t)n_img * (uint64_t)c.ty_max * (uint64_t)n_seg * (uint64_t)c.tx_max * 4) : 0;
+        if (ws.seg_off.bytes < seg_bytes)
+            return fail(GSR_E_INVALID, "asynchronous lists: segment offsets not planned");
+        c.pairs = ws.pairs.as<uint32_t>();
+        c.rows = ws.rows.as<uint2>();
+        uint32_t* seg_off = n_seg > 1 ? ws.seg_off.as<uint32_t>() : nullptr;
+        RasterParams rp{};
+        const int r = raster_params(ctx, ws, job, i0, n_img, &rp);
+        if (r) return r;
+        for (uint64_t v : {(uint64_t)(uintptr_t)c.pairs, (uint64_t)(uintptr_t)c.rows, (uint64_t)n_seg,
+                           (uint64_t)(uintptr_t)seg_off, (uint64_t)(uintptr_t)rp.counter, (uint64_t)rp.count_work,
+                           (uint64_t)(uintptr_t)c.fallback_counter})
+            key.push_back(v);
+        *pairs_total = 0;
+        return run_stage(ws, true, chunk_idx, kWholeChunk, sc->uid, key, st, [&](hipStream_t q) {
+            hipError_t e = launch_compose(s, c, q);
+            if (e == hipSuccess) e = launch_project(s, c, tu.ts, ctx->opt.cutoff, tu.ipt, q);
+            if (e == hipSuccess) e = launch_depth_sort(s, c, q);
+            if (e == hipSuccess) e = launch_tile_count(s, c, q);
+            if (e == hipSuccess) e = launch_tile_scatter(s, c, tu.bin, n_seg, seg_off, q);
+            if (e == hipSuccess) e = launch_raster(s, c, rp, q);
+            if (e == hipSuccess) e = launch_raster_fallback(s, c, rp, q);
+            return e;
+        });
+    }
     int rc = run_stage(ws, graph, chunk_idx, 0, sc->uid, key, st, [&](hipStream_t q) {
-        hipError_t e = launch_compose(s, c, job.viewmats, job.poses, q);
+        hipError_t e = launch_compose(s, c, q);
         if (e == hipSuccess)
             e = job.lidar ? launch_project_lidar(s, c, tu.ts, tu.ipt, q)
                           : launch_project(s, c, tu.ts, ctx->opt.cutoff, tu.ipt, q);
@@ -550,16 +628,7 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
     if (rc) return rc;
     if (prof) GSR_HIP_TRY(hipEventRecord(ev.e[2], st));
     rc = run_stage(ws, graph, chunk_idx, 2, sc->uid, key, st, [&](hipStream_t q) {
-        hipError_t e = launch_tile_count(s, c, q);
-        if (async_lists) return e;       // totals stay on the device
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(ws.h_total, c.pair_base + n_img, sizeof(uint64_t), hipMemcpyDeviceToHost, q);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(ws.h_total + 1, c.row_base + n_img, sizeof(uint64_t), hipMemcpyDeviceToHost, q);
-        if (e == hipSuccess)
-            e = hipMemcpyAsync(ws.h_total + 2, c.pair_base + n_img + 1, sizeof(uint64_t), hipMemcpyDeviceToHost, q);
-        if (e == hipSuccess) e = hipMemcpyAsync(ws.h_total + 3, c.err, sizeof(uint32_t), hipMemcpyDeviceToHost, q);
-        return e;
+        return launch_tile_count(s, c, q);       // the totals end up in the host's memory or stay on the device
     });
     if (rc) return rc;
     if (prof) GSR_HIP_TRY(hipEventRecord(ev.e[3], st));
@@ -575,7 +644,7 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
         GSR_HIP_TRY(hipEventRecord(ws.ev_total, st));
         GSR_HIP_TRY(hipEventSynchronize(ws.ev_total));
         // kernels of this or an earlier chunk met an entry their inputs cannot hold
-        const uint32_t err = reinterpret_cast<const uint32_t*>(ws.h_total + 3)[0];
+        const uint32_t err = (uint32_t)ws.h_total[3];
         if (err) {
             ctx->poisoned = true;
             char msg[160];
@@ -650,32 +719,7 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
     if (prof) GSR_HIP_TRY(hipEventRecord(ev.e[4], st));
 
     RasterParams rp{};
-    rp.ts = tu.ts;
-    rp.batch = tu.batch;
-    rp.persistent = tu.persistent;
-    rp.count_work = 0;
-    for (int k = 0; k < n_img; ++k) rp.count_work |= job.imgs[i0 + k].out_work != nullptr;
-    rp.persistent_blocks = ctx->cu_count * (tu.ts == 8 ? 16 : 4);
-    if (tu.persistent) {
-        if (!ws.fixed) GSR_HIP_TRY(ws.counter.ensure(256));
-        rp.counter = ws.counter.as<uint32_t>();
-    }
-    uint32_t blocks = 0;
-    const std::vector<ImageInfo>& imgs = job.imgs;
-    for (int k = 0; k < n_img;) {
-        const ImageInfo& a = imgs[i0 + k];
-        int m = k;
-        while (m < n_img && imgs[i0 + m].width == a.width && imgs[i0 + m].height == a.height) ++m;
-        if (rp.n_segs >= kMaxSegs) return fail(GSR_E_INVALID, "more than 8 image sizes in one chunk");
-        RasterSeg& sg = rp.segs[rp.n_segs++];
-        sg.first_tile = blocks;
-        sg.first_image = (uint32_t)k;
-        sg.n_images = (uint32_t)(m - k);
-        sg.tiles_per_image = (uint32_t)(a.tiles_x * a.tiles_y);
-        blocks += sg.n_images * sg.tiles_per_image;
-        k = m;
-    }
-    rp.n_blocks = blocks;
+    if ((rc = raster_params(ctx, ws, job, i0, n_img, &rp)) != GSR_OK) return rc;
     if (graph) {
         key.push_back((uint64_t)(uintptr_t)rp.counter);
         key.push_back((uint64_t)rp.count_work);
@@ -687,7 +731,7 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
         rc = run_stage(ws, graph, chunk_idx, 4, sc->uid, key, st, [&](hipStream_t q) {
             hipError_t e = launch_raster(s, c, rp, q);
             // asynchronous lists: the fallback composites the chunk if its lists overflowed (else it exits at once)
-            if (e == hipSuccess && async_lists) e = launch_raster_fallback(s, c, rp, ws.counter2.as<uint32_t>(), q);
+            if (e == hipSuccess && async_lists) e = launch_raster_fallback(s, c, rp, q);
             return e;
         });
     }
@@ -729,8 +773,8 @@ int render_job(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job_i
     bool two = two_streams && !plain && ctx->opt.overlap >= 0 && n_chunks > 1;
     // Asynchronous lists need a planning render of the same job shape on this
     // workspace (and its twin), whose list buffers and segment counts they
-    // reuse, and no overflow seen since: the counter's copy made at the end of
-    // this workspace's last render is read once that render has finished.
+    // reuse, and no overflow seen since: the word that the device sets when a
+    // chunk overflows is read once this workspace's last render has finished.
     std::vector<uint64_t> shape = {sc->uid, (uint64_t)plan.chunk, (uint64_t)job.imgs.size(), (uint64_t)job.tune.ts,
                                    (uint64_t)job.tune.batch, (uint64_t)job.tune.ipt, (uint64_t)job.tune.bin,
                                    (uint64_t)job.tune.persistent, (uint64_t)two, (uint64_t)ctx->list_cap};
@@ -746,28 +790,24 @@ int render_job(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job_i
                  ctx->opt.sync_lists >= 0 && ws.used && ws.plan_key == shape &&
                  (!two || (ws.twin && ws.twin->plan_key == shape));
     if (async && hipEventQuery(ws.ev_done) == hipSuccess) {
-        const uint32_t seen = reinterpret_cast<const uint32_t*>(ws.h_total + 5)[0];
-        if (seen != ctx->ovf_seen) {
-            ctx->ovf_seen = seen;
-            async = false;                              // a chunk overflowed: plan again (the buffers grow)
-        }
+        // a chunk of this workspace (or its twin) overflowed: plan again (the buffers grow)
+        for (Workspace* w : {&ws, two ? ws.twin.get() : nullptr})
+            if (w && w->h_total[5]) {
+                w->h_total[5] = 0;
+                async = false;
+            }
     }
     // synchronous renders may reallocate buffers: earlier work on this workspace must be finished
-    if (ws.used && !async) GSR_HIP_TRY(hipEventSynchronize(ws.ev_done));
+    if (ws.used && !async) {
+        GSR_HIP_TRY(hipEventSynchronize(ws.ev_done));
+        for (Workspace* w : {&ws, ws.twin.get()})
+            if (w && w->h_total) w->h_total[5] = 0;
+    }
     GSR_HIP_TRY(ensure_workspace(ws, sc, plan, job.imgs.size(), rec_bytes));
     // the staging buffer of the image descriptions is free once its last copy has run
     if (ws.used) GSR_HIP_TRY(hipEventSynchronize(ws.ev_staged));
-    // per-step inputs staged at fixed addresses, so captured graphs replay across steps
-    if (job.viewmats != ws.stage_vm.as<float>()) {
-        GSR_HIP_TRY(ws.stage_vm.ensure(std::max<size_t>(job.viewmat_floats, 1) * 4));
-        GSR_HIP_TRY(hipMemcpyAsync(ws.stage_vm.p, job.viewmats, job.viewmat_floats * 4, hipMemcpyDeviceToDevice, st));
-        job.viewmats = ws.stage_vm.as<float>();
-    }
-    if (job.pose_floats && job.poses != ws.stage_pose.as<float>()) {
-        GSR_HIP_TRY(ws.stage_pose.ensure(job.pose_floats * 4));
-        GSR_HIP_TRY(hipMemcpyAsync(ws.stage_pose.p, job.poses, job.pose_floats * 4, hipMemcpyDeviceToDevice, st));
-        job.poses = ws.stage_pose.as<float>();
-    }
+    // the descriptions (with the addresses of this step's inputs and outputs) are
+    // staged at a fixed address, so captured graphs replay across steps
     std::memcpy(ws.h_img, job.imgs.data(), job.imgs.size() * sizeof(ImageInfo));
     GSR_HIP_TRY(hipMemcpyAsync(ws.img.p, ws.h_img, job.imgs.size() * sizeof(ImageInfo), hipMemcpyHostToDevice, st));
     if (plain) job.tune.ipt = 1;
@@ -836,8 +876,6 @@ int render_job(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job_i
         if (ws.twin) ws.twin->plan_key.clear();
         return rc;
     }
-    // the overflow counter as of this render's end, read by a later render
-    GSR_HIP_TRY(hipMemcpyAsync(ws.h_total + 5, ctx->d_err + 1, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     GSR_HIP_TRY(hipEventRecord(ws.ev_done, st));
     ws.used = true;
     ws.last_stream = st;
@@ -900,10 +938,6 @@ int render_impl(gsr_ctx* ctx, const gsr_render_desc* d, void* stream, bool plain
         RenderJob job;
         job.tune = force ? *force : tuning_for(ctx, sc, d);
         job.imgs = images_of(d, job.tune.ts, sc->dev.n_bodies);
-        job.viewmats = d->viewmats;
-        job.poses = d->body_poses;
-        job.viewmat_floats = (size_t)d->n_cams * d->n_envs * 12;
-        job.pose_floats = (size_t)d->n_envs * sc->dev.n_bodies * 7;
         rc = render_job(ctx, *ws, sc, job, st, plain, true, true);
     }
     if (!rc) rc = mark_scene_use(ctx, sc, st);
@@ -939,8 +973,6 @@ int debug_run(gsr_ctx* ctx, const gsr_render_desc* d, int image, Mode mode, Scen
     job->tune.ipt = 1;
     job->tune.bin = tuning_for(ctx, sc, d).bin;     // the tile lists as the tuned renderer builds them
     job->imgs = images_of(d, ctx->opt.tile_size, sc->dev.n_bodies);
-    job->viewmats = d->viewmats;
-    job->poses = d->body_poses;
     *plan = plan_chunks(ctx, sc, job->imgs, true);
     GSR_HIP_TRY(ensure_workspace(*ws, sc, *plan, job->imgs.size()));
     std::memcpy(ws->h_img, job->imgs.data(), job->imgs.size() * sizeof(ImageInfo));
@@ -1425,8 +1457,8 @@ GSR_EXPORT int gsr_render_lidar(gsr_ctx* ctx, const gsr_lidar_desc* d, void* str
                 }
                 im.attach_body = L.attach_body;
                 im.key_tile_base = (uint32_t)tile_base;
-                im.vm_off = (uint32_t)(((size_t)l * E + e) * 12);
-                im.pose_off = (uint32_t)((size_t)e * B * 7);
+                im.viewmat = d->viewmats + ((size_t)l * E + e) * 12;
+                im.poses = B > 0 ? d->body_poses + (size_t)e * B * 7 : nullptr;
                 im.out_depth = d->out_range + ray_base;
                 im.out_alpha = d->out_hit ? d->out_hit + ray_base : nullptr;
                 tile_base += (uint64_t)tx * ty;
@@ -1439,10 +1471,6 @@ GSR_EXPORT int gsr_render_lidar(gsr_ctx* ctx, const gsr_lidar_desc* d, void* str
         std::stable_sort(job.imgs.begin(), job.imgs.end(), [](const ImageInfo& a, const ImageInfo& b) {
             return a.width != b.width ? a.width < b.width : a.height < b.height;
         });
-        job.viewmats = d->viewmats;
-        job.poses = d->body_poses;
-        job.viewmat_floats = (size_t)d->n_lidars * E * 12;
-        job.pose_floats = (size_t)E * B * 7;
         return render_job(ctx, *ws, sc, job, st, false, false, true);
     };
     rc = body();
@@ -1483,10 +1511,6 @@ GSR_EXPORT int gsr_debug_bins(gsr_ctx* ctx, const gsr_render_desc* d, int image,
         RenderJob job;
         job.tune = tuning_for(ctx, sc, d);
         job.imgs = images_of(d, job.tune.ts, sc->dev.n_bodies);
-        job.viewmats = d->viewmats;
-        job.poses = d->body_poses;
-        job.viewmat_floats = (size_t)d->n_cams * d->n_envs * 12;
-        job.pose_floats = (size_t)d->n_envs * sc->dev.n_bodies * 7;
         job.mode = Mode::kBins;
         DebugStop stop;
         stop.image = image;

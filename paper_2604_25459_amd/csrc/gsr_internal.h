@@ -30,8 +30,8 @@ struct ImageInfo {
     float fx, fy, cx, cy, near_plane;
     float guard_x, guard_y;   // Jacobian clamp of x/z, y/z: 1.3 * ((0.5 W) / fx), same in y (binary32)
     uint32_t key_tile_base;   // first global tile id of the image in its request (sort keys)
-    uint32_t vm_off;          // float offset of the image's world->camera [R | t] in the viewmat array
-    uint32_t pose_off;        // float offset of the image's env body poses [B][7] in the pose array
+    const float* viewmat;     // the image's world->camera [R | t] in the caller's viewmat array
+    const float* poses;       // the image's env body poses [B][7] in the caller's pose array (null without bodies)
     float bg[3];              // background colour of the image's request
     int attach_body;          // -1: viewmat is world->camera; b: viewmat is body-b->camera
     float* out_rgb;           // first pixel of the image: [H][W][3] or null
@@ -167,6 +167,13 @@ struct ChunkDev {
     uint64_t cap_pairs, cap_rows;
     uint32_t* ovf;             // device word of the workspace: 1 = this chunk's lists do not fit
     uint32_t* ovf_count;       // device counter of the context: overflowed chunks so far
+    // pinned host memory of the workspace, written by k_image_scan: the chunk's
+    // totals and the consistency bits (pairs, row entries, visible Gaussians,
+    // bits; null where the host does not wait for them), and a word set to 1
+    // when a chunk overflowed
+    uint64_t* host_totals;
+    uint32_t* host_ovf;
+    uint32_t* fallback_counter;   // kXcds tile counters of the fallback rasteriser, zeroed by k_image_scan (or null)
     unsigned long long* acc;   // device accumulators of the context: visible Gaussians, pairs, row entries
 };
 
@@ -216,8 +223,7 @@ constexpr int kMaxRowSegs = 128;
 
 // ------------------------------------------------------------ launchers
 // All launchers enqueue on `stream` and return hipGetLastError().
-hipError_t launch_compose(const SceneDev& s, const ChunkDev& c, const float* viewmats, const float* poses,
-                          hipStream_t stream);
+hipError_t launch_compose(const SceneDev& s, const ChunkDev& c, hipStream_t stream);
 hipError_t launch_project(const SceneDev& s, const ChunkDev& c, int ts, float cutoff, int img_per_thread,
                           hipStream_t stream);
 hipError_t launch_depth_sort(const SceneDev& s, const ChunkDev& c, hipStream_t stream);
@@ -250,9 +256,9 @@ struct RasterParams {
 hipError_t launch_raster_lidar(const SceneDev& s, const ChunkDev& c, const RasterParams& p, hipStream_t stream);
 hipError_t launch_raster(const SceneDev& s, const ChunkDev& c, const RasterParams& p, hipStream_t stream);
 // Fallback compositing of a chunk whose lists overflowed (a persistent grid
-// that exits at once when the chunk's lists fit); counter: kXcds words.
-hipError_t launch_raster_fallback(const SceneDev& s, const ChunkDev& c, const RasterParams& p, uint32_t* counter,
-                                  hipStream_t stream);
+// that exits at once when the chunk's lists fit; its tile counters are
+// ChunkDev::fallback_counter).
+hipError_t launch_raster_fallback(const SceneDev& s, const ChunkDev& c, const RasterParams& p, hipStream_t stream);
 
 // Scene upload: convert caller float32 attributes to resident storage.
 hipError_t launch_scene_convert(int storage, int64_t n, int64_t n_pad, int degree, const float* means,

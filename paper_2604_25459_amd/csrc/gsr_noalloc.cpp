@@ -104,7 +104,7 @@ int noalloc_setup(int device)
     if (!p) return fail(GSR_E_DEVICE, "allocation-free path: scratch array has no device address");
     d->ptr = static_cast<char*>(p);
     d->ws.fixed = true;
-    GSR_HIP_TRY(hipHostMalloc((void**)&d->ws.h_total, 64, hipHostMallocDefault));
+    GSR_HIP_TRY(alloc_totals(d->ws));
     GSR_HIP_TRY(hipHostMalloc((void**)&d->ws.h_img, (size_t)kMaxImages * sizeof(ImageInfo), hipHostMallocDefault));
     d->ws.h_img_cap = kMaxImages;
     GSR_HIP_TRY(hipEventCreateWithFlags(&d->ws.ev_total, hipEventDisableTiming));
@@ -126,10 +126,6 @@ int render_noalloc(gsr_ctx* ctx, NoallocDev& nd, SceneRes* sc, const gsr_render_
     job.tune.ipt = ctx->opt.images_per_thread;
     job.imgs.resize((size_t)n_img);           // within the reserved capacity: no allocation
     fill_images(d, job.tune.ts, sc->dev.n_bodies, job.imgs.data());
-    job.viewmats = d->viewmats;
-    job.poses = d->body_poses;
-    job.viewmat_floats = (size_t)d->n_cams * d->n_envs * 12;
-    job.pose_floats = (size_t)d->n_envs * sc->dev.n_bodies * 7;
 
     // sizes first, so that a call that can never fit enqueues nothing
     const size_t img_bytes = align_up((size_t)n_img * sizeof(ImageInfo));

@@ -76,10 +76,11 @@ struct StageGraph {
 // Working memory of one render call at a time.
 struct Workspace {
     DevBuf img, xform, keyz, rect, srect, rec, sk0, sk1, sv0, sv1, sort_hist, kmm, vis_count, tile_hist, tile_range,
-        pair_count, pair_base, pairs, row_hist, row_range, row_count, row_base, rows, debug, stage_vm, stage_pose,
-        stage_elev, seg_off;
+        pair_count, pair_base, pairs, row_hist, row_range, row_count, row_base, rows, debug, stage_elev, seg_off;
     uint64_t* h_total = nullptr;   // pinned: [0] pairs, [1] row entries, [2] visible Gaussians of the current chunk,
-                                   // [3] low word: the context's device consistency bits
+                                   // [3] the context's device consistency bits, [5] low word: 1 = a chunk overflowed
+                                   // (written by k_image_scan)
+    uint64_t* d_total = nullptr;   // device address of h_total
     ImageInfo* h_img = nullptr;    // pinned staging for image descriptions
     size_t h_img_cap = 0;
     float* h_elev = nullptr;       // pinned staging for LiDAR beam elevations
@@ -150,10 +151,6 @@ struct DebugStop {
 // that images of equal size are contiguous.
 struct RenderJob {
     std::vector<ImageInfo> imgs;
-    const float* viewmats = nullptr;   // base of ImageInfo::vm_off
-    const float* poses = nullptr;      // base of ImageInfo::pose_off
-    size_t viewmat_floats = 0;         // extent of the arrays above (staged into the workspace)
-    size_t pose_floats = 0;
     Tuning tune;
     bool lidar = false;                // LiDAR ray grids instead of camera images
     int64_t chunk_bytes = 0;           // working-memory budget of one chunk (0: the context's option)
@@ -188,6 +185,8 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
 // resolves the device address of its scratch array and allocates its pinned
 // staging, once per device.  Called by gsr_create.
 int noalloc_setup(int device);
+// The pinned totals of a workspace (zeroed) and their device address.
+hipError_t alloc_totals(Workspace& ws);
 
 // Enqueue the whole job on `st` (blocks once per chunk for its pair count);
 // `graphs` allows replaying captured stage graphs (batched path only);
@@ -222,7 +221,6 @@ struct gsr_ctx {
                                                       // at every synchronous chunk; [1] overflowed chunks
                                                       // (ChunkDev::ovf_count); from byte 64, three u64
                                                       // accumulators (ChunkDev::acc)
-    uint32_t ovf_seen = 0;                            // overflow count the host has acted on
     uint64_t list_cap = 0;                            // tests: list capacity (entries) of asynchronous chunks
     unsigned long long acc_base[3] = {0, 0, 0};       // accumulator values at the last stage-timer reset
     std::map<std::string, gsr::Tuning> tuned;         // shape class -> launch parameters

@@ -80,46 +80,10 @@ int render_batch(gsr_server* srv, Workspace& ws, hipStream_t st, const std::vect
     SceneRes* sc = batch.front()->scene;
     const int B = sc->dev.n_bodies;
     RenderJob job;
-    size_t vm_floats = 0, pose_floats = 0;
     for (Request* r : batch) {
-        vm_floats += (size_t)r->desc.n_cams * r->desc.n_envs * 12;
-        pose_floats += (size_t)r->desc.n_envs * B * 7;
-    }
-    const bool single = batch.size() == 1;
-    if (!single) {
-        GSR_HIP_TRY(ws.stage_vm.ensure(std::max<size_t>(vm_floats, 1) * 4));
-        GSR_HIP_TRY(ws.stage_pose.ensure(std::max<size_t>(pose_floats, 1) * 4));
-    }
-    size_t vm_at = 0, pose_at = 0;
-    for (Request* r : batch) {
-        std::vector<ImageInfo> imgs = images_of(&r->desc, ctx->opt.tile_size, B);
-        const size_t nvm = (size_t)r->desc.n_cams * r->desc.n_envs * 12;
-        const size_t npose = (size_t)r->desc.n_envs * B * 7;
-        if (!single) {
-            GSR_HIP_TRY(hipMemcpyAsync(ws.stage_vm.as<float>() + vm_at, r->desc.viewmats, nvm * 4,
-                                       hipMemcpyDeviceToDevice, st));
-            if (npose)
-                GSR_HIP_TRY(hipMemcpyAsync(ws.stage_pose.as<float>() + pose_at, r->desc.body_poses, npose * 4,
-                                           hipMemcpyDeviceToDevice, st));
-            for (ImageInfo& im : imgs) {
-                im.vm_off += (uint32_t)vm_at;
-                im.pose_off += (uint32_t)pose_at;
-            }
-        }
-        vm_at += nvm;
-        pose_at += npose;
+        const std::vector<ImageInfo> imgs = images_of(&r->desc, ctx->opt.tile_size, B);
         job.imgs.insert(job.imgs.end(), imgs.begin(), imgs.end());
     }
-    if (vm_at > 0xFFFFFFFFull || pose_at > 0xFFFFFFFFull) return fail(GSR_E_INVALID, "batch inputs too large");
-    if (single) {
-        job.viewmats = batch.front()->desc.viewmats;
-        job.poses = batch.front()->desc.body_poses;
-    } else {
-        job.viewmats = ws.stage_vm.as<float>();
-        job.poses = ws.stage_pose.as<float>();
-    }
-    job.viewmat_floats = vm_at;
-    job.pose_floats = pose_at;
     job.tune.ts = ctx->opt.tile_size;
     job.tune.batch = ctx->opt.tile_size == 8 ? 64 : 256;
     job.tune.ipt = ctx->opt.images_per_thread;

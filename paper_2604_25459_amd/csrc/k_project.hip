@@ -18,28 +18,32 @@
 #include "gsr_device.h"
 #include "gsr_wave.h"
 
+#include <algorithm>
+
 namespace gsr {
 namespace {
 
 // ---------------------------------------------------------------- compose
 // One thread per (image, body slot).  xform row: A (9, row-major), a (3),
-// camera centre expressed in the slot's local frame (3), unused (1).
-__global__ __launch_bounds__(256) void k_compose(SceneDev s, ChunkDev c, const float* __restrict__ viewmats,
-                                                 const float* __restrict__ poses)
+// camera centre expressed in the slot's local frame (3), unused (1).  The
+// launch also clears the chunk's tile-count differences (`n_diff` words, read
+// by k_tile_hist after the depth sort), which saves a launch of their own.
+__global__ __launch_bounds__(256) void k_compose(SceneDev s, ChunkDev c, uint64_t n_diff)
 {
     const int slots = s.n_bodies + 1;
     const int idx = blockIdx.x * blockDim.x + threadIdx.x;
+    for (uint64_t k = (uint64_t)idx; k < n_diff; k += (uint64_t)gridDim.x * blockDim.x) c.tile_hist[k] = 0;
     if (idx >= c.n_img * slots) return;
     const int i = idx / slots;
     const int slot = idx - i * slots;
     const ImageInfo im = c.img[i];
-    const float* vm = viewmats + im.vm_off;
+    const float* vm = im.viewmat;
     float Rc[9] = {vm[0], vm[1], vm[2], vm[4], vm[5], vm[6], vm[8], vm[9], vm[10]};
     float tc[3] = {vm[3], vm[7], vm[11]};
     if (im.attach_body >= 0) {
         // camera rides on a body: the viewmat is body->camera [R_o | t_o];
         // world->camera = R_o R_k^T, t_o - (R_o R_k^T) t_k (k = attach_body)
-        const float* pk = poses + im.pose_off + (size_t)im.attach_body * 7;
+        const float* pk = im.poses + (size_t)im.attach_body * 7;
         float Rk[9], RkT[9], Ro[9];
         quat_rot(pk[0], pk[1], pk[2], pk[3], Rk);
 #pragma unroll
@@ -70,7 +74,7 @@ __global__ __launch_bounds__(256) void k_compose(SceneDev s, ChunkDev c, const f
         out[15] = 0.0f;
         return;
     }
-    const float* p = poses + im.pose_off + (size_t)(slot - 1) * 7;
+    const float* p = im.poses + (size_t)(slot - 1) * 7;
     float Rb[9], A[9];
     quat_rot(p[0], p[1], p[2], p[3], Rb);
     mat3_mul(Rc, Rb, A);
@@ -378,11 +382,14 @@ __global__ __launch_bounds__(256) void k_scene_convert(int64_t n, int64_t n_pad,
 
 }  // namespace
 
-hipError_t launch_compose(const SceneDev& s, const ChunkDev& c, const float* viewmats, const float* poses,
-                          hipStream_t stream)
+hipError_t launch_compose(const SceneDev& s, const ChunkDev& c, hipStream_t stream)
 {
+    if (c.n_img == 0) return hipSuccess;
     const int total = c.n_img * (s.n_bodies + 1);
-    hipLaunchKernelGGL(k_compose, dim3((total + 255) / 256), dim3(256), 0, stream, s, c, viewmats, poses);
+    const uint64_t n_diff = (uint64_t)c.n_img * (uint64_t)(c.tx_max + 1) * (uint64_t)(c.ty_max + 1);
+    // blocks for the transforms, and enough to clear the differences a few words per thread
+    const uint64_t blocks = std::max<uint64_t>((total + 255) / 256, std::min<uint64_t>((n_diff + 1023) / 1024, 1024));
+    hipLaunchKernelGGL(k_compose, dim3((unsigned)blocks), dim3(256), 0, stream, s, c, n_diff);
     return hipGetLastError();
 }
 

@@ -534,7 +534,8 @@ __global__ __launch_bounds__(Layout<TS>::kThreads) void k_raster_persistent(Scen
 }
 
 // Fallback compositing of an overflowed chunk: persistent workgroups take the
-// chunk's tiles from per-XCD counters (as k_raster_persistent) and filter
+// chunk's tiles from per-XCD counters (as k_raster_persistent, zeroed by
+// k_image_scan) and filter
 // each tile's list from the depth-ordered Gaussians.  Exits at once when the
 // chunk's lists fit.
 template <int TS, bool COUNT>
@@ -603,11 +604,10 @@ hipError_t launch_batch(const SceneDev& s, const ChunkDev& c, const RasterParams
 
 }  // namespace
 
-hipError_t launch_raster_fallback(const SceneDev& s, const ChunkDev& c, const RasterParams& p, uint32_t* counter,
-                                  hipStream_t stream)
+hipError_t launch_raster_fallback(const SceneDev& s, const ChunkDev& c, const RasterParams& p, hipStream_t stream)
 {
     if (p.n_blocks == 0) return hipSuccess;
-    hipLaunchKernelGGL(k_zero_counter, dim3(1), dim3(64), 0, stream, counter);
+    uint32_t* counter = c.fallback_counter;
     const uint32_t grid = std::min<uint32_t>(p.n_blocks, (uint32_t)p.persistent_blocks);
     switch (p.ts) {
     case 8:

@@ -138,12 +138,6 @@ __device__ __forceinline__ void expand_group(ExpandLds& ex, uint64_t* occ, uint3
 // needed per image (the tile lists are written by rows), so the block's 2D
 // differences are added into the image's array; row counts are needed per
 // block (level-1 offsets), so each block writes its own.
-__global__ __launch_bounds__(256) void k_zero_diff(int32_t* __restrict__ d, uint64_t n)
-{
-    const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < n) d[i] = 0;
-}
-
 // One block per kTileGauss depth-ordered Gaussians: the image's tile counts (2D
 // differences) and, for each of its sub-blocks of tile_items, the row counts.
 __global__ __launch_bounds__(256) void k_tile_hist(ChunkDev c, uint64_t n)
@@ -380,8 +374,19 @@ __global__ __launch_bounds__(256) void k_image_scan(ChunkDev c)
     if (tid == 0) {
         const uint32_t over = tot[0] > c.cap_pairs || tot[1] > c.cap_rows ? 1u : 0u;
         *c.ovf = over;
-        if (over) atomicAdd(c.ovf_count, 1u);
+        if (over) {
+            atomicAdd(c.ovf_count, 1u);
+            __hip_atomic_store(c.host_ovf, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
+        // the totals go straight to the host's memory: four small copies and the gaps between them otherwise
+        if (c.host_totals) {
+            const uint64_t bits = *c.err;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                __hip_atomic_store(&c.host_totals[k], k < 3 ? tot[k] : bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        }
     }
+    if (c.fallback_counter && tid < kXcds) c.fallback_counter[tid] = 0u;
     uint64_t rp = part[0][tid], rr = part[1][tid];
     for (int k = 0; k < per; ++k) {
         const int i = tid * per + k;
@@ -978,8 +983,6 @@ hipError_t launch_tile_count(const SceneDev& s, const ChunkDev& c, hipStream_t s
 {
     if (c.n_img == 0) return hipSuccess;
     const uint64_t n = (uint64_t)s.n;
-    const uint64_t nd = (uint64_t)c.n_img * (uint64_t)(c.tx_max + 1) * (uint64_t)(c.ty_max + 1);
-    hipLaunchKernelGGL(k_zero_diff, dim3((unsigned)((nd + 255) / 256)), dim3(256), 0, stream, c.tile_hist, nd);
     if (n > 0) {
         const size_t subs = (size_t)(kTileGauss / c.tile_items);
         const size_t lds = ((size_t)(c.tx_max + 1) * (c.ty_max + 1) + subs * (c.ty_max + 1)) * 4;
