@@ -304,6 +304,11 @@ __device__ __forceinline__ float dot3(const float a[3], const float b[3])
     return fmaf(a[2], b[2], fmaf(a[1], b[1], a[0] * b[0]));
 }
 
+__device__ __forceinline__ float lane_value(float x, int lane)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
+
 // Smallest and largest x over the lanes with `on` set (the same in every lane).
 __device__ __forceinline__ void wave_range(float x, bool on, float* lo, float* hi)
 {
@@ -318,7 +323,7 @@ __device__ __forceinline__ void wave_range(float x, bool on, float* lo, float* h
 }
 
 // One workgroup per TS x TS tile of rays; batches of kLBatch records in LDS.
-// Culling, per wave, in two steps.  First the bound stored in the record.
+// Culling in two steps.  First the bound stored in the record.
 // Angular rays: the wave bounds its rays by a cone (axis = their normalised
 // mean direction, half-angle beta = the widest ray), and a Gaussian stays when
 // its own cone (half-angle alpha around its centre direction, as used for the
@@ -334,18 +339,22 @@ __device__ __forceinline__ void wave_range(float x, bool on, float* lo, float* h
 // is a quadratic in (u, v) that is <= 0 exactly where q <= Q, Q the value at
 // which alpha falls to 1/255.  A Gaussian whose quadratic stays above a bound
 // for its rounding on the rectangle of the live rays is taken by none of them.
+// The rectangle is taken per quarter of the wave (8 x 2 rays, sixteen lanes),
+// and each quarter walks its own list of survivors: one LDS read instruction
+// serves four records, and a Gaussian costs only the quarters that it may meet.
 // A 16 x 4 ray wave of a 32 x 1024 scan over 300k Gaussians of 0.03 m walks
-// 2900 candidates: the first step leaves 716, the second 300 to 400, of which
-// 286 are taken by some ray; evaluating one costs 45 vector instructions and
-// four 16-byte LDS reads (these bound the kernel), the second test about 110
-// instructions per 64 candidates.  With it 512 such scans take 21.2 instead of
-// 26.7 ms, 512 heightmaps of 64 x 64 rays 11.3 instead of 16.2, 64 rosette
-// scans of 24,576 rays 7.4 instead of 10.3.
+// 2900 candidates: the first step leaves 716, of which 286 are taken by some
+// ray; the quarters evaluate about 300 in turn, each 48 vector instructions and
+// four 16-byte LDS reads (these bound the kernel), the second test costs about
+// 250 instructions per 64 candidates.  512 such scans: 26.7 ms with the first
+// step alone, 21.2 with the second per wave, 20.8 per quarter; 512 heightmaps of
+// 64 x 64 rays 16.2, 11.3, 9.2 ms; 64 rosette scans of 24,576 rays 10.3, 7.1, 6.1 ms.
 template <int TS>
 struct LidarLds {
     float4 sr[kLidarRec][TS * TS];
     uint32_t live_w[2][TS * TS / 64];     // per wave: live rays left after a batch (by batch parity)
-    uint16_t pick[TS * TS / 64][TS * TS];  // per wave: the batch's candidates that the first step keeps
+    uint8_t pick[TS * TS / 64][TS * TS];        // per wave: the batch's candidates that the first step keeps
+    uint8_t quart[TS * TS / 64][4][TS * TS];    // per quarter of a wave: those that the second step keeps
 };
 
 template <int TS, bool GRID>
@@ -357,7 +366,10 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
     auto& sr = L_.sr;
     auto& live_w = L_.live_w;
     const int tid = threadIdx.x, lane = __lane_id();
-    const int col = tx * TS + (tid % TS), row = ty * TS + (tid / TS);
+    // a wave's rays: 16 x 4 of a 16 x 16 tile (8 x 8 of an 8 x 8 one), each quarter of the lanes 8 x 2 of them
+    const int quarter = lane >> 4;
+    const int col = tx * TS + (lane & 7) + (TS == 16 ? 8 * (quarter & 1) : 0);
+    const int row = ty * TS + ((lane >> 3) & 1) + (TS == 16 ? 4 * (tid >> 6) + 2 * (quarter >> 1) : 2 * quarter);
     const bool inside = col < im.width && row < im.height;
     // ray: origin o (grid; the sensor origin otherwise) and direction d
     float d[3] = {0.0f, 0.0f, GRID ? -1.0f : 0.0f};
@@ -424,25 +436,35 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
         ru = dot3(d, e1) * dw;
         rv = dot3(d, e2) * dw;
     }
-    // rectangle of the live rays' points, taken again whenever a quarter of
-    // them have stopped; the second step needs rays within about 45 degrees of
-    // the axis
-    float u0 = 0.0f, u1 = 0.0f, v0 = 0.0f, v1 = 0.0f;
+    // per quarter, the rectangle of the live rays' points, taken again whenever
+    // a quarter of them have stopped; the second step needs rays within about
+    // 45 degrees of the axis
+    float u0[4], u1[4], v0[4], v1[4];
     const bool tight = GRID || (cull && cb > 0.75f);
     auto live_rect = [&](bool on) {
-        wave_range(ru, on, &u0, &u1);
-        wave_range(rv, on, &v0, &v1);
-        const float pu = 4e-6f * (1.0f + fmaxf(fabsf(u0), fabsf(u1))), pv = 4e-6f * (1.0f + fmaxf(fabsf(v0), fabsf(v1)));
-        u0 -= pu;
-        u1 += pu;
-        v0 -= pv;
-        v1 += pv;
+        float r[4] = {on ? ru : 3.0e38f, on ? -ru : 3.0e38f, on ? rv : 3.0e38f, on ? -rv : 3.0e38f};
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+#pragma unroll
+            for (int m = 1; m < 16; m <<= 1) r[k] = fminf(r[k], __shfl_xor(r[k], m, 64));
+        }
+        const float pu = 4e-6f * (1.0f + fmaxf(fabsf(r[0]), fabsf(r[1])));
+        const float pv = 4e-6f * (1.0f + fmaxf(fabsf(r[2]), fabsf(r[3])));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            u0[q] = lane_value(r[0] - pu, 16 * q);
+            u1[q] = lane_value(pu - r[1], 16 * q);
+            v0[q] = lane_value(r[2] - pv, 16 * q);
+            v1[q] = lane_value(pv - r[3], 16 * q);
+        }
     };
 
+    const float um = fmaxf(fabsf(bx0), fabsf(bx1)), vm = fmaxf(fabsf(by0), fabsf(by1));     // grid: largest |u|, |v|
     bool live = inside;
     uint32_t rect_rays = (uint32_t)__popcll(__ballot(live));
-    if (tight) live_rect(live);
-    uint16_t* const pick = L_.pick[tid >> 6];
+    live_rect(live);
+    uint8_t* const pick = L_.pick[tid >> 6];
+    uint8_t (*const quart)[NT] = L_.quart[tid >> 6];
     float T = 1.0f, Rg = 0.0f;
     const float near = im.near_plane;
     const uint32_t* R = c.tile_range + ((size_t)i * c.t_max + t) * 2;
@@ -494,20 +516,22 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
                 }
             }
             const uint64_t kept = __ballot(keep);
-            if (keep) pick[n_pick + lanes_below(kept)] = (uint16_t)jl;
+            if (keep) pick[n_pick + lanes_below(kept)] = (uint8_t)jl;
             n_pick += (uint32_t)__popcll(kept);
         }
         wave_lds_sync();
+        uint32_t n_q[4] = {0u, 0u, 0u, 0u};
+        const uint64_t live_m = __ballot(live);
+        if (tight && 4u * (uint32_t)__popcll(live_m) <= 3u * rect_rays) {
+            rect_rays = (uint32_t)__popcll(live_m);
+            live_rect(live);
+        }
         for (uint32_t p0 = 0; p0 < n_pick && wave_live; p0 += 64) {
             const bool have = p0 + (uint32_t)lane < n_pick;
             const int jp = have ? (int)pick[p0 + (uint32_t)lane] : 0;
-            bool keep = have;
+            Quad2 qd = {};
+            float bound = 0.0f;
             if (tight) {
-                const uint32_t n_live = (uint32_t)__popcll(__ballot(live));
-                if (4u * n_live <= 3u * rect_rays) {
-                    rect_rays = n_live;
-                    live_rect(live);
-                }
                 const float4 m0 = sr[0][jp], m1 = sr[1][jp], m2 = sr[2][jp], m3 = sr[3][jp];
                 auto whiten = [&](const float x[3], float y[3]) {
                     y[0] = fmaf(m0.z, x[2], fmaf(m0.y, x[1], m0.x * x[0]));
@@ -519,8 +543,6 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
                 // q at which log2 alpha = log2(1/255), with a margin for the rays' own rounding
                 const float Q = fmaf(1.3862944f * 1.002f, m3.x - kLidarLogAlphaMin, 0.01f);
                 float a0[3], a1[3], a2[3];
-                Quad2 qd;
-                float bound;
                 if (GRID) {
 #pragma unroll
                     for (int k = 0; k < 3; ++k) {
@@ -536,7 +558,6 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
                     qd.b1 = fmaf(gc, g1, -dot3(cw, a1) * aa);
                     qd.b2 = fmaf(gc, g2, -dot3(cw, a2) * aa);
                     qd.f0 = fmaf(cc - Q, aa, -gc * gc);
-                    const float um = fmaxf(fabsf(u0), fabsf(u1)), vm = fmaxf(fabsf(v0), fabsf(v1));
                     bound = 2e-6f * aa * (cc + n1 * um * um + n2 * vm * vm);
                 } else {
                     whiten(w, a0);
@@ -552,8 +573,18 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
                     qd.f0 = fmaf(k, n0, -h0 * h0);
                     bound = cc > 2.0f * Q ? 2e-6f * cc * (n0 + n1 + n2) : INFINITY;      // the sensor well outside
                 }
-                keep = have && !above_on_rect(qd, u0, u1, v0, v1, bound);
             }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (((live_m >> (16 * q)) & 0xFFFFull) == 0ull) continue;       // wave-uniform
+                const bool keep = have && !(tight && above_on_rect(qd, u0[q], u1[q], v0[q], v1[q], bound));
+                const uint64_t kept = __ballot(keep);
+                if (keep) quart[q][n_q[q] + lanes_below(kept)] = (uint8_t)jp;
+                n_q[q] += (uint32_t)__popcll(kept);
+            }
+        }
+        wave_lds_sync();
+        {
             // survivors two at a time: both are evaluated (independent
             // dependency chains the wave interleaves), then composited in list order
             auto eval = [&](int j, float* ts_out, float* la_out) {
@@ -600,19 +631,19 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
                     }
                 }
             };
-            uint64_t mask = __ballot(keep);
-            while (mask) {
-                const int j0 = __builtin_amdgcn_readlane(jp, (int)__builtin_ctzll(mask));
-                mask &= mask - 1ull;
-                const bool two = mask != 0ull;                  // wave-uniform
-                const int j1 = two ? __builtin_amdgcn_readlane(jp, (int)__builtin_ctzll(mask)) : j0;
-                if (two) mask &= mask - 1ull;
-                if (!live) continue;
+            // each quarter walks its own list: the reads of a pair of records
+            // take the same LDS instructions as one list for the wave would
+            const uint32_t my_n = quarter == 0 ? n_q[0] : quarter == 1 ? n_q[1] : quarter == 2 ? n_q[2] : n_q[3];
+            const uint32_t most = max(max(n_q[0], n_q[1]), max(n_q[2], n_q[3]));
+            for (uint32_t k = 0; k < most; k += 2) {
+                const uint32_t jj = *reinterpret_cast<const uint16_t*>(&quart[quarter][k]);
+                if (!live || k >= my_n) continue;
+                const int j0 = (int)(jj & (uint32_t)(NT - 1)), j1 = (int)((jj >> 8) & (uint32_t)(NT - 1));
                 float t0, l0, t1, l1;
                 eval(j0, &t0, &l0);
                 eval(j1, &t1, &l1);
                 take(t0, l0);
-                if (two) take(t1, l1);
+                if (k + 1 < my_n) take(t1, l1);
             }
             if (__ballot(live) == 0ull) wave_live = false;
         }
