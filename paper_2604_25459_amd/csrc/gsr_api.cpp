@@ -656,16 +656,19 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
         total = ws.h_total[0];
         row_total = ws.h_total[1];
         *pairs_total = total;
-        // segments per tile-row list: enough level-2 waves for the launch, none shorter than kRowSegEntries
+        // segments per tile-row list (see kLevel2Rows)
         const uint64_t per_row = n_rows ? row_total / n_rows : 0;
-        uint64_t by_len = std::max<uint64_t>(1, per_row / kRowSegEntries), most = 32;
-        uint64_t by_waves = n_rows ? ((uint64_t)kLevel2Waves + n_rows - 1) / n_rows : 1;
-        if (n_rows * std::min(by_len, most) < (uint64_t)kLevel2FewWaves) {
+        uint64_t by_len = std::max<uint64_t>(1, per_row / kRowSegEntries), waves = (uint64_t)kLevel2Waves;
+        if (n_rows * by_len < (uint64_t)kLevel2FewWaves) {
             by_len = std::max<uint64_t>(1, per_row / kRowSegEntriesFew);
-            by_waves = n_rows ? ((uint64_t)kLevel2FewWaves + n_rows - 1) / n_rows : 1;
-            most = kMaxRowSegs;
+            waves = (uint64_t)kLevel2FewWaves;
         }
-        n_seg = (int)std::min<uint64_t>(most, std::min(by_len, by_waves));
+        const uint64_t by_waves = n_rows == 0 || n_rows >= (uint64_t)kLevel2Rows ? 1 : (waves + n_rows - 1) / n_rows;
+        n_seg = (int)std::min<uint64_t>(kMaxRowSegs, std::min(by_len, by_waves));
+        // a fixed list region: no segments where their offsets would not fit beside the lists
+        const uint64_t lists = ((total * 4 + 255) & ~255ull) + ((row_total * 8 + 255) & ~255ull);
+        while (ws.fixed && n_seg > 1 && lists + n_rows * (uint64_t)n_seg * (uint64_t)c.tx_max * 4 > ws.list_bytes)
+            n_seg /= 2;
         if ((int)ws.nseg_hint.size() <= chunk_idx) ws.nseg_hint.resize((size_t)chunk_idx + 1, 1);
         ws.nseg_hint[chunk_idx] = n_seg;
     }

@@ -208,16 +208,19 @@ inline int tile_items_for(uint64_t n, uint64_t n_img, int tx_max, int ty_max)
         items /= 2;
     return items;
 }
-// Level 2 runs one wave per (image, tile row, segment).  Tile-row lists are
-// cut into segments only as far as the launch needs to have about
-// kLevel2Waves waves, and never into segments shorter than kRowSegEntries:
-// every extra segment costs a per-segment count pass over its entries, and
-// many short waves crowd out a rasteriser running beside them.  A launch that
-// would stay below kLevel2FewWaves waves that way takes segments of down to
-// kRowSegEntriesFew entries instead: there the longest wave is what it waits for.
-constexpr int kRowSegEntries = 1024;
+// Level 2 runs one wave per (image, tile row, segment).  A launch that has
+// kLevel2Rows tile rows takes each as one segment: an extra segment costs a
+// count pass over its entries.  Fewer rows are cut into kLevel2Waves segments of
+// at least kRowSegEntries entries: the entries are in depth order, so a row's
+// first segments hold the widest rectangles and take several times as long as
+// its last ones, and short segments keep the launch from waiting for those (512
+// scans of 32 x 1024 rays, 1024 rows: 3.6 ms with 16 segments per row, 2.1 with
+// 128).  A launch that would stay below kLevel2FewWaves waves takes segments of
+// down to kRowSegEntriesFew entries: there the longest wave is what it waits for.
+constexpr int kRowSegEntries = 512;
 constexpr int kRowSegEntriesFew = 256;
-constexpr int kLevel2Waves = 16384;
+constexpr int kLevel2Rows = 16384;
+constexpr int kLevel2Waves = 131072;
 constexpr int kLevel2FewWaves = 4096;
 constexpr int kMaxRowSegs = 128;
 

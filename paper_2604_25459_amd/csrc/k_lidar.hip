@@ -52,28 +52,49 @@ __device__ __forceinline__ int first_at_least(const float* v, int H, float x, bo
     return lo;
 }
 
-// Columns c in [0, W) whose ray azimuth az0 + (c + 0.5) step lies in
-// [a0, a1] (radians, a1 - a0 < 2 pi); returns an empty range when none.
-__device__ __forceinline__ void column_range(float a0, float a1, float az0, float step, int W, int* c0, int* c1)
+// Rows [r0, r1) with lo[r] >= a (r0) and hi[r] > b (r1): both binary searches
+// over H ascending values step for step, so each waits for one pair of reads
+// per halving.
+__device__ __forceinline__ void rows_between(const float* lo, const float* hi, int H, float a, float b, int* r0, int* r1)
 {
-    const float lo = (a0 - az0) / step - 0.5f;
-    const float hi = (a1 - az0) / step - 0.5f;
-    int x0 = (int)ceilf(fmaxf(lo, -1.0f));
-    int x1 = (int)floorf(fminf(hi, (float)W)) + 1;
-    x0 = max(x0, 0);
-    x1 = min(x1, W);
-    *c0 = x0;
-    *c1 = x1;
+    int p = 0, q = 0;
+    for (int step = 1 << (31 - __builtin_clz((unsigned)H)); step > 0; step >>= 1) {     // H is the same in every lane
+        const int pn = p + step, qn = q + step;
+        const float x = lo[min(pn, H) - 1], y = hi[min(qn, H) - 1];
+        if (pn <= H && x < a) p = pn;
+        if (qn <= H && y <= b) q = qn;
+    }
+    *r0 = p;
+    *r1 = q;
 }
 
-// Grid rays with index k in [0, n) whose origin c0 + (k + 0.5) step lies in
-// [a0, a1]; an empty range when none.
-__device__ __forceinline__ void column_range_grid(float a0, float a1, float c0, float step, int n, int* k0, int* k1)
+// Rectangles, cones and the azimuth window are bounds (any ray tile too many
+// costs time only), so their angles come from polynomials, with kAngleSlack
+// added against their errors: asin x = pi/2 - sqrt(1 - x) P3(x) (Abramowitz and
+// Stegun 4.4.45, 6.8e-5) and an odd fit of atan on [0, 1] (1.2e-5).
+constexpr float kAngleSlack = 1.5e-4f;
+__device__ __forceinline__ float asin_poly(float x)       // x in [0, 1]
 {
-    const float lo = (a0 - c0) / step - 0.5f;
-    const float hi = (a1 - c0) / step - 0.5f;
-    int x0 = (int)ceilf(fmaxf(lo, -1.0f));
-    int x1 = (int)floorf(fminf(hi, (float)n)) + 1;
+    const float p = fmaf(x, fmaf(x, fmaf(x, -0.0187293f, 0.0742610f), -0.2121144f), 1.5707288f);
+    return fmaf(-__builtin_amdgcn_sqrtf(fmaxf(0.0f, 1.0f - x)), p, kHalfPi);
+}
+__device__ __forceinline__ float atan2_poly(float y, float x)
+{
+    const float ax = fabsf(x), ay = fabsf(y);
+    const float t = fminf(ax, ay) * __builtin_amdgcn_rcpf(fmaxf(fmaxf(ax, ay), 1e-30f)), t2 = t * t;
+    float r = t * fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, 0.02084509f, -0.0851563f), 0.18015926f), -0.33030478f), 0.99986633f);
+    r = ay > ax ? kHalfPi - r : r;
+    r = x < 0.0f ? 2.0f * kHalfPi - r : r;
+    return y < 0.0f ? -r : r;
+}
+
+// Columns c in [0, n) with c0 + (c + 0.5) step in [a, b], both given in columns
+// (less c0 and divided by the step); an empty range when none.  The products
+// with an approximate 1 / step are off by less than 0.01 of a column (8192 of
+// them, twice over); 0.02 is allowed for.
+__device__ __forceinline__ void columns_between(float a, float b, int n, int* k0, int* k1)
+{
+    const int x0 = (int)ceilf(fmaxf(a - 0.52f, -1.0f)), x1 = (int)floorf(fminf(b - 0.48f, (float)n)) + 1;
     *k0 = max(x0, 0);
     *k1 = min(x1, n);
 }
@@ -141,7 +162,9 @@ __global__ __launch_bounds__(256) void k_project_lidar(SceneDev s, ChunkDev c, c
         const float tz = ((A[6] * mu[0] + A[7] * mu[1]) + A[8] * mu[2]) + X[11];
         const bool grid = im.kind == 2;
         // key: centre distance (angular), depth of the centre below the sensor plane (grid)
-        const float D = grid ? (-tz > 0.0f ? -tz : 0.0f) : sqrtf((tx * tx + ty * ty) + tz * tz);
+        const float d2 = (tx * tx + ty * ty) + tz * tz;
+        float D = grid ? (-tz > 0.0f ? -tz : 0.0f) : sqrt_rn(d2);
+        if (!grid && __ballot(!(d2 > 0x1p-100f && d2 < 0x1p126f)) != 0ull) D = sqrtf(d2);
         const size_t o = (size_t)i * (size_t)s.n + (size_t)g;
         bool ok = valid && isfinite(tx) && isfinite(ty) && isfinite(tz) && op >= 1.0f / 255.0f && isfinite(D) &&
                   sc[0] > 0.0f && sc[1] > 0.0f && sc[2] > 0.0f;
@@ -155,8 +178,9 @@ __global__ __launch_bounds__(256) void k_project_lidar(SceneDev s, ChunkDev c, c
             ok = ok && tz < rho;
             disc = rho * 1.0001f + 1e-6f * ((((1.0f + fabsf(tx)) + fabsf(ty)) + fabsf(im.gx0)) + fabsf(im.gy0));
             if (ok) {
-                column_range_grid(tx - disc, tx + disc, im.gx0, im.gdx, im.width, &c0, &c1);
-                column_range_grid(ty - disc, ty + disc, im.gy0, im.gdy, im.height, &r0, &r1);
+                const float ix = __builtin_amdgcn_rcpf(im.gdx), iy = __builtin_amdgcn_rcpf(im.gdy);
+                columns_between(((tx - disc) - im.gx0) * ix, ((tx + disc) - im.gx0) * ix, im.width, &c0, &c1);
+                columns_between(((ty - disc) - im.gy0) * iy, ((ty + disc) - im.gy0) * iy, im.height, &r0, &r1);
             }
         } else if ((ok = ok && D > 0.0f)) {
             if (D <= rho * 1.001f + 1e-6f) {            // the sensor may sit inside: every ray
@@ -165,27 +189,26 @@ __global__ __launch_bounds__(256) void k_project_lidar(SceneDev s, ChunkDev c, c
                 c0 = 0;
                 c1 = im.width;
             } else {
-                const float ang = asinf(rho / D) * 1.0001f + 2e-6f;
-                cone_c = cosf(ang);
-                const float el = asinf(fminf(1.0f, fmaxf(-1.0f, tz / D)));
-                if (im.kind == 3) {
-                    // bands whose elevation span [lo, hi] meets [el - ang, el + ang]
-                    r0 = first_at_least(ev + im.height, im.height, el - ang, false);   // hi >= el - ang
-                    r1 = first_at_least(ev, im.height, el + ang, true);                // lo <= el + ang
-                } else {
-                    r0 = first_at_least(ev, im.height, el - ang, false);   // rows with el - ang <= elev
-                    r1 = first_at_least(ev, im.height, el + ang, true);    // ... <= el + ang
-                }
-                if (fabsf(el) + ang >= kHalfPi - 1e-4f) {
+                // sine and cosine of the cone's half-angle (widened), of the centre's elevation and of their sum
+                const float iD = rcp_rn(D);
+                const float sa = fminf(1.0f, fmaf(rho * iD, 1.0002f, 4e-6f));
+                const float ca = __builtin_amdgcn_sqrtf(fmaxf(0.0f, fmaf(-sa, sa, 1.0f)));
+                const float se = fminf(1.0f, fabsf(tz) * iD);
+                const float ce = __builtin_amdgcn_sqrtf(fmaxf(0.0f, fmaf(-se, se, 1.0f)));
+                const float cs = fmaf(ce, ca, -se * sa);
+                cone_c = ca;
+                // towards the poles the elevation is as uncertain as se / ce
+                const float ang = asin_poly(sa) + kAngleSlack + 5e-7f * __builtin_amdgcn_rcpf(fmaxf(ce, 5e-4f));
+                const float el = copysignf(asin_poly(se), tz);
+                // angular: rows with |elevation - el| <= ang; listed rays: bands whose [smallest, largest] meets that
+                rows_between(im.kind == 3 ? ev + im.height : ev, ev, im.height, el - ang, el + ang, &r0, &r1);
+                if (cs <= 0.02f) {                          // the cone reaches (almost) over the pole
                     c0 = 0;
                     c1 = im.width;
                 } else {
-                    const float daz = asinf(fminf(1.0f, sinf(ang) / cosf(fabsf(el) + ang))) * 1.0001f + 2e-6f;
-                    const float th = atan2f(ty, tx);
-                    if (2.0f * daz >= kTwoPi - 1e-4f) {
-                        c0 = 0;
-                        c1 = im.width;
-                    } else if (im.kind == 3) {
+                    const float daz = asin_poly(fminf(1.0f, fmaf(sa * 1.002f, __builtin_amdgcn_rcpf(cs), 1e-5f))) + 2.0f * kAngleSlack;
+                    const float th = atan2_poly(ty, tx);
+                    if (im.kind == 3) {
                         // per tile row of the bands, the ray tiles whose azimuth span
                         // [smallest, largest] meets the window, at each 2 pi shift that
                         // meets [-pi, pi]; the hull over the tile rows, in rays
@@ -210,12 +233,13 @@ __global__ __launch_bounds__(256) void k_project_lidar(SceneDev s, ChunkDev c, c
                         c1 = min(im.width, hi * ts);
                     } else {
                         // the azimuth window, tested at its three 2 pi shifts; the hull of the hits
+                        const float is = __builtin_amdgcn_rcpf(im.az_step), turn = kTwoPi * is;
+                        const float wa = ((th - daz) - im.az0) * is, wb = ((th + daz) - im.az0) * is;
                         int lo = im.width, hi = 0;
 #pragma unroll
                         for (int k = -1; k <= 1; ++k) {
                             int a, b;
-                            column_range(th - daz + (float)k * kTwoPi, th + daz + (float)k * kTwoPi, im.az0,
-                                         im.az_step, im.width, &a, &b);
+                            columns_between(fmaf((float)k, turn, wa), fmaf((float)k, turn, wb), im.width, &a, &b);
                             if (a < b) {
                                 lo = min(lo, a);
                                 hi = max(hi, b);
@@ -253,7 +277,7 @@ __global__ __launch_bounds__(256) void k_project_lidar(SceneDev s, ChunkDev c, c
             if (grid) {
                 r[4] = make_float4(tx, ty, disc, 0.0f);
             } else {
-                const float iD = 1.0f / D;
+                const float iD = __builtin_amdgcn_rcpf(D);
                 r[4] = make_float4(tx * iD, ty * iD, tz * iD, cone_c);
             }
         }

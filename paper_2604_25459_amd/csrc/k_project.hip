@@ -239,7 +239,11 @@ __global__ __launch_bounds__(256) void k_project(SceneDev s, ChunkDev c, const I
 
         const float fx = im.fx, fy = im.fy;
         const float lx = im.guard_x, ly = im.guard_y;
-        const float itz = 1.0f / tz;            // the one division by depth; products below
+        // The one division by depth; products below.  Depths that are not
+        // positive normals are culled whatever they give here; those past 2^126
+        // (and a wave that holds one) take the full division.
+        float itz = rcp_rn(tz);
+        if (__ballot(tz > 0x1p126f) != 0ull) itz = 1.0f / tz;
         const float itz2 = itz * itz;
         const float xcl = fminf(lx, fmaxf(-lx, tx * itz)) * tz;
         const float ycl = fminf(ly, fmaxf(-ly, ty * itz)) * tz;
@@ -264,13 +268,15 @@ __global__ __launch_bounds__(256) void k_project(SceneDev s, ChunkDev c, const I
         const float det = (((w0 * w0 + w1 * w1) + w2 * w2) + 0.3f * (n1 + n2)) + 0.09f;
         const float m = 0.5f * (ca + cc);
         const float h = 0.5f * (ca - cc);
-        const float lam = m + sqrtf(fmaxf(0.1f, h * h + cb * cb));
-        const float r = ceilf(cutoff * sqrtf(lam));
+        // arguments of at least 0.1: a finite one takes no part of sqrtf's range handling, and an infinite
+        // one leaves r NaN or infinite (culled) or loses against r below, as with sqrtf
+        const float lam = m + sqrt_rn(fmaxf(0.1f, h * h + cb * cb));
+        const float r = ceilf(cutoff * sqrt_rn(lam));
         const float u = (fx * tx) * itz + im.cx;
         const float v = (fy * ty) * itz + im.cy;
         // tighter of the radius square and the box of the ellipse q <= qmax
-        const float rx = fminf(r, sqrtf(qmax * ca));
-        const float ry = fminf(r, sqrtf(qmax * cc));
+        const float rx = fminf(r, sqrt_rn(qmax * ca));
+        const float ry = fminf(r, sqrt_rn(qmax * cc));
         const float x0 = fminf(fmaxf(floorf((u - rx) * inv_ts), 0.0f), (float)im.tiles_x);
         const float x1 = fminf(fmaxf(floorf((u + rx) * inv_ts) + 1.0f, 0.0f), (float)im.tiles_x);
         const float y0 = fminf(fmaxf(floorf((v - ry) * inv_ts), 0.0f), (float)im.tiles_y);

@@ -365,3 +365,56 @@ def test_ellipsoid_culling_matches_oracle(ts, shape):
             _compare(out[l][0][e].cpu().numpy(), out[l][1][e].cpu().numpy(), ref, f"{shape} ts {ts} slot {l} env {e}",
                      scene, batch, l, e, min_hits=1)
     r.close()
+
+
+@pytest.mark.parametrize("el_lo,el_hi,az0,width", [(-89.0, 89.0, -180.0, 360), (86.0, 89.9, 10.0, 90),
+                                                   (-60.0, 20.0, -7.0, 8192)])
+def test_angular_bounds_at_poles_and_many_columns(R, el_lo, el_hi, az0, width):
+    """Beams near the poles, a turn that starts anywhere and the widest scan:
+    the projection's angular bounds leave out no ray that takes a Gaussian."""
+    rng = np.random.default_rng(width)
+    n = 600
+    d = rng.standard_normal((n, 3)) * [1, 1, 2.5]
+    means = d / np.linalg.norm(d, axis=1, keepdims=True) * rng.uniform(0.3, 4.0, (n, 1))
+    scene = scene_from(means, 0.05 * np.exp(0.5 * rng.standard_normal((n, 3))), quats=rng.standard_normal((n, 4)),
+                       opac=rng.uniform(0.1, 0.99, n), degree=0)
+    el = np.radians(np.linspace(el_lo, el_hi, 7)).astype(np.float32)
+    span = 2.0 * math.pi if width != 90 else 0.5 * math.pi
+    lid = synth.LidarSpec(width=width, height=7, az0=float(np.float32(math.radians(az0))),
+                          az_step=float(np.float32(span / width)), elevations=el, near_range=0.05)
+    vm = np.concatenate([np.eye(3), np.zeros((3, 1))], axis=1).astype(np.float32).reshape(1, 1, 3, 4)
+    batch = synth.LidarBatch(cams=[lid], viewmats=vm, poses=np.zeros((1, 0, 7), np.float32))
+    sid = R.add_synth_scene(scene)
+    out = R.render_lidar(sid, [lid], *_tensors(batch))
+    ref = lidar_ref(scene, batch, 0, 0)
+    _compare(out[0][0][0].cpu().numpy(), out[0][1][0].cpu().numpy(), ref, f"el {el_lo}..{el_hi}", scene, batch, 0, 0)
+    R.remove_scene(sid)
+
+
+def test_rounded_roots_and_reciprocals_match_the_specification(R):
+    """Projected keys, rectangles and radii of Gaussians over forty decades of
+    depth and size: the shortened square roots and the reciprocal of depth
+    round as the specification's do."""
+    from oracle.spec32 import project32
+    from paper_2604_25459_amd import gsr
+    rng = np.random.default_rng(9)
+    n = 20_000
+    z = np.exp(rng.uniform(math.log(1e-4), math.log(1e30), n))
+    xy = rng.uniform(-0.4, 0.4, (n, 2)) * z[:, None]
+    means = np.concatenate([xy, z[:, None]], axis=1)
+    scales = np.exp(rng.uniform(math.log(1e-6), math.log(2.0), (n, 3))) * z[:, None]
+    scene = scene_from(means, scales, quats=rng.standard_normal((n, 4)), opac=rng.uniform(0.0, 1.0, n), degree=0)
+    vm = np.concatenate([np.eye(3), np.zeros((3, 1))], axis=1).astype(np.float32).reshape(1, 1, 3, 4)
+    batch = synth.Batch(cams=[synth.pinhole(640, 480, 60.0)], viewmats=vm, poses=np.zeros((1, 0, 7), np.float32))
+    sid = R.add_synth_scene(scene)
+    cams, vm_t, poses = gsr.batch_tensors(batch)
+    got = R.debug_project(sid, cams, vm_t, poses, 0, n)
+    ref = project32(scene, batch, 0, 0)
+    vis = ref["visible"]
+    assert vis.sum() > n // 4
+    np.testing.assert_array_equal(got["zkey"] != 0xFFFFFFFF, vis)
+    np.testing.assert_array_equal(got["zkey"][vis], ref["zbits"][vis])
+    np.testing.assert_array_equal(got["rect"][vis], ref["rect"][vis])
+    np.testing.assert_array_equal(got["rec"][vis][:, 7], ref["radius"][vis])
+    np.testing.assert_array_equal(got["rec"][vis][:, 0], ref["u"][vis])
+    R.remove_scene(sid)
