@@ -770,7 +770,7 @@ int render_job(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job_i
 {
     if (job_in.imgs.empty()) return GSR_OK;
     RenderJob job = job_in;
-    const size_t rec_bytes = job.lidar ? 80 : 48;
+    const size_t rec_bytes = job.lidar ? 64 : 48;
     const ChunkPlan plan = plan_chunks(ctx, sc, job.imgs, plain, job.tune.chunk_images, rec_bytes, job.chunk_bytes);
     const int n_chunks = (int)((job.imgs.size() + plan.chunk - 1) / plan.chunk);
     bool two = two_streams && !plain && ctx->opt.overlap >= 0 && n_chunks > 1;

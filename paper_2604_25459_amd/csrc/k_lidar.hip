@@ -16,8 +16,11 @@
 //     functions; a cone across the seam of a full turn takes the hull of its
 //     two column ranges, a sensor inside the sphere takes the whole grid;
 //   * record: whitening W = S^-1 R^T (R, S the Gaussian's rotation in the
-//     sensor frame and its scales), the centre t, log2 o and W t, and the
-//     cone (centre direction, cosine of the half-angle) for wave culling.
+//     sensor frame and its scales), the centre t, log2 o, the cosine of the
+//     cone's half-angle for culling, and W t as far as it fits: 64 bytes, one
+//     aligned sector, since the projection is bound by these stores and the
+//     rasteriser gathers them at 2.5 TB/s.  What else a ray needs (the last of
+//     W t, the centre direction) is made when a record is staged.
 // Raster (one workgroup per tile of rays, one ray per thread): for each
 // listed Gaussian, d' = W d, t* = (d' . W t) / |d'|^2 (the peak of the
 // Gaussian along the ray), q = |W (t - t* d)|^2 (the offset taken in metres
@@ -37,7 +40,8 @@ constexpr float kHalfPi = 1.5707963267948966f;
 constexpr float kTwoPi = 6.283185307179586f;
 constexpr int kLdsBeams = 256;      // angular scans with at most this many beams search their elevations in LDS
 constexpr int kLdsTileAz = 1024;     // listed rays: tile azimuth tables up to this many floats are read from LDS
-constexpr int kLidarRec = 5;        // float4s per record: whitening rows + centre, log2 o + W t, cone
+constexpr int kLidarRec = 4;        // float4s per record: whitening rows + centre, (log2 o, cone, first two of W t)
+constexpr int kLidarStage = 5;      // float4s per staged record: whitening rows + centre, log2 o + W t, cone
 
 // First index r in [0, H) with v[r] >= x (strict = false) or v[r] > x
 // (strict = true), v ascending; H if none.
@@ -100,7 +104,7 @@ __device__ __forceinline__ void columns_between(float a, float b, int n, int* k0
 }
 
 // Records leave through LDS as in the camera projection: a wave's 64 records
-// (80 bytes each) are written to LDS and stored back lane-contiguously, so
+// (64 bytes each) are written to LDS and stored back lane-contiguously, so
 // each store instruction writes 1 KB of consecutive records.  The image
 // descriptions come in as a restrict argument (uniform reads become scalar
 // loads).
@@ -268,18 +272,11 @@ __global__ __launch_bounds__(256) void k_project_lidar(SceneDev s, ChunkDev c, c
                 for (int j = 0; j < 3; ++j) W[3 * k + j] = Rs[3 * j + k] * isc[k];
             const float w0 = (W[0] * tx + W[1] * ty) + W[2] * tz;
             const float w1 = (W[3] * tx + W[4] * ty) + W[5] * tz;
-            const float w2 = (W[6] * tx + W[7] * ty) + W[8] * tz;
             float4* r = st + kLidarRec * lane;
             r[0] = make_float4(W[0], W[1], W[2], tx);
             r[1] = make_float4(W[3], W[4], W[5], ty);
             r[2] = make_float4(W[6], W[7], W[8], tz);
-            r[3] = make_float4(log2o, w0, w1, w2);
-            if (grid) {
-                r[4] = make_float4(tx, ty, disc, 0.0f);
-            } else {
-                const float iD = __builtin_amdgcn_rcpf(D);
-                r[4] = make_float4(tx * iD, ty * iD, tz * iD, cone_c);
-            }
+            r[3] = make_float4(log2o, grid ? disc : cone_c, w0, w1);
         }
         wave_lds_sync();
         // float4 q of the wave's records belongs to lane q / kLidarRec
@@ -375,7 +372,7 @@ __device__ __forceinline__ void wave_range(float x, bool on, float* lo, float* h
 // 64 x 64 rays 16.2, 11.3, 9.2 ms; 64 rosette scans of 24,576 rays 10.3, 7.1, 6.1 ms.
 template <int TS>
 struct LidarLds {
-    float4 sr[kLidarRec][TS * TS];
+    float4 sr[kLidarStage][TS * TS];
     uint32_t live_w[2][TS * TS / 64];     // per wave: live rays left after a batch (by batch parity)
     uint8_t pick[TS * TS / 64][TS * TS];        // per wave: the batch's candidates that the first step keeps
     uint8_t quart[TS * TS / 64][4][TS * TS];    // per quarter of a wave: those that the second step keeps
@@ -499,7 +496,22 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
     bool wave_live = __ballot(live) != 0ull;
     bool bad_entry = false;
     int par = 0;
+    // ids are read one batch ahead, and a batch's records before the barrier
+    // that frees the staged ones: both reads pass while other waves still work
+    uint32_t gid = start + (uint32_t)tid < end ? list[start + (uint32_t)tid] : 0u;
     for (uint32_t b0 = start; b0 < end; b0 += kLBatch, par ^= 1) {
+        float4 rr[kLidarRec];
+        {
+            uint32_t g = gid;
+            if (b0 + (uint32_t)tid < end && g >= n) {       // impossible by construction: reported at the end, a
+                bad_entry = true;                           // valid record read
+                g = 0;
+            }
+#pragma unroll
+            for (int k = 0; k < kLidarRec; ++k) rr[k] = rec[kLidarRec * (size_t)g + k];
+            const uint32_t e = b0 + (uint32_t)(kLBatch + tid);
+            gid = e < end ? list[e] : 0u;
+        }
         __syncthreads();
         // every wave's flag from the previous batch is visible after the
         // barrier, so all waves take the same decision
@@ -509,15 +521,19 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
             for (int ww = 0; ww < NT / 64; ++ww) any |= live_w[par ^ 1][ww];
             if (!any) break;
         }
-        const uint32_t e = b0 + (uint32_t)tid;
-        if (e < end) {
-            uint32_t g = list[e];
-            if (g >= n) {               // impossible by construction: reported at the end, a valid record read
-                bad_entry = true;
-                g = 0;
+        {
+            const float4 m0 = rr[0], m1 = rr[1], m2 = rr[2], m3 = rr[3];
+            sr[0][tid] = m0;
+            sr[1][tid] = m1;
+            sr[2][tid] = m2;
+            // the last of W t, rounded as the projection rounds the others
+            sr[3][tid] = make_float4(m3.x, m3.z, m3.w, (m2.x * m0.w + m2.y * m1.w) + m2.z * m2.w);
+            if (GRID) {
+                sr[4][tid] = make_float4(m0.w, m1.w, m3.y, 0.0f);
+            } else {
+                const float iD = __builtin_amdgcn_rsqf(fmaf(m2.w, m2.w, fmaf(m1.w, m1.w, m0.w * m0.w)));
+                sr[4][tid] = make_float4(m0.w * iD, m1.w * iD, m2.w * iD, m3.y);
             }
-#pragma unroll
-            for (int k = 0; k < kLidarRec; ++k) sr[k][tid] = rec[kLidarRec * (size_t)g + k];
         }
         __syncthreads();
         const int cnt = (int)min((uint32_t)kLBatch, end - b0);
