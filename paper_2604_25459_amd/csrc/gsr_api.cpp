@@ -92,7 +92,7 @@ Workspace::~Workspace()
     if (!fixed)
         for (DevBuf* b : {&img, &xform, &keyz, &rect, &srect, &rec, &sk0, &sk1, &sv0, &sv1, &sort_hist, &kmm, &vis_count,
                       &tile_hist, &tile_range, &pair_count, &pair_base, &pairs, &row_hist, &row_range, &row_count,
-                          &row_base, &rows, &debug, &stage_elev, &seg_off, &counter,
+                          &row_base, &rows, &debug, &vmask, &stage_elev, &seg_off, &counter,
                           &ovf, &counter2})
             b->release();
     if (h_total) (void)hipHostFree(h_total);
@@ -530,6 +530,10 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
         return fail(GSR_E_INVALID, "asynchronous lists without a planned chunk");
     const SceneDev& s = sc->dev;
     const Tuning& tu = job.tune;
+    if (mode != Mode::kRender) {
+        GSR_HIP_TRY(ws.vmask.ensure((size_t)n_img * (size_t)((s.n + 63) / 64) * 8));
+        c.vmask = ws.vmask.as<uint64_t>();
+    }
     const bool prof = ctx->opt.profile && mode == Mode::kRender && !ws.fixed;
     StageEvents ev;
     // events of a chunk that fails before they are queued for reading go back to the spares
@@ -579,7 +583,8 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
                           (void*)c.sk[1], (void*)c.sv[0], (void*)c.sv[1], (void*)c.sort_hist, (void*)c.kmm,
                           (void*)c.vis_count,
                           (void*)c.tile_hist, (void*)c.tile_range, (void*)c.pair_count, (void*)c.pair_base,
-                          (void*)c.row_hist, (void*)c.row_range, (void*)c.row_count, (void*)c.row_base})
+                          (void*)c.row_hist, (void*)c.row_range, (void*)c.row_count, (void*)c.row_base,
+                          (void*)c.vmask})
             key.push_back((uint64_t)(uintptr_t)ptr);
         for (int k = 0; k < n_img; ++k)
             key.push_back(((uint64_t)job.imgs[i0 + k].width << 32) | (uint64_t)job.imgs[i0 + k].height);
@@ -1527,6 +1532,7 @@ GSR_EXPORT int gsr_debug_bins(gsr_ctx* ctx, const gsr_render_desc* d, int image,
         const ImageInfo& im = job.imgs[image];
         const int T = im.tiles_x * im.tiles_y;
         ChunkDev c = chunk_view(cw, sc, stop.plan, stop.i0, stop.n_img, job.imgs);
+        c.vmask = cw.vmask.as<uint64_t>();
         uint32_t vis = 0, npairs = 0;
         uint64_t pbase = 0;
         if (sc->dev.n > 0) GSR_HIP_TRY(hipMemcpy(&vis, c.vis_count + k, 4, hipMemcpyDeviceToHost));
@@ -1545,13 +1551,14 @@ GSR_EXPORT int gsr_debug_bins(gsr_ctx* ctx, const gsr_render_desc* d, int image,
         }
         if ((int64_t)npairs > out->capacity) return fail(GSR_E_INVALID, "capacity smaller than the number of pairs");
         if (npairs == 0) return GSR_OK;
-        GSR_HIP_TRY(cw.debug.ensure((size_t)npairs * 8));
-        GSR_HIP_TRY(launch_debug_keys(c, k, (uint64_t)sc->dev.n, c.pairs + pbase, npairs, cw.debug.as<uint64_t>(),
-                                      nullptr));
+        GSR_HIP_TRY(cw.debug.ensure((size_t)npairs * 12));
+        uint64_t* d_keys = cw.debug.as<uint64_t>();
+        uint32_t* d_ids = reinterpret_cast<uint32_t*>(d_keys + npairs);
+        GSR_HIP_TRY(launch_debug_keys(c, k, (uint64_t)sc->dev.n, c.pairs + pbase, npairs, d_keys, d_ids, nullptr));
         GSR_HIP_TRY(hipDeviceSynchronize());
         if (out->keys) GSR_HIP_TRY(hipMemcpy(out->keys, cw.debug.p, (size_t)npairs * 8, hipMemcpyDeviceToHost));
         if (out->values)
-            GSR_HIP_TRY(hipMemcpy(out->values, c.pairs + pbase, (size_t)npairs * 4, hipMemcpyDeviceToHost));
+            GSR_HIP_TRY(hipMemcpy(out->values, d_ids, (size_t)npairs * 4, hipMemcpyDeviceToHost));
         return GSR_OK;
     };
     rc = body();
@@ -1583,33 +1590,38 @@ GSR_EXPORT int gsr_debug_project(gsr_ctx* ctx, const gsr_render_desc* d, int ima
     uint64_t total = 0;
     int rc = debug_run(ctx, d, image, Mode::kProject, &sc, &ws, &job, &plan, &total);
     const int64_t n = out->n;
-    if (!rc && out->zkey && hipMemcpy(out->zkey, ws->keyz.p, (size_t)n * 4, hipMemcpyDeviceToHost) != hipSuccess)
-        rc = fail(GSR_E_DEVICE, "copy of keys failed");
-    if (!rc && out->rect) {
-        std::vector<uint32_t> r((size_t)n * 2);
-        if (hipMemcpy(r.data(), ws->rect.p, (size_t)n * 8, hipMemcpyDeviceToHost) != hipSuccess) {
-            rc = fail(GSR_E_DEVICE, "copy of rectangles failed");
-        } else {
-            const ImageInfo& im = job.imgs[image];
-            const bool packed = rect4_format(im.tiles_x, im.tiles_y) != 0;   // the debug chunk is this one image
-            for (int64_t g = 0; g < n; ++g) {
-                if (packed) {
-                    const uint32_t v = r[g];
-                    out->rect[4 * g + 0] = (int32_t)(v & 0xFF);
-                    out->rect[4 * g + 1] = (int32_t)((v >> 8) & 0xFF);
-                    out->rect[4 * g + 2] = (int32_t)((v >> 16) & 0xFF);
-                    out->rect[4 * g + 3] = (int32_t)(v >> 24);
-                } else {
-                    out->rect[4 * g + 0] = (int32_t)(r[2 * g] & 0xFFFF);
-                    out->rect[4 * g + 1] = (int32_t)(r[2 * g] >> 16);
-                    out->rect[4 * g + 2] = (int32_t)(r[2 * g + 1] & 0xFFFF);
-                    out->rect[4 * g + 3] = (int32_t)(r[2 * g + 1] >> 16);
+    // the slots of the projection's results, unpacked to the Gaussians (see ChunkDev::keyz)
+    std::vector<uint64_t> mask((size_t)(n + 63) / 64);
+    std::vector<uint32_t> key((size_t)n), rect((size_t)n * 2);
+    std::vector<float> rec(out->rec ? (size_t)n * 12 : 0);
+    if (!rc && (hipMemcpy(mask.data(), ws->vmask.p, mask.size() * 8, hipMemcpyDeviceToHost) != hipSuccess ||
+                hipMemcpy(key.data(), ws->keyz.p, (size_t)n * 4, hipMemcpyDeviceToHost) != hipSuccess ||
+                hipMemcpy(rect.data(), ws->rect.p, (size_t)n * 8, hipMemcpyDeviceToHost) != hipSuccess ||
+                (out->rec && hipMemcpy(rec.data(), ws->rec.p, (size_t)n * 48, hipMemcpyDeviceToHost) != hipSuccess)))
+        rc = fail(GSR_E_DEVICE, "copy of the projection's results failed");
+    if (!rc) {
+        const ImageInfo& im = job.imgs[image];
+        const bool packed = rect4_format(im.tiles_x, im.tiles_y) != 0;   // the debug chunk is this one image
+        if (out->zkey) std::fill(out->zkey, out->zkey + n, kInvalidKey);
+        if (out->rect) std::memset(out->rect, 0, (size_t)n * 16);
+        if (out->rec) std::memset(out->rec, 0, (size_t)n * 48);
+        for (size_t w = 0; w < mask.size(); ++w) {
+            size_t slot = w * 64;
+            for (uint64_t m = mask[w]; m; m &= m - 1, ++slot) {
+                const size_t g = w * 64 + (size_t)__builtin_ctzll(m);
+                if (out->zkey) out->zkey[g] = key[slot];
+                if (out->rect) {
+                    int32_t* r = out->rect + 4 * g;
+                    if (packed) {
+                        for (int k = 0; k < 4; ++k) r[k] = (int32_t)((rect[slot] >> (8 * k)) & 0xFF);
+                    } else {
+                        for (int k = 0; k < 4; ++k) r[k] = (int32_t)((rect[2 * slot + k / 2] >> (16 * (k & 1))) & 0xFFFF);
+                    }
                 }
+                if (out->rec) std::memcpy(out->rec + 12 * g, rec.data() + 12 * slot, 48);
             }
         }
     }
-    if (!rc && out->rec && hipMemcpy(out->rec, ws->rec.p, (size_t)n * 48, hipMemcpyDeviceToHost) != hipSuccess)
-        rc = fail(GSR_E_DEVICE, "copy of records failed");
     debug_finish(ctx, sc, ws);
     return rc;
 }

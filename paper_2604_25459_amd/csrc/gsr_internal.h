@@ -132,9 +132,15 @@ struct ChunkDev {
     int tile_items;            // depth-ordered Gaussians per tile-pass block (level 1: one wave each)
     const ImageInfo* img;      // [n_img]
     float* xform;              // [n_img][n_bodies + 1][16]
+    // What the projection writes per (image, Gaussian).  Cameras: in slots, the
+    // visible Gaussians of each 64 consecutive ones (a wave's) packed to the
+    // front of the 64 slots, in index order, so slots order like indices; the
+    // ids of the sort and of the lists are slots, and `vmask` maps them back.
+    // LiDAR: a Gaussian's slot is its index.
     uint32_t* keyz;            // [n_img][n] depth bits or kInvalidKey
     uint2* rect;               // [n_img][n] tile rectangle (format: rect4 below)
     float4* rec;               // [n_img][n][3] raster records ([..][4] for LiDAR)
+    uint64_t* vmask;           // [n_img][ceil(n / 64)] visible Gaussians of each 64 (debug runs; else null)
     uint32_t* sk[2];           // depth-sort keys, ping-pong [n_img][n]
     uint32_t* sv[2];           // depth-sort values (Gaussian ids); sorted result in sv[0]
     uint2* srect;              // [n_img][n] tile rectangle of the j-th depth-ordered Gaussian
@@ -268,9 +274,15 @@ hipError_t launch_scene_convert(int storage, int64_t n, int64_t n_pad, int degre
                                 const float* scales, const float* quats, const float* opac, const float* sh,
                                 float4* pos, void* rot, float4* scale, void* sh_planes, hipStream_t stream);
 
-// Debug: 64-bit keys of one image from its sorted pairs.
+// Debug: 64-bit keys and Gaussian indices of one image from its sorted pairs.
 hipError_t launch_debug_keys(const ChunkDev& c, int image, uint64_t n, const uint32_t* pairs, uint64_t n_pairs,
-                             uint64_t* keys_out, hipStream_t stream);
+                             uint64_t* keys_out, uint32_t* ids_out, hipStream_t stream);
+// Index of the k-th set bit of m (k < popcount(m)).
+__host__ __device__ inline uint32_t select_bit(uint64_t m, uint32_t k)
+{
+    for (; k > 0; --k) m &= m - 1;
+    return (uint32_t)__builtin_ctzll(m);
+}
 
 // Workgroups of a launch are handed to the chip's 8 XCDs round-robin by
 // linear id, and each XCD has its own L2.  xcd_remap renumbers linear id b of

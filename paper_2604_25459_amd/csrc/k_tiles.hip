@@ -964,7 +964,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_rowtile_rank(ChunkDev c
 
 // Keys of one image: key = (global tile << 32) | depth bits of the Gaussian.
 __global__ __launch_bounds__(256) void k_debug_keys(ChunkDev c, int image, uint64_t n, const uint32_t* pairs,
-                                                    uint64_t* keys)
+                                                    uint64_t* keys, uint32_t* ids)
 {
     const ImageInfo im = c.img[image];
     const int T = im.tiles_x * im.tiles_y;
@@ -972,8 +972,10 @@ __global__ __launch_bounds__(256) void k_debug_keys(ChunkDev c, int image, uint6
     if (t >= T) return;
     const uint32_t* R = c.tile_range + (size_t)image * c.t_max * 2;
     for (uint32_t k = R[2 * t]; k < R[2 * t + 1]; ++k) {
-        const uint32_t g = pairs[k];
-        keys[k] = ((uint64_t)(im.key_tile_base + (uint32_t)t) << 32) | c.keyz[(size_t)image * n + g];
+        const uint32_t slot = pairs[k];
+        keys[k] = ((uint64_t)(im.key_tile_base + (uint32_t)t) << 32) | c.keyz[(size_t)image * n + slot];
+        const uint64_t m = c.vmask[(size_t)image * ((n + 63) / 64) + slot / 64u];
+        ids[k] = (slot & ~63u) + select_bit(m, slot & 63u);
     }
 }
 
@@ -1036,11 +1038,11 @@ hipError_t launch_tile_scatter(const SceneDev& s, const ChunkDev& c, int schedul
 }
 
 hipError_t launch_debug_keys(const ChunkDev& c, int image, uint64_t n, const uint32_t* pairs, uint64_t n_pairs,
-                             uint64_t* keys_out, hipStream_t stream)
+                             uint64_t* keys_out, uint32_t* ids_out, hipStream_t stream)
 {
     (void)n_pairs;
     hipLaunchKernelGGL(k_debug_keys, dim3((unsigned)((c.t_max + 255) / 256)), dim3(256), 0, stream, c, image, n,
-                       pairs, keys_out);
+                       pairs, keys_out, ids_out);
     return hipGetLastError();
 }
 
