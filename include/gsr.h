@@ -292,9 +292,9 @@ int gsr_render_noalloc(gsr_ctx* ctx, const gsr_render_desc* desc, void* stream);
  * are listed one by one, ray k with azimuth ray_az[k] and elevation
  * ray_el[k] (any arrangement, e.g. the points of a rosette pattern at one
  * instant); results come back in the same order (out index k).  The library
- * sorts the rays into H elevation bands of W rays (azimuth order within a
- * band) and bins each Gaussian to the bands its cone crosses and, within
- * them, to the ray tiles whose azimuth span meets its azimuth window (the
+ * sorts the rays by elevation into tile rows and each of those by azimuth into
+ * ray tiles, and bins each Gaussian to the tile rows its cone crosses and,
+ * within them, to the tiles whose azimuth span meets its azimuth window (the
  * hull over the tile rows), so the result is again that of casting every
  * ray against every Gaussian.
  *

@@ -1262,13 +1262,55 @@ GSR_EXPORT int gsr_render_plain(gsr_ctx* ctx, const gsr_render_desc* desc, void*
 
 namespace {
 
+// Rays of a listed-ray slot as (angle, index) keys: the angle's order in the
+// high word (equal angles order by index; -0 and 0 are equal).
+uint64_t ray_key(float angle, uint32_t k)
+{
+    const float a = angle + 0.0f;
+    uint32_t u;
+    std::memcpy(&u, &a, sizeof u);
+    return ((uint64_t)(u ^ ((u >> 31) ? 0xFFFFFFFFu : 0x80000000u)) << 32) | k;
+}
+
+// Stable radix sort of n keys by their high words (tmp: n words; the result is in `key`).
+void sort_ray_keys(uint64_t* key, uint64_t* tmp, size_t n)
+{
+    if (n < 512) {
+        std::sort(key, key + n);
+        return;
+    }
+    constexpr int kBits = 11, kPasses = 3;
+    std::vector<uint32_t> at((size_t)kPasses << kBits, 0u);
+    const uint32_t mask = (1u << kBits) - 1u;
+    for (size_t k = 0; k < n; ++k)
+        for (int p = 0; p < kPasses; ++p) ++at[((size_t)p << kBits) + ((key[k] >> (32 + kBits * p)) & mask)];
+    uint64_t *from = key, *to = tmp;
+    for (int p = 0; p < kPasses; ++p) {
+        uint32_t* o = at.data() + ((size_t)p << kBits);
+        uint32_t run = 0;
+        for (uint32_t d = 0; d <= mask; ++d) {
+            const uint32_t c = o[d];
+            o[d] = run;
+            run += c;
+        }
+        for (size_t k = 0; k < n; ++k) to[o[(from[k] >> (32 + kBits * p)) & mask]++] = from[k];
+        std::swap(from, to);
+    }
+    if (from != key) std::memcpy(key, from, n * sizeof *key);
+}
+
 // A listed-ray slot's device tables, written to `out` (floats; the caller
-// indices as their bit patterns): rays ordered by (elevation, index) and cut
-// into H bands of W; within a band by (azimuth, index).  out = [H] smallest
-// and [H] largest elevation of each band, then [H][W] azimuths, [H][W]
-// elevations and [H][W] caller indices, then per ts x ts tile of rays the
-// smallest and the largest azimuth ([TY][TX] each; along a tile row both
-// ascend, since each band's azimuths do).
+// indices as their bit patterns).  The rays are cut by elevation into tile rows
+// (ts bands of W rays), each tile row by azimuth into its tiles, each tile by
+// elevation into its rows and each of those put in azimuth order: tiles are
+// compact, disjoint in azimuth along a tile row, and so are the 8 x 2 blocks of
+// rays that the rasteriser culls for.  (Sorting every band by azimuth on its own
+// instead gave tiles as wide as the widest difference between their bands'
+// azimuths: lists several times as long for a rosette's outer tiles.)
+// out = [H] smallest and [H] largest elevation of each band, then [H][W]
+// azimuths, [H][W] elevations and [H][W] caller indices, then per tile the
+// smallest and the largest azimuth ([TY][TX] each).  Bands' elevations ascend,
+// and tiles' azimuths along a tile row.
 size_t ray_list_floats(const gsr_lidar& L, int ts)
 {
     const size_t H = (size_t)L.height, W = (size_t)L.width;
@@ -1278,41 +1320,53 @@ size_t ray_list_floats(const gsr_lidar& L, int ts)
 
 void stage_ray_list(const gsr_lidar& L, int ts, float* out)
 {
-    const size_t H = (size_t)L.height, W = (size_t)L.width, n = H * W;
-    std::vector<uint32_t> idx(n);
-    for (size_t k = 0; k < n; ++k) idx[k] = (uint32_t)k;
-    std::stable_sort(idx.begin(), idx.end(), [&](uint32_t a, uint32_t b) { return L.ray_el[a] < L.ray_el[b]; });
+    const size_t H = (size_t)L.height, W = (size_t)L.width, n = H * W, T = (size_t)ts;
+    const size_t TX = (W + T - 1) / T, TY = (H + T - 1) / T;
     float* lo = out;
     float* hi = out + H;
     float* az = out + 2 * H;
     float* el = az + n;
     float* perm = el + n;
-    for (size_t r = 0; r < H; ++r) {
-        uint32_t* band = idx.data() + r * W;
-        lo[r] = L.ray_el[band[0]];
-        hi[r] = L.ray_el[band[W - 1]];
-        std::stable_sort(band, band + W, [&](uint32_t a, uint32_t b) { return L.ray_az[a] < L.ray_az[b]; });
-        for (size_t c = 0; c < W; ++c) {
-            const uint32_t k = band[c];
-            az[r * W + c] = L.ray_az[k];
-            el[r * W + c] = L.ray_el[k];
-            std::memcpy(perm + r * W + c, &k, sizeof k);
-        }
-    }
-    const size_t TX = (W + ts - 1) / ts, TY = (H + ts - 1) / ts;
     float* tmin = perm + n;
     float* tmax = tmin + TX * TY;
-    for (size_t ty = 0; ty < TY; ++ty)
+    for (size_t r = 0; r < H; ++r) {
+        lo[r] = 4.0f;
+        hi[r] = -4.0f;
+    }
+    std::vector<uint64_t> key(n), tmp(n);
+    for (size_t k = 0; k < n; ++k) key[k] = ray_key(L.ray_el[k], (uint32_t)k);
+    sort_ray_keys(key.data(), tmp.data(), n);
+    auto rekey = [](uint64_t* k, size_t m, const float* angle) {
+        for (size_t q = 0; q < m; ++q) k[q] = ray_key(angle[(uint32_t)k[q]], (uint32_t)k[q]);
+    };
+    for (size_t ty = 0; ty < TY; ++ty) {
+        const size_t rows = std::min(T, H - ty * T);
+        uint64_t* band = key.data() + ty * T * W;
+        rekey(band, rows * W, L.ray_az);
+        sort_ray_keys(band, tmp.data(), rows * W);
         for (size_t tx = 0; tx < TX; ++tx) {
-            float a = az[ty * ts * W + tx * ts], b = a;
-            const size_t c_end = std::min(W, (tx + 1) * ts) - 1;
-            for (size_t r = ty * ts; r < std::min(H, (ty + 1) * ts); ++r) {
-                a = std::min(a, az[r * W + tx * ts]);
-                b = std::max(b, az[r * W + c_end]);
+            const size_t cols = std::min(T, W - tx * T);
+            uint64_t* tile = band + rows * tx * T;
+            tmin[ty * TX + tx] = L.ray_az[(uint32_t)tile[0]];
+            tmax[ty * TX + tx] = L.ray_az[(uint32_t)tile[rows * cols - 1]];
+            rekey(tile, rows * cols, L.ray_el);
+            std::sort(tile, tile + rows * cols);
+            for (size_t r = 0; r < rows; ++r) {
+                uint64_t* row = tile + r * cols;
+                const size_t at = (ty * T + r) * W + tx * T;
+                lo[ty * T + r] = std::min(lo[ty * T + r], L.ray_el[(uint32_t)row[0]]);
+                hi[ty * T + r] = std::max(hi[ty * T + r], L.ray_el[(uint32_t)row[cols - 1]]);
+                rekey(row, cols, L.ray_az);
+                std::sort(row, row + cols);
+                for (size_t c = 0; c < cols; ++c) {
+                    const uint32_t k = (uint32_t)row[c];
+                    az[at + c] = L.ray_az[k];
+                    el[at + c] = L.ray_el[k];
+                    std::memcpy(perm + at + c, &k, sizeof k);
+                }
             }
-            tmin[ty * TX + tx] = a;
-            tmax[ty * TX + tx] = b;
         }
+    }
 }
 
 int validate_lidar(const gsr_ctx* ctx, const gsr_lidar_desc* d, const SceneRes* sc)
@@ -1394,9 +1448,10 @@ GSR_EXPORT int gsr_render_lidar(gsr_ctx* ctx, const gsr_lidar_desc* d, void* str
     }
     auto body = [&]() -> int {
         GSR_HIP_TRY(hipSetDevice(ctx->device));
-        // beam elevations of every slot, staged in pinned memory and copied to
-        // the device (earlier work on this workspace must be done with them)
-        if (ws->used) GSR_HIP_TRY(hipEventSynchronize(ws->ev_done));
+        // beam elevations and ray lists of every slot, staged in pinned memory
+        // and copied to the device; the lists are sorted before the wait for
+        // the workspace's earlier work (which reads the staged ones), so that
+        // sorting a scan's rays runs beside the scan before it
         // per slot: angular, its H beam elevations; listed rays, the band
         // tables [2][H], azimuths, elevations and caller indices [H][W] each
         // and the tiles' azimuth spans [2][TY][TX]
@@ -1408,6 +1463,13 @@ GSR_EXPORT int gsr_render_lidar(gsr_ctx* ctx, const gsr_lidar_desc* d, void* str
         size_t n_elev = 0;
         for (int l = 0; l < d->n_lidars; ++l) n_elev += staged(d->lidars[l]);
         n_elev = std::max<size_t>(n_elev, 1);
+        std::vector<float> elev(n_elev);
+        for (size_t l = 0, at = 0; l < (size_t)d->n_lidars; at += staged(d->lidars[l]), ++l) {
+            const gsr_lidar& L = d->lidars[l];
+            if (L.pattern == GSR_LIDAR_ANGULAR) std::memcpy(elev.data() + at, L.elevations, (size_t)L.height * sizeof(float));
+            if (L.pattern == GSR_LIDAR_RAYS) stage_ray_list(L, ctx->opt.tile_size, elev.data() + at);
+        }
+        if (ws->used) GSR_HIP_TRY(hipEventSynchronize(ws->ev_done));
         if (ws->h_elev_cap < n_elev) {
             if (ws->h_elev) (void)hipHostFree(ws->h_elev);
             ws->h_elev = nullptr;
@@ -1433,8 +1495,6 @@ GSR_EXPORT int gsr_render_lidar(gsr_ctx* ctx, const gsr_lidar_desc* d, void* str
             const gsr_lidar& L = d->lidars[l];
             const bool grid = L.pattern == GSR_LIDAR_GRID, rays = L.pattern == GSR_LIDAR_RAYS;
             const size_t H = (size_t)L.height, W = (size_t)L.width;
-            if (L.pattern == GSR_LIDAR_ANGULAR) std::memcpy(ws->h_elev + eo, L.elevations, H * sizeof(float));
-            if (rays) stage_ray_list(L, ts, ws->h_elev + eo);
             const int tx = (L.width + ts - 1) / ts, ty = (L.height + ts - 1) / ts;
             for (int e = 0; e < E; ++e) {
                 ImageInfo& im = job.imgs[(size_t)l * E + e];
@@ -1474,6 +1534,7 @@ GSR_EXPORT int gsr_render_lidar(gsr_ctx* ctx, const gsr_lidar_desc* d, void* str
             }
             eo += staged(L);
         }
+        std::memcpy(ws->h_elev, elev.data(), n_elev * sizeof(float));
         GSR_HIP_TRY(hipMemcpyAsync(ws->stage_elev.p, ws->h_elev, n_elev * sizeof(float), hipMemcpyHostToDevice, st));
         // grids of equal size contiguous (one raster segment each)
         std::stable_sort(job.imgs.begin(), job.imgs.end(), [](const ImageInfo& a, const ImageInfo& b) {
