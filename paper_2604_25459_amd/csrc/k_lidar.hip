@@ -487,7 +487,8 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
     uint8_t* const pick = L_.pick[tid >> 6];
     uint8_t (*const quart)[NT] = L_.quart[tid >> 6];
     float T = 1.0f, Rg = 0.0f;
-    const float near = im.near_plane;
+    // returns at t* <= reach are not taken: the sensor's near range, infinity once the ray has stopped
+    float reach = inside ? im.near_plane : INFINITY;
     const uint32_t* R = c.tile_range + ((size_t)i * c.t_max + t) * 2;
     const uint32_t start = R[0], end = R[1];
     const uint32_t* list = c.pairs + c.pair_base[i];
@@ -529,7 +530,9 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
             // the last of W t, rounded as the projection rounds the others
             sr[3][tid] = make_float4(m3.x, m3.z, m3.w, (m2.x * m0.w + m2.y * m1.w) + m2.z * m2.w);
             if (GRID) {
-                sr[4][tid] = make_float4(m0.w, m1.w, m3.y, 0.0f);
+                // every ray's direction is (0, 0, -1): W d = -(third column of W), the same for all of them
+                sr[4][tid] = make_float4(m0.w, m1.w, m3.y,
+                                         __builtin_amdgcn_rcpf(fmaf(m2.z, m2.z, fmaf(m1.z, m1.z, m0.z * m0.z))));
             } else {
                 const float iD = __builtin_amdgcn_rsqf(fmaf(m2.w, m2.w, fmaf(m1.w, m1.w, m0.w * m0.w)));
                 sr[4][tid] = make_float4(m0.w * iD, m1.w * iD, m2.w * iD, m3.y);
@@ -629,26 +632,30 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
             // dependency chains the wave interleaves), then composited in list order
             auto eval = [&](int j, float* ts_out, float* la_out) {
                 const float4 m0 = sr[0][j], m1 = sr[1][j], m2 = sr[2][j], m3 = sr[3][j];
-                // d' = W d
-                const float dx = fmaf(m0.z, d[2], fmaf(m0.y, d[1], m0.x * d[0]));
-                const float dy = fmaf(m1.z, d[2], fmaf(m1.y, d[1], m1.x * d[0]));
-                const float dz = fmaf(m2.z, d[2], fmaf(m2.y, d[1], m2.x * d[0]));
-                const float aa = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                // centre relative to the ray origin, and W times it
-                float cx = m0.w, cy = m1.w, wcx = m3.y, wcy = m3.z, wcz = m3.w;
+                float tstar, px, py, pz;
                 if (GRID) {
-                    cx = m0.w - ox;
-                    cy = m1.w - oy;
-                    wcx = m3.y - fmaf(m0.y, oy, m0.x * ox);
-                    wcy = m3.z - fmaf(m1.y, oy, m1.x * ox);
-                    wcz = m3.w - fmaf(m2.y, oy, m2.x * ox);
+                    // centre relative to the ray origin, and W times it
+                    px = m0.w - ox;
+                    py = m1.w - oy;
+                    const float wcx = m3.y - fmaf(m0.y, oy, m0.x * ox);
+                    const float wcy = m3.z - fmaf(m1.y, oy, m1.x * ox);
+                    const float wcz = m3.w - fmaf(m2.y, oy, m2.x * ox);
+                    tstar = fmaf(-m2.z, wcz, fmaf(-m1.z, wcy, -m0.z * wcx)) * sr[4][j].w;
+                    pz = m2.w + tstar;
+                } else {
+                    // d' = W d
+                    const float dx = fmaf(m0.z, d[2], fmaf(m0.y, d[1], m0.x * d[0]));
+                    const float dy = fmaf(m1.z, d[2], fmaf(m1.y, d[1], m1.x * d[0]));
+                    const float dz = fmaf(m2.z, d[2], fmaf(m2.y, d[1], m2.x * d[0]));
+                    const float aa = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                    const float bb = fmaf(dz, m3.w, fmaf(dy, m3.z, dx * m3.y));
+                    tstar = bb * __builtin_amdgcn_rcpf(aa);
+                    // offset of the centre from the ray's closest point, in metres
+                    px = fmaf(-tstar, d[0], m0.w);
+                    py = fmaf(-tstar, d[1], m1.w);
+                    pz = fmaf(-tstar, d[2], m2.w);
                 }
-                const float bb = fmaf(dz, wcz, fmaf(dy, wcy, dx * wcx));
-                const float tstar = bb * __builtin_amdgcn_rcpf(aa);
-                // offset of the centre from the ray's closest point, in metres, then whitened
-                const float px = fmaf(-tstar, d[0], cx);
-                const float py = fmaf(-tstar, d[1], cy);
-                const float pz = fmaf(-tstar, d[2], m2.w);
+                // the offset whitened
                 const float wx = fmaf(m0.z, pz, fmaf(m0.y, py, m0.x * px));
                 const float wy = fmaf(m1.z, pz, fmaf(m1.y, py, m1.x * px));
                 const float wz = fmaf(m2.z, pz, fmaf(m2.y, py, m2.x * px));
@@ -657,34 +664,37 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
                 *la_out = fmaf(-0.72134752044448170f, qq, m3.x);      // log2 o - q/2 log2 e
             };
             auto take = [&](float tstar, float la) {
-                if (live && tstar > near && la >= kLidarLogAlphaMin) {
+                if (tstar > reach && la >= kLidarLogAlphaMin) {
                     // only the rays that take the Gaussian run this (exec mask);
                     // the empty asm keeps it a branch rather than selects
                     asm volatile("");
                     const float alpha = fminf(0.99f, __builtin_amdgcn_exp2f(la));
                     const float Tn = fmaf(-T, alpha, T);
-                    if (Tn < 1e-4f) {
-                        live = false;                   // stops here, adds nothing
-                    } else {
-                        Rg = fmaf(tstar, alpha * T, Rg);
-                        T = Tn;
-                    }
+                    const bool stop = Tn < 1e-4f;           // stops here, adds nothing
+                    Rg = stop ? Rg : fmaf(tstar, alpha * T, Rg);
+                    T = stop ? T : Tn;
+                    reach = stop ? INFINITY : reach;
                 }
             };
             // each quarter walks its own list: the reads of a pair of records
             // take the same LDS instructions as one list for the wave would
             const uint32_t my_n = quarter == 0 ? n_q[0] : quarter == 1 ? n_q[1] : quarter == 2 ? n_q[2] : n_q[3];
             const uint32_t most = max(max(n_q[0], n_q[1]), max(n_q[2], n_q[3]));
+            uint32_t jj = *reinterpret_cast<const uint16_t*>(&quart[quarter][0]);
             for (uint32_t k = 0; k < most; k += 2) {
-                const uint32_t jj = *reinterpret_cast<const uint16_t*>(&quart[quarter][k]);
-                if (!live || k >= my_n) continue;
                 const int j0 = (int)(jj & (uint32_t)(NT - 1)), j1 = (int)((jj >> 8) & (uint32_t)(NT - 1));
+                jj = *reinterpret_cast<const uint16_t*>(&quart[quarter][(k + 2u) & (uint32_t)(NT - 1)]);
+                if (k >= my_n) continue;
                 float t0, l0, t1, l1;
                 eval(j0, &t0, &l0);
                 eval(j1, &t1, &l1);
+                l1 = k + 1u < my_n ? l1 : -INFINITY;
+                // both are complete before the first is taken: two independent chains
+                asm volatile("" : "+v"(t0), "+v"(l0), "+v"(t1), "+v"(l1));
                 take(t0, l0);
-                if (k + 1 < my_n) take(t1, l1);
+                take(t1, l1);
             }
+            live = reach < INFINITY;
             if (__ballot(live) == 0ull) wave_live = false;
         }
         if (lane == 0) live_w[par][tid >> 6] = wave_live ? 1u : 0u;
