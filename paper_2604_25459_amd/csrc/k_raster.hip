@@ -33,6 +33,20 @@
 // have accepted.  Blending runs under the mask of the pixels that take the
 // Gaussian and takes a short path when none of them stops at it.
 //
+// Bound: a survivor costs about 21 ns of a SIMD's vector issue (13 ordinary
+// instructions and an exp2; with eight waves 1.1 ns each, a compare 1.8, an
+// exp2 3.4) and 20 ns of its share of LDS (2.5 16-byte reads, 2 ns each per
+// CU), so both are close to full and the rest of the loop is kept off the
+// issue: a branch costs 1.2 ns not taken and 2 ns taken, and with one wave per
+// SIMD (the tail of a launch, small launches) 6 and 9 ns, more than what a
+// branch here could skip.  Hence one branch per survivor over the blend and
+// one in it for the stop; the clamp is unconditional and an odd survivor is
+// paired with an empty one.  With three more branches per survivor: 2048
+// images of 640x480, 76.2 -> 73.5 ms; 64 of 320x240, 1.38 -> 1.28 ms; 16 of
+// 128x128 with one heavy tile, 1.32 -> 1.14 ms; one of 128x96, 195 -> 180 us.
+// The same sums on f32 matrix instructions (4x4x1, bit for bit equal) took
+// 6 % longer: their rate is that of the vector unit and the two do not overlap.
+//
 // Output: rgb = C + T bg, depth = D / (1 - T) (0 where nothing was added),
 // optional alpha = 1 - T, optional work counts, and optionally the fused
 // observation epilogue (gain, contrast about 0.5, brightness, clamp to
@@ -54,9 +68,6 @@ constexpr float kCullMargin = 0.05f;                  // in log2(alpha) units
 // -inf and the pixel never takes another Gaussian; no separate liveness flag
 // is needed in the per-Gaussian loop.
 constexpr float kDead = 1.0e30f;
-// log2(0.99) less a little: a Gaussian whose log2(opacity) is at most this
-// never reaches alpha = 0.99, so its blends skip the clamp.
-constexpr float kLog2ClampFree = -0.0145f;
 constexpr float kDeadTest = 1.0e29f;
 
 // Pixel layout: TS <= 16: one pixel per thread, waves own 8x8 blocks.
@@ -131,7 +142,6 @@ struct RasterLds {
     // a1, b1, c1, lo, -s1, -s2, R, G, B, z (a pair of survivors = five
     // 16-byte words; survivor k starts at float 10 k)
     float4 w[Layout<TS>::kWaves][160];
-    uint32_t bright[Layout<TS>::kWaves][64];   // survivor may reach alpha = 0.99
     uint32_t origin[Layout<TS>::kWaves][64];   // candidate index of the survivor (work counts)
     // per wave, whether it still has live pixels after a batch (by batch parity)
     uint32_t live[2][Layout<TS>::kWaves];
@@ -301,6 +311,8 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
     if (FILTER) refill((uint32_t)kBatch);
     if (start < (FILTER ? qt : end)) fetch(start);
     int buf = 0;
+    uint32_t alpha_max = __float_as_uint(0.99f);
+    asm("" : "+v"(alpha_max));          // in a vector register: a scalar operand halves the rate
     bool wave_live = __ballot(any_live) != 0ull;
     // pixel-centre rectangle still to be shaded (the live pixels' bounding
     // box), recomputed only when the set of live pixels has changed
@@ -354,9 +366,7 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
             const float4 a = sA[buf][jc], bq = sB[buf][jc];
             const float m = max_logalpha_rect(a.z, a.w, bq.x, bq.y, lx0 - a.x, lx1 - a.x, ly0 - a.y, ly1 - a.y);
             const bool keep = jl < cnt && m >= kLogAlphaMin - kCullMargin;
-            const bool bright = keep && bq.y > kLog2ClampFree;
             const uint64_t mask = __ballot(keep);
-            const uint64_t bright_lanes = __ballot(bright);
             const uint32_t n_surv = (uint32_t)__popcll(mask);
             const uint32_t r = lanes_below(mask);
             if (keep) {
@@ -371,30 +381,24 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
                 d[4] = make_float2(col.z, bq.z);
                 if (COUNT) L_.origin[w][r] = (uint32_t)jl;
             }
-            // bit k: survivor k may reach alpha = 0.99 (only those pay for the
-            // clamp); bright survivors are rare, so the packed mask is built
-            // only when the batch has one
-            uint64_t clampmask = 0;
-            if (bright_lanes != 0ull) {
-                if (keep) L_.bright[w][r] = bright ? 1u : 0u;
-                wave_lds_sync();
-                clampmask = __ballot((uint32_t)lane < n_surv && L_.bright[w][lane] != 0u);
+            // an odd last survivor is paired with one that no pixel takes, so
+            // that the walk has no branch on it (64 survivors are all pairs)
+            if ((n_surv & 1u) && lane == 0) {
+                float2* d = reinterpret_cast<float2*>(Wf + 10u * n_surv);
+                d[0] = d[2] = d[3] = d[4] = make_float2(0.0f, 0.0f);
+                d[1] = make_float2(0.0f, -INFINITY);
             }
             wave_lds_sync();
             // one survivor: a1, b1, c1, -s1 in q0; -s2, lo, z; colour
             auto shade = [&](const float4 q0, float ms2, float lo, float z, float cr, float cg, float cb,
                              uint32_t k_surv) {
                 float pw[PPT];
-                bool anyt = false;
 #pragma unroll
                 for (int k = 0; k < PPT; ++k) {
                     const float t1 = fmaf(q0.x, xl[k], fmaf(q0.y, yl[k], q0.w));
                     const float t2 = fmaf(q0.z, yl[k], ms2);
                     pw[k] = fmaf(-t1, t1, fmaf(-t2, t2, lo));
-                    anyt = anyt || pw[k] >= kLogAlphaMin;
                 }
-                if (__ballot(anyt) == 0ull) return;        // no live pixel of the wave reaches 1/255
-                const bool clamp = (clampmask >> k_surv) & 1ull;     // wave-uniform
 #pragma unroll
                 for (int k = 0; k < PPT; ++k) {
                     if (pw[k] >= kLogAlphaMin) {
@@ -402,15 +406,13 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
                         // (exec mask; the others keep T and the sums as they
                         // are, which adding 0 would have left them)
                         asm volatile("");
-                        float e = __builtin_amdgcn_exp2f(pw[k]);
-                        if (clamp) {
-                            // only survivors whose opacity can reach 0.99 pay for the clamp
-                            asm volatile("");
-                            e = fminf(0.99f, e);
-                        }
+                        // alpha = min(0.99, 2^p) on the bit patterns, which
+                        // order like the floats (neither is negative or NaN):
+                        // one instruction, where fminf is two
+                        const float e = __uint_as_float(min(alpha_max, __float_as_uint(__builtin_amdgcn_exp2f(pw[k]))));
                         float wgt = e * T[k];
                         T[k] = T[k] - wgt;
-                        if (__ballot(T[k] < 1e-4f) != 0ull) {
+                        if (__builtin_expect(__ballot(T[k] < 1e-4f) != 0ull, 0)) {
                             // rare: a pixel that stops here adds nothing and
                             // keeps its transmittance (T' + alpha T restores it
                             // to within one rounding)
@@ -429,16 +431,12 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
                     }
                 }
             };
-            // survivors two at a time: five 16-byte reads per pair (the second
-            // survivor's last two words are read only when it exists)
-            for (uint32_t k = 0; k < n_surv; k += 2) {
-                const float4* P = reinterpret_cast<const float4*>(Wf + 10u * k);     // 16-byte aligned (k even)
-                const float4 r0 = P[0], r1 = P[1], r2 = P[2];
+            // survivors two at a time: five 16-byte reads per pair
+            const float4* P = reinterpret_cast<const float4*>(Wf);
+            for (uint32_t k = 0; k < n_surv; k += 2, P += 5) {
+                const float4 r0 = P[0], r1 = P[1], r2 = P[2], r3 = P[3], r4 = P[4];
                 shade(make_float4(r0.x, r0.y, r0.z, r1.x), r1.y, r0.w, r2.y, r1.z, r1.w, r2.x, k);
-                if (k + 1 < n_surv) {
-                    const float4 r3 = P[3], r4 = P[4];
-                    shade(make_float4(r2.z, r2.w, r3.x, r3.z), r3.w, r3.y, r4.w, r4.x, r4.y, r4.z, k + 1);
-                }
+                shade(make_float4(r2.z, r2.w, r3.x, r3.z), r3.w, r3.y, r4.w, r4.x, r4.y, r4.z, k + 1);
             }
             // the wave stops once none of its pixels is live (checked per 64 candidates)
             bool lv = false;

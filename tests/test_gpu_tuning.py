@@ -313,3 +313,32 @@ def test_lists_at_every_launch_size(n, envs, w, h, ts):
             np.testing.assert_array_equal(got["values"], ref.values)
             np.testing.assert_array_equal(got["ranges"], ref.ranges)
     r.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 63, 64, 65, 127, 129])
+def test_survivor_counts_around_a_pair_and_a_batch(n):
+    """Wide, faint splats that every wave of the tile keeps, so that n counts
+    its survivors: one alone, odd and even counts, a full group of 64 and the
+    remainders beside it; every fifth is opaque beyond the 0.99 clamp and small."""
+    torch = _torch()
+    from oracle import render_ref
+    from paper_2604_25459_amd import gsr
+    from tests.parity import compare
+    from tests.scenes import one_camera, scene_from
+    rng = np.random.default_rng(500 + n)
+    i = np.arange(n)
+    opaque = i % 5 == 4
+    means = rng.uniform([-0.2, -0.2, 1.0], [0.2, 0.2, 3.0], (n, 3))
+    scales = np.where(opaque[:, None], 0.03, 0.6) * np.ones((n, 3))
+    opac = np.where(opaque, 0.998, 0.02)
+    scene = scene_from(means, scales, rng.standard_normal((n, 4)), opac, rng.uniform(0, 1, (n, 1, 3)), 0)
+    batch = one_camera(16, 16, 60.0, bg=(0.2, 0.3, 0.4))
+    R = gsr.Renderer(0)
+    sid = R.add_synth_scene(scene)
+    cams, vm, poses = gsr.batch_tensors(batch)
+    rgb, depth, alpha = R.render(sid, cams, vm, poses, bg=tuple(batch.bg), alpha=True)[0]
+    torch.cuda.synchronize()
+    ref = render_ref(scene, batch, 0, 0, R.tile_size)
+    res = compare(rgb[0].cpu().numpy(), depth[0].cpu().numpy(), ref, gpu_alpha=alpha[0].cpu().numpy(), rgb_tol=1e-3)
+    assert res["ok"], res
+    R.close()
