@@ -4,7 +4,8 @@
 // One workgroup per (image, tile) of the whole chunk, images of all camera
 // slots in one launch.  The tile's depth-sorted Gaussian list is staged into
 // LDS in batches of records (double-buffered: the next batch is fetched into
-// registers while the current one is composited).  Per pixel and Gaussian,
+// registers while the current one is composited), or in launches of few tiles
+// read by each wave for itself (kDirectTiles).  Per pixel and Gaussian,
 // with the conic in whitened form (a1, b1, c1) so that
 //     p = log2(o) - (a1 dx + b1 dy)^2 - (c1 dy)^2 = log2(alpha before the clamp)
 //     p < log2(1/255)          -> skip
@@ -134,9 +135,12 @@ __device__ __forceinline__ float max_logalpha_rect(float a1, float b1, float c1,
 constexpr int kQueue = 1024;
 constexpr int kRowScan = 512;
 
+// kBatch: records staged per batch, or 0 for the direct kernel.
 template <int TS, int kBatch>
 struct RasterLds {
-    float4 a[2][kBatch], b[2][kBatch], c[2][kBatch];    // staged records: (u, v, a1, b1), (c1, lo, z, r), rgb
+    static constexpr bool kDirect = kBatch == 0;
+    static constexpr int kStaged = kDirect ? 1 : kBatch;
+    float4 a[2][kStaged], b[2][kStaged], c[2][kStaged];    // staged records: (u, v, a1, b1), (c1, lo, z, r), rgb
     // per wave, the survivors of the current 64 candidates re-centred on the
     // wave's block, packed in candidate order, 10 floats each:
     // a1, b1, c1, lo, -s1, -s2, R, G, B, z (a pair of survivors = five
@@ -146,6 +150,21 @@ struct RasterLds {
     // per wave, whether it still has live pixels after a batch (by batch parity)
     uint32_t live[2][Layout<TS>::kWaves];
 };
+
+// Launches of at most this many tiles (with the default batch) use the direct
+// kernel: no staging, no barrier; each wave reads its 64 candidates, a lane
+// each, into registers one batch ahead and their ids two ahead, and stops as
+// soon as its own pixels have.  There the time is a few long lists' latency
+// per batch of 64 (a heavy tile of 15,390 entries: 1.6 -> 1.3 us a batch,
+// without the barrier, the flags and the reads behind it).  Staging reads
+// each record once for the tile's four waves; a full chip runs at its power
+// limit, and four times the reads then cost clock (2.11 -> 2.03 GHz).
+// Staged and direct: 16 images of 128x128, 1.14 and 0.95 ms; one 640x480, 309
+// and 295 us; 37 of 317x203 (9,620 tiles), 566 and 525 us; 64 of 320x240
+// (19,200), 1.28 and 1.25 ms; 512 of 128x128 (32,768), 3.25 and 3.24; 256
+// pairs of 128x128 and 640x480 (323,584), 22.6 and 23.5; 2048 of 640x480, 71
+// to 72 both.
+constexpr uint32_t kDirectTiles = 24576;
 
 // Ring of the fallback lists: filtered ids and per-wave counts of one round.
 template <int TS>
@@ -164,8 +183,11 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
     using L = Layout<TS>;
     constexpr int NT = L::kThreads;
     constexpr int PPT = L::kPpt;
-    constexpr int PER_THREAD = (kBatch + NT - 1) / NT;     // records each thread stages per batch
-    static_assert(kBatch % 64 == 0, "batch must be a multiple of 64");
+    constexpr bool DIRECT = kBatch == 0;                   // no staging: every wave reads its records itself
+    constexpr int BATCH = DIRECT ? 64 : kBatch;
+    constexpr int PER_THREAD = DIRECT ? 1 : (BATCH + NT - 1) / NT;     // records each thread holds of the next batch
+    static_assert(BATCH % 64 == 0, "batch must be a multiple of 64");
+    static_assert(!(DIRECT && FILTER), "the fallback shares its ring");
     auto& sA = L_.a;
     auto& sB = L_.b;
     auto& sC = L_.c;
@@ -223,7 +245,7 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
     const uint32_t* list = nullptr;
     constexpr int F = kRowScan / NT;                   // entries per thread per filtering round
     constexpr uint32_t QMASK = (uint32_t)kQueue - 1u;
-    static_assert(kBatch + kRowScan <= kQueue, "the ring must hold a batch and a filtering round");
+    static_assert(BATCH + kRowScan <= kQueue, "the ring must hold a batch and a filtering round");
     const uint32_t* sv = nullptr;
     uint32_t vend = 0, scan = 0, qt = 0;
     uint32_t pre_g[F];
@@ -288,28 +310,42 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
     const float4* rec = c.rec + (size_t)i * (size_t)s.n * 3;
     const uint32_t n = (uint32_t)s.n;
 
-    // register staging of the next batch
+    // the next batch in registers (DIRECT: the wave's next 64 records, and the ids of the 64 after them)
     float4 ra[PER_THREAD], rb[PER_THREAD], rc[PER_THREAD];
+    uint32_t id_ahead = 0;
     bool bad_entry = false;
+    auto load_record = [&](int q, uint32_t g) {
+        if (g >= n) {           // impossible by construction: reported at the end, a valid record read
+            bad_entry = true;
+            g = 0;
+        }
+        ra[q] = rec[3 * (size_t)g];
+        rb[q] = rec[3 * (size_t)g + 1];
+        rc[q] = rec[3 * (size_t)g + 2];
+    };
     auto fetch = [&](uint32_t b0) {
 #pragma unroll
         for (int q = 0; q < PER_THREAD; ++q) {
             const uint32_t slot = (uint32_t)(q * NT + tid);
             const uint32_t e = b0 + slot;
-            if (slot < (uint32_t)kBatch && e < (FILTER ? qt : end)) {
-                uint32_t g = FILTER ? Q->id[e & QMASK] : list[e];
-                if (g >= n) {           // impossible by construction: reported at the end, a valid record read
-                    bad_entry = true;
-                    g = 0;
-                }
-                ra[q] = rec[3 * (size_t)g];
-                rb[q] = rec[3 * (size_t)g + 1];
-                rc[q] = rec[3 * (size_t)g + 2];
-            }
+            if (slot < (uint32_t)BATCH && e < (FILTER ? qt : end)) load_record(q, FILTER ? Q->id[e & QMASK] : list[e]);
         }
     };
-    if (FILTER) refill((uint32_t)kBatch);
-    if (start < (FILTER ? qt : end)) fetch(start);
+    auto fetch_id = [&](uint32_t b0) {
+        const uint32_t e = b0 + (uint32_t)lane;
+        id_ahead = 0;           // past the end: the image's first record, which no lane keeps
+        if (e < end) id_ahead = list[e];
+    };
+    if (FILTER) refill((uint32_t)BATCH);
+    if (start < (FILTER ? qt : end)) {
+        if (DIRECT) {
+            fetch_id(start);
+            load_record(0, id_ahead);
+            fetch_id(start + (uint32_t)BATCH);
+        } else {
+            fetch(start);
+        }
+    }
     int buf = 0;
     uint32_t alpha_max = __float_as_uint(0.99f);
     asm("" : "+v"(alpha_max));          // in a vector register: a scalar operand halves the rate
@@ -319,30 +355,42 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
     float lx0 = wx0, lx1 = wx1, ly0 = wy0, ly1 = wy1;
     uint64_t live_seen = 0;
 
-    for (uint32_t b0 = start; b0 < (FILTER ? qt : end); b0 += kBatch) {
-#pragma unroll
-        for (int q = 0; q < PER_THREAD; ++q) {
-            const int slot = q * NT + tid;
-            if (slot < kBatch) {
-                sA[buf][slot] = ra[q];
-                sB[buf][slot] = rb[q];
-                sC[buf][slot] = rc[q];
+    for (uint32_t b0 = start; b0 < (FILTER ? qt : end); b0 += BATCH) {
+        float4 na, nb, nc;                                 // DIRECT: this batch's records, a lane each
+        if (DIRECT) {
+            if (!wave_live) break;
+            na = ra[0];
+            nb = rb[0];
+            nc = rc[0];
+            if (b0 + BATCH < end) {
+                load_record(0, id_ahead);
+                fetch_id(b0 + 2u * (uint32_t)BATCH);
             }
-        }
-        __syncthreads();
-        // every wave's flag from the previous batch is visible after the
-        // barrier, so all waves take the same decision
-        if (b0 != start) {
-            uint32_t any = 0;
+        } else {
 #pragma unroll
-            for (int ww = 0; ww < L::kWaves; ++ww) any |= L_.live[buf ^ 1][ww];
-            if (!any) break;
+            for (int q = 0; q < PER_THREAD; ++q) {
+                const int slot = q * NT + tid;
+                if (slot < BATCH) {
+                    sA[buf][slot] = ra[q];
+                    sB[buf][slot] = rb[q];
+                    sC[buf][slot] = rc[q];
+                }
+            }
+            __syncthreads();
+            // every wave's flag from the previous batch is visible after the
+            // barrier, so all waves take the same decision
+            if (b0 != start) {
+                uint32_t any = 0;
+#pragma unroll
+                for (int ww = 0; ww < L::kWaves; ++ww) any |= L_.live[buf ^ 1][ww];
+                if (!any) break;
+            }
+            // the batch at b0 is staged: its ring slots may be reused
+            if (FILTER) refill(b0 + 2u * (uint32_t)BATCH);
         }
-        // the batch at b0 is staged: its ring slots may be reused
-        if (FILTER) refill(b0 + 2u * (uint32_t)kBatch);
         const uint32_t lim = FILTER ? qt : end;
-        if (b0 + kBatch < lim) fetch(b0 + kBatch);
-        const int cnt = (int)min((uint32_t)kBatch, lim - b0);
+        if (!DIRECT && b0 + BATCH < lim) fetch(b0 + BATCH);
+        const int cnt = (int)min((uint32_t)BATCH, lim - b0);
         for (int sub = 0; sub < cnt && wave_live; sub += 64) {
             if (PPT == 1) {
                 const uint64_t M = __ballot(xl[0] < kDeadTest);  // lane = 8 * row + column
@@ -363,7 +411,7 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
             const int jl = sub + lane;
             // lanes past the batch's end test its last candidate and keep nothing
             const int jc = jl < cnt ? jl : cnt - 1;
-            const float4 a = sA[buf][jc], bq = sB[buf][jc];
+            const float4 a = DIRECT ? na : sA[buf][jc], bq = DIRECT ? nb : sB[buf][jc];
             const float m = max_logalpha_rect(a.z, a.w, bq.x, bq.y, lx0 - a.x, lx1 - a.x, ly0 - a.y, ly1 - a.y);
             const bool keep = jl < cnt && m >= kLogAlphaMin - kCullMargin;
             const uint64_t mask = __ballot(keep);
@@ -372,7 +420,7 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
             if (keep) {
                 const float du = a.x - cxo, dv = a.y - cyo;
                 const float s1 = fmaf(a.z, du, a.w * dv), s2 = bq.x * dv;
-                const float4 col = sC[buf][jl];
+                const float4 col = DIRECT ? nc : sC[buf][jl];
                 float2* d = reinterpret_cast<float2*>(Wf + 10u * r);     // 8-byte aligned
                 d[0] = make_float2(a.z, a.w);
                 d[1] = make_float2(bq.x, bq.y);
@@ -444,8 +492,10 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
             for (int k = 0; k < PPT; ++k) lv = lv || xl[k] < kDeadTest;
             if (__ballot(lv) == 0ull) wave_live = false;
         }
-        if (lane == 0) L_.live[buf][w] = wave_live ? 1u : 0u;
-        buf ^= 1;
+        if (!DIRECT) {
+            if (lane == 0) L_.live[buf][w] = wave_live ? 1u : 0u;
+            buf ^= 1;
+        }
     }
 
     if (bad_entry) atomicOr(c.err, kErrListEntry);
@@ -587,12 +637,13 @@ hipError_t launch_ts(const SceneDev& s, const ChunkDev& c, const RasterParams& p
     return p.count_work ? launch_tsc<TS, kBatch, true>(s, c, p, stream) : launch_tsc<TS, kBatch, false>(s, c, p, stream);
 }
 
-// LDS batch sizes: 64 / 128 / 256 records for 8x8 tiles (one wave), 64 to 512
+// The direct kernel, or one of the LDS batch sizes: 64 / 128 / 256 records for 8x8 tiles (one wave), 64 to 512
 // for the 256-thread layouts (smaller batches leave room for more workgroups
 // per CU; batches below the block size are staged by the first threads).
 template <int TS>
 hipError_t launch_batch(const SceneDev& s, const ChunkDev& c, const RasterParams& p, hipStream_t stream)
 {
+    if (p.batch == 64 && !p.persistent && p.n_blocks <= kDirectTiles) return launch_ts<TS, 0>(s, c, p, stream);
     if (p.batch == 64) return launch_ts<TS, 64>(s, c, p, stream);
     if (p.batch == 128) return launch_ts<TS, 128>(s, c, p, stream);
     if constexpr (TS != 8)

@@ -342,3 +342,30 @@ def test_survivor_counts_around_a_pair_and_a_batch(n):
     res = compare(rgb[0].cpu().numpy(), depth[0].cpu().numpy(), ref, gpu_alpha=alpha[0].cpu().numpy(), rgb_tol=1e-3)
     assert res["ok"], res
     R.close()
+
+
+@pytest.mark.parametrize("ts", [8, 16, 32])
+def test_images_equal_on_both_sides_of_the_direct_line(ts):
+    """One-tile images, once as many as one launch composites without staging
+    and once a few more: the images both have are the same bits."""
+    torch = _torch()
+    from paper_2604_25459_amd import gsr
+    from tests.scenes import one_camera, scene_from
+    rng = np.random.default_rng(77)
+    n, line = 300, 24576
+    scene = scene_from(rng.uniform([-0.3, -0.3, 1.0], [0.3, 0.3, 3.0], (n, 3)), np.exp(rng.normal(-3.0, 0.8, (n, 3))),
+                       rng.standard_normal((n, 4)), rng.uniform(0.02, 1.0, n), rng.uniform(0, 1, (n, 1, 3)), 0)
+    batch = one_camera(ts, ts, 0.9 * ts)
+    R = gsr.Renderer(0, tile_size=ts)
+    sid = R.add_synth_scene(scene)
+    cams, vm, _ = gsr.batch_tensors(batch)
+    views = vm.repeat(1, line + 7, 1, 1)
+    views[0, :, 0, 3] = torch.linspace(-0.3, 0.3, line + 7, device=vm.device)
+    poses = torch.zeros(line + 7, 0, 7, device=vm.device)
+    some = [t.clone() for t in R.render(sid, cams, views[:, :line].contiguous(), poses[:line], alpha=True)[0]]
+    more = R.render(sid, cams, views, poses, alpha=True)[0]
+    torch.cuda.synchronize()
+    for a, b in zip(some, more):
+        assert torch.equal(a, b[:line])
+    assert float(some[2].amax()) > 0.5 and not torch.equal(some[0][0], some[0][line - 1])
+    R.close()
