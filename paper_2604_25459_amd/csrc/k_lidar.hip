@@ -344,7 +344,7 @@ __device__ __forceinline__ void wave_range(float x, bool on, float* lo, float* h
 }
 
 // One workgroup per TS x TS tile of rays; batches of kLBatch records in LDS.
-// Culling in two steps.  First the bound stored in the record.
+// Culling in three steps.  First the bound stored in the record.
 // Angular rays: the wave bounds its rays by a cone (axis = their normalised
 // mean direction, half-angle beta = the widest ray), and a Gaussian stays when
 // its own cone (half-angle alpha around its centre direction, as used for the
@@ -360,23 +360,38 @@ __device__ __forceinline__ void wave_range(float x, bool on, float* lo, float* h
 // is a quadratic in (u, v) that is <= 0 exactly where q <= Q, Q the value at
 // which alpha falls to 1/255.  A Gaussian whose quadratic stays above a bound
 // for its rounding on the rectangle of the live rays is taken by none of them.
-// The rectangle is taken per quarter of the wave (8 x 2 rays, sixteen lanes),
-// and each quarter walks its own list of survivors: one LDS read instruction
-// serves four records, and a Gaussian costs only the quarters that it may meet.
+// Third, each ray evaluates the quadratics of the survivors at its own (u, v),
+// five multiply-adds each, into a mask, 32 survivors to a word, and evaluates
+// only those of its mask: the rays of a wave walk different survivors side by
+// side, each reading its own from LDS.  What is evaluated in full costs 33
+// vector instructions (48 with its blending) and four 16-byte LDS reads.
 // A 16 x 4 ray wave of a 32 x 1024 scan over 300k Gaussians of 0.03 m walks
-// 2900 candidates: the first step leaves 716, of which 286 are taken by some
-// ray; the quarters evaluate about 300 in turn, each 48 vector instructions and
-// four 16-byte LDS reads (these bound the kernel), the second test costs about
-// 250 instructions per 64 candidates.  512 such scans: 26.7 ms with the first
-// step alone, 21.2 with the second per wave, 20.8 per quarter; 512 heightmaps of
-// 64 x 64 rays 16.2, 11.3, 9.2 ms; 64 rosette scans of 24,576 rays 10.3, 7.1, 6.1 ms.
+// 2900 candidates: the first step leaves 759, the second 346, the third 87 per
+// ray, of which 64 are taken; the longest mask of each word adds up to 167, for
+// which the lanes evaluate together.  (A heightmap's wave: 2252, 1224, 87, 62
+// and 349; a rosette's: 336, 140, 83, 60 and 93.)  Before, each quarter of a
+// wave walked the survivors of its own rectangle, about 300 in a scan.  512
+// scans 17.5 -> 17.1 ms with the third step, 512 heightmaps of 64 x 64 rays
+// 7.5 -> 7.1 ms, 64 rosette scans of 24,576 rays 2.55 -> 2.20 ms; without any
+// but the first 26.7, 16.2 and 10.3 ms.  Measured and no faster: waves without
+// shared staging (17.1, 7.7, 2.18 ms: four times the reads miss L2, 18.7 GB
+// instead of 8.8 a pass), survivors kept in two halves so that a ray may lag
+// (18.1, 7.9, 2.4 ms), masks of 96 survivors (18.9, 7.8, 2.3 ms).
 template <int TS>
 struct LidarLds {
     float4 sr[kLidarStage][TS * TS];
     uint32_t live_w[2][TS * TS / 64];     // per wave: live rays left after a batch (by batch parity)
     uint8_t pick[TS * TS / 64][TS * TS];        // per wave: the batch's candidates that the first step keeps
-    uint8_t quart[TS * TS / 64][4][TS * TS];    // per quarter of a wave: those that the second step keeps
+    float quad[TS * TS / 64][64 * 6];           // those the second step keeps: their quadratics less the bound,
+                                                // a11, 2 a12, a22, 2 b1, 2 b2, f0 - bound
+    uint8_t surv[TS * TS / 64][64];             // and their places in the batch
 };
+
+// m = 2 m + (f > 0 ? 0 : 1), in two instructions
+__device__ __forceinline__ void shift_in(uint32_t& m, float f)
+{
+    asm("v_cmp_nlt_f32 vcc, 0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(m) : "v"(f) : "vcc");
+}
 
 template <int TS, bool GRID>
 __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c, int i, const ImageInfo& im, int tx,
@@ -457,35 +472,34 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
         ru = dot3(d, e1) * dw;
         rv = dot3(d, e2) * dw;
     }
-    // per quarter, the rectangle of the live rays' points, taken again whenever
-    // a quarter of them have stopped; the second step needs rays within about
-    // 45 degrees of the axis
-    float u0[4], u1[4], v0[4], v1[4];
+    // the rectangle of the live rays' points, taken again whenever a quarter of
+    // them have stopped; the second step needs rays within about 45 degrees of
+    // the axis
+    float u0, u1, v0, v1;
     const bool tight = GRID || (cull && cb > 0.75f);
     auto live_rect = [&](bool on) {
         float r[4] = {on ? ru : 3.0e38f, on ? -ru : 3.0e38f, on ? rv : 3.0e38f, on ? -rv : 3.0e38f};
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
 #pragma unroll
-            for (int m = 1; m < 16; m <<= 1) r[k] = fminf(r[k], __shfl_xor(r[k], m, 64));
+            for (int m = 1; m < 64; m <<= 1) r[k] = fminf(r[k], __shfl_xor(r[k], m, 64));
         }
         const float pu = 4e-6f * (1.0f + fmaxf(fabsf(r[0]), fabsf(r[1])));
         const float pv = 4e-6f * (1.0f + fmaxf(fabsf(r[2]), fabsf(r[3])));
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            u0[q] = lane_value(r[0] - pu, 16 * q);
-            u1[q] = lane_value(pu - r[1], 16 * q);
-            v0[q] = lane_value(r[2] - pv, 16 * q);
-            v1[q] = lane_value(pv - r[3], 16 * q);
-        }
+        u0 = lane_value(r[0] - pu, 0);
+        u1 = lane_value(pu - r[1], 0);
+        v0 = lane_value(r[2] - pv, 0);
+        v1 = lane_value(pv - r[3], 0);
     };
+    const float uu = ru * ru, uv = ru * rv, vv = rv * rv;
 
     const float um = fmaxf(fabsf(bx0), fabsf(bx1)), vm = fmaxf(fabsf(by0), fabsf(by1));     // grid: largest |u|, |v|
     bool live = inside;
     uint32_t rect_rays = (uint32_t)__popcll(__ballot(live));
     live_rect(live);
     uint8_t* const pick = L_.pick[tid >> 6];
-    uint8_t (*const quart)[NT] = L_.quart[tid >> 6];
+    float* const quad = L_.quad[tid >> 6];
+    uint8_t* const surv = L_.surv[tid >> 6];
     float T = 1.0f, Rg = 0.0f;
     // returns at t* <= reach are not taken: the sensor's near range, infinity once the ray has stopped
     float reach = inside ? im.near_plane : INFINITY;
@@ -563,12 +577,57 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
             n_pick += (uint32_t)__popcll(kept);
         }
         wave_lds_sync();
-        uint32_t n_q[4] = {0u, 0u, 0u, 0u};
         const uint64_t live_m = __ballot(live);
         if (tight && 4u * (uint32_t)__popcll(live_m) <= 3u * rect_rays) {
             rect_rays = (uint32_t)__popcll(live_m);
             live_rect(live);
         }
+        auto eval = [&](int j, float* ts_out, float* la_out) {
+            const float4 m0 = sr[0][j], m1 = sr[1][j], m2 = sr[2][j], m3 = sr[3][j];
+            float tstar, px, py, pz;
+            if (GRID) {
+                // centre relative to the ray origin, and W times it
+                px = m0.w - ox;
+                py = m1.w - oy;
+                const float wcx = m3.y - fmaf(m0.y, oy, m0.x * ox);
+                const float wcy = m3.z - fmaf(m1.y, oy, m1.x * ox);
+                const float wcz = m3.w - fmaf(m2.y, oy, m2.x * ox);
+                tstar = fmaf(-m2.z, wcz, fmaf(-m1.z, wcy, -m0.z * wcx)) * sr[4][j].w;
+                pz = m2.w + tstar;
+            } else {
+                // d' = W d
+                const float dx = fmaf(m0.z, d[2], fmaf(m0.y, d[1], m0.x * d[0]));
+                const float dy = fmaf(m1.z, d[2], fmaf(m1.y, d[1], m1.x * d[0]));
+                const float dz = fmaf(m2.z, d[2], fmaf(m2.y, d[1], m2.x * d[0]));
+                const float aa = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
+                const float bb = fmaf(dz, m3.w, fmaf(dy, m3.z, dx * m3.y));
+                tstar = bb * __builtin_amdgcn_rcpf(aa);
+                // offset of the centre from the ray's closest point, in metres
+                px = fmaf(-tstar, d[0], m0.w);
+                py = fmaf(-tstar, d[1], m1.w);
+                pz = fmaf(-tstar, d[2], m2.w);
+            }
+            // the offset whitened
+            const float wx = fmaf(m0.z, pz, fmaf(m0.y, py, m0.x * px));
+            const float wy = fmaf(m1.z, pz, fmaf(m1.y, py, m1.x * px));
+            const float wz = fmaf(m2.z, pz, fmaf(m2.y, py, m2.x * px));
+            const float qq = fmaf(wz, wz, fmaf(wy, wy, wx * wx));
+            *ts_out = tstar;
+            *la_out = fmaf(-0.72134752044448170f, qq, m3.x);      // log2 o - q/2 log2 e
+        };
+        auto take = [&](float tstar, float la) {
+            if (tstar > reach && la >= kLidarLogAlphaMin) {
+                // only the rays that take the Gaussian run this (exec mask);
+                // the empty asm keeps it a branch rather than selects
+                asm volatile("");
+                const float alpha = fminf(0.99f, __builtin_amdgcn_exp2f(la));
+                const float Tn = fmaf(-T, alpha, T);
+                const bool stop = Tn < 1e-4f;           // stops here, adds nothing
+                Rg = stop ? Rg : fmaf(tstar, alpha * T, Rg);
+                T = stop ? T : Tn;
+                reach = stop ? INFINITY : reach;
+            }
+        };
         for (uint32_t p0 = 0; p0 < n_pick && wave_live; p0 += 64) {
             const bool have = p0 + (uint32_t)lane < n_pick;
             const int jp = have ? (int)pick[p0 + (uint32_t)lane] : 0;
@@ -614,89 +673,71 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
                     qd.b1 = fmaf(k, dot3(a0, a1), -h0 * h1);
                     qd.b2 = fmaf(k, dot3(a0, a2), -h0 * h2);
                     qd.f0 = fmaf(k, n0, -h0 * h0);
-                    bound = cc > 2.0f * Q ? 2e-6f * cc * (n0 + n1 + n2) : INFINITY;      // the sensor well outside
+                    // f's own rounding, below 2e-6, and that of the rays' (u, v), which moves a direction by
+                    // 1.3e-6 and f where it is near 0 by at most 3.5e-6 sqrt(Q / |c|^2) of the same product
+                    bound = cc > 2.0f * Q ? 5e-6f * cc * (n0 + n1 + n2) : INFINITY;      // the sensor well outside
                 }
             }
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                if (((live_m >> (16 * q)) & 0xFFFFull) == 0ull) continue;       // wave-uniform
-                const bool keep = have && !(tight && above_on_rect(qd, u0[q], u1[q], v0[q], v1[q], bound));
-                const uint64_t kept = __ballot(keep);
-                if (keep) quart[q][n_q[q] + lanes_below(kept)] = (uint8_t)jp;
-                n_q[q] += (uint32_t)__popcll(kept);
+            const bool keep = have && !(tight && above_on_rect(qd, u0, u1, v0, v1, bound));
+            const uint64_t kept = __ballot(keep);
+            const uint32_t n_s = (uint32_t)__popcll(kept);
+            if (keep) {
+                const uint32_t r = lanes_below(kept);
+                float2* qp = reinterpret_cast<float2*>(&quad[6u * r]);
+                qp[0] = make_float2(qd.a11, 2.0f * qd.a12);
+                qp[1] = make_float2(qd.a22, 2.0f * qd.b1);
+                qp[2] = make_float2(2.0f * qd.b2, qd.f0 - bound);
+                surv[r] = (uint8_t)jp;
             }
+            wave_lds_sync();
+            // third step: each ray evaluates the quadratics at its own point
+            // and walks those that do not stay above the bound there
+            for (uint32_t s0 = 0; s0 < n_s; s0 += 32u) {
+                const uint32_t some = min(32u, n_s - s0);
+                uint32_t mask = 0;
+                for (uint32_t k = (some + 1u) & ~1u; k != 0u; k -= 2u) {
+                    const float4* qp = reinterpret_cast<const float4*>(&quad[6u * (s0 + k - 2u)]);
+                    const float4 q0 = qp[0], q1 = qp[1], q2 = qp[2];
+                    const float fa = fmaf(q0.x, uu, fmaf(q0.y, uv, fmaf(q0.z, vv, fmaf(q0.w, ru, fmaf(q1.x, rv, q1.y)))));
+                    const float fb = fmaf(q1.z, uu, fmaf(q1.w, uv, fmaf(q2.x, vv, fmaf(q2.y, ru, fmaf(q2.z, rv, q2.w)))));
+                    shift_in(mask, fb);
+                    shift_in(mask, fa);
+                }
+                // (an odd count's last pair holds one of an earlier group)
+                mask &= some == 32u ? 0xFFFFFFFFu : (1u << some) - 1u;
+                if (!(reach < INFINITY)) mask = 0u;
+                // two at a time: both are evaluated (independent dependency
+                // chains the wave interleaves), then composited in list order
+                auto next = [&]() {             // place of the lowest of the mask in the batch
+                    const uint32_t j = (s0 + (uint32_t)__builtin_ctz(mask)) & 63u;
+                    mask &= mask - 1u;
+                    return (int)surv[j] & (NT - 1);
+                };
+                bool a_on = mask != 0u;
+                int ja = next();
+                bool b_on = mask != 0u;
+                int jb = next();
+                while (a_on) {
+                    const int j0 = ja, j1 = jb;
+                    const bool two = b_on;
+                    a_on = mask != 0u;
+                    ja = next();
+                    b_on = mask != 0u;
+                    jb = next();
+                    float t0, l0, t1, l1;
+                    eval(j0, &t0, &l0);
+                    eval(j1, &t1, &l1);
+                    l1 = two ? l1 : -INFINITY;
+                    // both are complete before the first is taken: two independent chains
+                    asm volatile("" : "+v"(t0), "+v"(l0), "+v"(t1), "+v"(l1));
+                    take(t0, l0);
+                    take(t1, l1);
+                }
+            }
+            wave_lds_sync();
         }
-        wave_lds_sync();
-        {
-            // survivors two at a time: both are evaluated (independent
-            // dependency chains the wave interleaves), then composited in list order
-            auto eval = [&](int j, float* ts_out, float* la_out) {
-                const float4 m0 = sr[0][j], m1 = sr[1][j], m2 = sr[2][j], m3 = sr[3][j];
-                float tstar, px, py, pz;
-                if (GRID) {
-                    // centre relative to the ray origin, and W times it
-                    px = m0.w - ox;
-                    py = m1.w - oy;
-                    const float wcx = m3.y - fmaf(m0.y, oy, m0.x * ox);
-                    const float wcy = m3.z - fmaf(m1.y, oy, m1.x * ox);
-                    const float wcz = m3.w - fmaf(m2.y, oy, m2.x * ox);
-                    tstar = fmaf(-m2.z, wcz, fmaf(-m1.z, wcy, -m0.z * wcx)) * sr[4][j].w;
-                    pz = m2.w + tstar;
-                } else {
-                    // d' = W d
-                    const float dx = fmaf(m0.z, d[2], fmaf(m0.y, d[1], m0.x * d[0]));
-                    const float dy = fmaf(m1.z, d[2], fmaf(m1.y, d[1], m1.x * d[0]));
-                    const float dz = fmaf(m2.z, d[2], fmaf(m2.y, d[1], m2.x * d[0]));
-                    const float aa = fmaf(dz, dz, fmaf(dy, dy, dx * dx));
-                    const float bb = fmaf(dz, m3.w, fmaf(dy, m3.z, dx * m3.y));
-                    tstar = bb * __builtin_amdgcn_rcpf(aa);
-                    // offset of the centre from the ray's closest point, in metres
-                    px = fmaf(-tstar, d[0], m0.w);
-                    py = fmaf(-tstar, d[1], m1.w);
-                    pz = fmaf(-tstar, d[2], m2.w);
-                }
-                // the offset whitened
-                const float wx = fmaf(m0.z, pz, fmaf(m0.y, py, m0.x * px));
-                const float wy = fmaf(m1.z, pz, fmaf(m1.y, py, m1.x * px));
-                const float wz = fmaf(m2.z, pz, fmaf(m2.y, py, m2.x * px));
-                const float qq = fmaf(wz, wz, fmaf(wy, wy, wx * wx));
-                *ts_out = tstar;
-                *la_out = fmaf(-0.72134752044448170f, qq, m3.x);      // log2 o - q/2 log2 e
-            };
-            auto take = [&](float tstar, float la) {
-                if (tstar > reach && la >= kLidarLogAlphaMin) {
-                    // only the rays that take the Gaussian run this (exec mask);
-                    // the empty asm keeps it a branch rather than selects
-                    asm volatile("");
-                    const float alpha = fminf(0.99f, __builtin_amdgcn_exp2f(la));
-                    const float Tn = fmaf(-T, alpha, T);
-                    const bool stop = Tn < 1e-4f;           // stops here, adds nothing
-                    Rg = stop ? Rg : fmaf(tstar, alpha * T, Rg);
-                    T = stop ? T : Tn;
-                    reach = stop ? INFINITY : reach;
-                }
-            };
-            // each quarter walks its own list: the reads of a pair of records
-            // take the same LDS instructions as one list for the wave would
-            const uint32_t my_n = quarter == 0 ? n_q[0] : quarter == 1 ? n_q[1] : quarter == 2 ? n_q[2] : n_q[3];
-            const uint32_t most = max(max(n_q[0], n_q[1]), max(n_q[2], n_q[3]));
-            uint32_t jj = *reinterpret_cast<const uint16_t*>(&quart[quarter][0]);
-            for (uint32_t k = 0; k < most; k += 2) {
-                const int j0 = (int)(jj & (uint32_t)(NT - 1)), j1 = (int)((jj >> 8) & (uint32_t)(NT - 1));
-                jj = *reinterpret_cast<const uint16_t*>(&quart[quarter][(k + 2u) & (uint32_t)(NT - 1)]);
-                if (k >= my_n) continue;
-                float t0, l0, t1, l1;
-                eval(j0, &t0, &l0);
-                eval(j1, &t1, &l1);
-                l1 = k + 1u < my_n ? l1 : -INFINITY;
-                // both are complete before the first is taken: two independent chains
-                asm volatile("" : "+v"(t0), "+v"(l0), "+v"(t1), "+v"(l1));
-                take(t0, l0);
-                take(t1, l1);
-            }
-            live = reach < INFINITY;
-            if (__ballot(live) == 0ull) wave_live = false;
-        }
+        live = reach < INFINITY;
+        if (__ballot(live) == 0ull) wave_live = false;
         if (lane == 0) live_w[par][tid >> 6] = wave_live ? 1u : 0u;
     }
     if (bad_entry) atomicOr(c.err, kErrListEntry);

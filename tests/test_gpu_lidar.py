@@ -367,6 +367,33 @@ def test_ellipsoid_culling_matches_oracle(ts, shape):
     r.close()
 
 
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 63, 64, 65, 257])
+def test_ray_masks_at_word_and_batch_edges(R, n):
+    """n faint Gaussians that every ray of a tile meets, so that n counts a
+    wave's survivors: single, odd, and around a mask word, a group of 64 and a
+    batch; every seventh is small and opaque."""
+    rng = np.random.default_rng(900 + n)
+    small = np.arange(n) % 7 == 6
+    means = rng.uniform([-0.3, -0.3, 1.5], [0.3, 0.3, 3.0], (n, 3))
+    scene = scene_from(means, np.where(small[:, None], 0.04, 0.7) * np.ones((n, 3)), quats=rng.standard_normal((n, 4)),
+                       opac=np.where(small, 0.97, 0.03), degree=0)
+    grid = synth.height_grid(16, 16, 0.05)
+    scan = synth.LidarSpec(width=16, height=16, az0=-0.2, az_step=0.025,
+                           elevations=np.linspace(-0.2, 0.2, 16).astype(np.float32), near_range=0.05)
+    # the grid looks down on the Gaussians from above, the scan along them
+    down = np.concatenate([np.eye(3), [[0.0], [0.0], [-4.0]]], axis=1)
+    along = np.array([[0.0, 0.0, 1.0, 0.0], [1.0, 0.0, 0.0, 0.0], [0.0, 1.0, 0.0, 0.0]])
+    batch = synth.LidarBatch(cams=[grid, scan], viewmats=np.stack([down, along])[:, None].astype(np.float32),
+                             poses=np.zeros((1, 0, 7), np.float32))
+    sid = R.add_synth_scene(scene)
+    out = R.render_lidar(sid, [grid, scan], *_tensors(batch))
+    for l in range(2):
+        ref = lidar_ref(scene, batch, l, 0)
+        _compare(out[l][0][0].cpu().numpy(), out[l][1][0].cpu().numpy(), ref, f"n {n} slot {l}", scene, batch, l, 0,
+                 min_hits=1 if n > 30 else 0)
+    R.remove_scene(sid)
+
+
 @pytest.mark.parametrize("el_lo,el_hi,az0,width", [(-89.0, 89.0, -180.0, 360), (86.0, 89.9, 10.0, 90),
                                                    (-60.0, 20.0, -7.0, 8192)])
 def test_angular_bounds_at_poles_and_many_columns(R, el_lo, el_hi, az0, width):
