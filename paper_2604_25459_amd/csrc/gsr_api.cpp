@@ -492,7 +492,6 @@ int raster_params(gsr_ctx* ctx, Workspace& ws, const RenderJob& job, int i0, int
         while (m < n_img && imgs[i0 + m].width == a.width && imgs[i0 + m].height == a.height) ++m;
         if (rp.n_segs >= kMaxSegs) return fail(GSR_E_INVALID, "more than 8 image sizes in one chunk");
         RasterSeg& sg = rp.segs[rp.n_segs++];
-        sg.first_tile = blocks;
         sg.first_image = (uint32_t)k;
         sg.n_images = (uint32_t)(m - k);
         sg.tiles_per_image = (uint32_t)(a.tiles_x * a.tiles_y);

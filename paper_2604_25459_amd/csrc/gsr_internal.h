@@ -75,7 +75,6 @@ struct SceneDev {
 
 // Segment of the chunk that shares one camera slot (uniform resolution).
 struct RasterSeg {
-    uint32_t first_tile;   // first block id of the segment
     uint32_t first_image;  // first chunk-local image
     uint32_t n_images;
     uint32_t tiles_per_image;
@@ -295,6 +294,35 @@ __host__ __device__ inline uint32_t xcd_remap(uint32_t b, uint32_t G)
 {
     const uint32_t q = G / kXcds, r = G % kXcds, x = b % kXcds, k = b / kXcds;
     return x * q + (x < r ? x : r) + k;
+}
+
+// The k-th tile of part x of a chunk's tiles cut into `parts` parts (the XCDs
+// that have workgroups): chunk-local image and tile in it.  Each segment is
+// cut into contiguous ranges by itself, its remainder dealt out from where the
+// last segment's ended, so that parts differ by at most one tile in all and
+// every part gets its share of every image size.  One cut through all segments
+// gave the first XCD the images of the first: the 256 wrist views of 128x128
+// before 256 head views of 640x480 kept it busy to 13.9 ms, the others to 10.5.
+__host__ __device__ inline void tile_of(const RasterParams& p, uint32_t x, uint32_t k, uint32_t parts, int* image,
+                                        uint32_t* tile)
+{
+    uint32_t from = 0;                  // part that takes the segment's first extra tile
+    RasterSeg seg = p.segs[0];
+    uint32_t rel;
+    for (int s = 0;;) {
+        const uint32_t n = seg.n_images * seg.tiles_per_image, q = n / parts, r = n % parts;
+        const uint32_t xs = x >= from ? x - from : x + parts - from;
+        const uint32_t count = q + (xs < r ? 1u : 0u);
+        rel = xs * q + (xs < r ? xs : r) + k;
+        if (++s == p.n_segs || k < count) break;
+        k -= count;
+        from += r;
+        if (from >= parts) from -= parts;
+        seg = p.segs[s];
+    }
+    const uint32_t io = rel / seg.tiles_per_image;
+    *image = (int)(seg.first_image + io);
+    *tile = rel - io * seg.tiles_per_image;
 }
 
 }  // namespace gsr

@@ -754,16 +754,9 @@ template <int TS>
 __global__ __launch_bounds__(TS * TS) void k_raster_lidar(SceneDev s, ChunkDev c, RasterParams p)
 {
     __shared__ LidarLds<TS> lds;
-    const uint32_t bid = xcd_remap(blockIdx.x, gridDim.x);
-    int sgi = 0;
-#pragma unroll
-    for (int k = 1; k < kMaxSegs; ++k)
-        if (k < p.n_segs && bid >= p.segs[k].first_tile) sgi = k;
-    const RasterSeg seg = p.segs[sgi];
-    const uint32_t rel = bid - seg.first_tile;
-    const uint32_t io = rel / seg.tiles_per_image;
-    const uint32_t t = rel - io * seg.tiles_per_image;
-    const int i = (int)(seg.first_image + io);
+    int i;
+    uint32_t t;
+    tile_of(p, blockIdx.x % (uint32_t)kXcds, blockIdx.x / (uint32_t)kXcds, (uint32_t)kXcds, &i, &t);
     const ImageInfo im = c.img[i];
     const int tx = (int)(t % (uint32_t)im.tiles_x);
     const int ty = (int)(t / (uint32_t)im.tiles_x);

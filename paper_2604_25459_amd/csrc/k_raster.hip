@@ -173,12 +173,12 @@ struct FilterLds {
     uint32_t wcount[kRowScan / Layout<TS>::kThreads][Layout<TS>::kWaves];
 };
 
-// Composites tile `bid` of the chunk (block id in segment order).  FILTER:
-// the tile's list is filtered on the fly from the image's depth-ordered
+// Composites tile `k_tile` of part `part` of `parts` of the chunk.  FILTER: the
+// tile's list is filtered on the fly from the image's depth-ordered
 // Gaussians (Q holds the ring); else it is read from the tile lists.
 template <int TS, int kBatch, bool COUNT, bool FILTER>
-__device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c, const RasterParams& p, uint32_t bid,
-                                            RasterLds<TS, kBatch>& L_, FilterLds<TS>* Q)
+__device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c, const RasterParams& p, uint32_t part,
+                                            uint32_t k_tile, uint32_t parts, RasterLds<TS, kBatch>& L_, FilterLds<TS>* Q)
 {
     using L = Layout<TS>;
     constexpr int NT = L::kThreads;
@@ -192,15 +192,9 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
     auto& sB = L_.b;
     auto& sC = L_.c;
 
-    int sgi = 0;
-#pragma unroll
-    for (int k = 1; k < kMaxSegs; ++k)
-        if (k < p.n_segs && bid >= p.segs[k].first_tile) sgi = k;
-    const RasterSeg seg = p.segs[sgi];
-    const uint32_t rel = bid - seg.first_tile;
-    const uint32_t io = rel / seg.tiles_per_image;
-    const uint32_t t = rel - io * seg.tiles_per_image;
-    const int i = (int)(seg.first_image + io);
+    int i;
+    uint32_t t;
+    tile_of(p, part, k_tile, parts, &i, &t);
     const ImageInfo im = c.img[i];
     const int tx = (int)(t % (uint32_t)im.tiles_x);
     const int ty = (int)(t / (uint32_t)im.tiles_x);
@@ -550,12 +544,13 @@ __global__ __launch_bounds__(Layout<TS>::kThreads) void k_raster(SceneDev s, Chu
 {
     __shared__ RasterLds<TS, kBatch> lds;
     if (*c.ovf) return;                 // no tile lists: the fallback composites this chunk
-    raster_tile<TS, kBatch, COUNT, false>(s, c, p, xcd_remap(blockIdx.x, gridDim.x), lds, nullptr);
+    raster_tile<TS, kBatch, COUNT, false>(s, c, p, blockIdx.x % (uint32_t)kXcds, blockIdx.x / (uint32_t)kXcds,
+                                          (uint32_t)kXcds, lds, nullptr);
 }
 
-// Persistent workgroups.  The tiles are split into one contiguous range per
-// XCD that has workgroups (min(8, grid) of them); the workgroups of an XCD take
-// that range's tiles in image order from the XCD's own counter (zeroed by
+// Persistent workgroups.  The tiles are split into one part per XCD that has
+// workgroups (min(8, grid) of them, tile_of); the workgroups of an XCD take
+// that part's tiles in image order from the XCD's own counter (zeroed by
 // k_zero_counter before the launch), so concurrently shaded tiles share their
 // images' records in that XCD's L2.  Every workgroup exits once its counter
 // passes its range.
@@ -568,15 +563,14 @@ __global__ __launch_bounds__(Layout<TS>::kThreads) void k_raster_persistent(Scen
     if (*c.ovf) return;                 // no tile lists: the fallback composites this chunk
     const uint32_t parts = gridDim.x < (uint32_t)kXcds ? gridDim.x : (uint32_t)kXcds;
     const uint32_t x = blockIdx.x % (uint32_t)kXcds;       // < parts
-    const uint32_t q = p.n_blocks / parts, r = p.n_blocks % parts;
-    const uint32_t first = x * q + (x < r ? x : r), count = q + (x < r ? 1u : 0u);
+    const uint32_t count = p.n_blocks / parts + (x < p.n_blocks % parts ? 1u : 0u);
     for (;;) {
         if (threadIdx.x == 0) next = atomicAdd(&counter[x], 1u);
         __syncthreads();
         const uint32_t k = next;
         __syncthreads();
         if (k >= count) break;
-        raster_tile<TS, kBatch, COUNT, false>(s, c, p, first + k, lds, nullptr);
+        raster_tile<TS, kBatch, COUNT, false>(s, c, p, x, k, parts, lds, nullptr);
         __syncthreads();
     }
 }
@@ -597,15 +591,14 @@ __global__ __launch_bounds__(Layout<TS>::kThreads) void k_raster_fallback(SceneD
     if (!*c.ovf) return;
     const uint32_t parts = gridDim.x < (uint32_t)kXcds ? gridDim.x : (uint32_t)kXcds;
     const uint32_t x = blockIdx.x % (uint32_t)kXcds;       // < parts
-    const uint32_t q = p.n_blocks / parts, r = p.n_blocks % parts;
-    const uint32_t first = x * q + (x < r ? x : r), count = q + (x < r ? 1u : 0u);
+    const uint32_t count = p.n_blocks / parts + (x < p.n_blocks % parts ? 1u : 0u);
     for (;;) {
         if (threadIdx.x == 0) next = atomicAdd(&counter[x], 1u);
         __syncthreads();
         const uint32_t k = next;
         __syncthreads();
         if (k >= count) break;
-        raster_tile<TS, kB, COUNT, true>(s, c, p, first + k, lds, &ring);
+        raster_tile<TS, kB, COUNT, true>(s, c, p, x, k, parts, lds, &ring);
         __syncthreads();
     }
 }

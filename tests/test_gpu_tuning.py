@@ -369,3 +369,36 @@ def test_images_equal_on_both_sides_of_the_direct_line(ts):
         assert torch.equal(a, b[:line])
     assert float(some[2].amax()) > 0.5 and not torch.equal(some[0][0], some[0][line - 1])
     R.close()
+
+
+@pytest.mark.parametrize("persistent", [0, 1])
+@pytest.mark.parametrize("envs,sides", [(1, [(17, 16), (130, 47)]), (3, [(16, 16), (48, 16), (80, 33)]),
+                                        (5, [(97, 35), (16, 16), (64, 64), (33, 7), (16, 32)])])
+def test_several_image_sizes_in_a_launch(envs, sides, persistent):
+    """Image sizes whose tile counts leave every kind of remainder when the
+    tiles are dealt out: a launch over all of them gives the bits of launches
+    over each."""
+    torch = _torch()
+    from paper_2604_25459_amd import gsr
+    from tests.scenes import scene_from
+    rng = np.random.default_rng(envs)
+    n = 800
+    scene = scene_from(rng.uniform([-0.6, -0.6, 1.0], [0.6, 0.6, 3.0], (n, 3)), np.exp(rng.normal(-3.0, 0.8, (n, 3))),
+                       rng.standard_normal((n, 4)), rng.uniform(0.02, 1.0, n), rng.uniform(0, 1, (n, 1, 3)), 0)
+    R = gsr.Renderer(0)
+    sid = R.add_synth_scene(scene)
+    cams = [gsr.Camera(w, h, 60.0, 60.0, w / 2, h / 2, 0.01, -1) for w, h in sides]
+    views = torch.eye(4, device="cuda")[:3].repeat(len(sides), envs, 1, 1)
+    views[:, :, 0, 3] = torch.linspace(-0.3, 0.3, len(sides) * envs, device="cuda").view(len(sides), envs)
+    poses = torch.zeros(envs, 0, 7, device="cuda")
+    if persistent:
+        R.set_tuning(sid, cams, views, poses, persistent=1)
+    got = R.render(sid, cams, views, poses, alpha=True)
+    torch.cuda.synchronize()
+    for k, cam in enumerate(cams):
+        one = R.render(sid, [cam], views[k:k + 1].contiguous(), poses, alpha=True)[0]
+        torch.cuda.synchronize()
+        for a, b in zip(got[k], one):
+            assert torch.equal(a, b), (k, sides[k])
+        assert float(one[2].amax()) > 0.1
+    R.close()
