@@ -589,6 +589,14 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
             key.push_back(((uint64_t)job.imgs[i0 + k].width << 32) | (uint64_t)job.imgs[i0 + k].height);
     }
 
+    RasterParams rp{};
+    if (mode == Mode::kRender) {
+        const int r = raster_params(ctx, ws, job, i0, n_img, &rp);
+        if (r) return r;
+        // the tile counts' difference arrays are done with once the ranges are known
+        if (!rp.persistent && rp.n_blocks > kOrderTilesMin && rp.n_blocks <= kOrderTilesMax)
+            rp.order = reinterpret_cast<uint32_t*>(c.tile_hist);
+    }
     if (graph && async_lists && !prof && mode == Mode::kRender) {
         // nothing of this chunk waits for the host: its stages are one graph
         const int n_seg = ws.nseg_hint[chunk_idx];
@@ -599,9 +607,6 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
         c.pairs = ws.pairs.as<uint32_t>();
         c.rows = ws.rows.as<uint2>();
         uint32_t* seg_off = n_seg > 1 ? ws.seg_off.as<uint32_t>() : nullptr;
-        RasterParams rp{};
-        const int r = raster_params(ctx, ws, job, i0, n_img, &rp);
-        if (r) return r;
         for (uint64_t v : {(uint64_t)(uintptr_t)c.pairs, (uint64_t)(uintptr_t)c.rows, (uint64_t)n_seg,
                            (uint64_t)(uintptr_t)seg_off, (uint64_t)(uintptr_t)rp.counter, (uint64_t)rp.count_work,
                            (uint64_t)(uintptr_t)c.fallback_counter})
@@ -611,7 +616,7 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
             hipError_t e = launch_compose(s, c, q);
             if (e == hipSuccess) e = launch_project(s, c, tu.ts, ctx->opt.cutoff, tu.ipt, q);
             if (e == hipSuccess) e = launch_depth_sort(s, c, q);
-            if (e == hipSuccess) e = launch_tile_count(s, c, q);
+            if (e == hipSuccess) e = launch_tile_count(s, c, rp, q);
             if (e == hipSuccess) e = launch_tile_scatter(s, c, tu.bin, n_seg, seg_off, q);
             if (e == hipSuccess) e = launch_raster(s, c, rp, q);
             if (e == hipSuccess) e = launch_raster_fallback(s, c, rp, q);
@@ -632,7 +637,7 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
     if (rc) return rc;
     if (prof) GSR_HIP_TRY(hipEventRecord(ev.e[2], st));
     rc = run_stage(ws, graph, chunk_idx, 2, sc->uid, key, st, [&](hipStream_t q) {
-        return launch_tile_count(s, c, q);       // the totals end up in the host's memory or stay on the device
+        return launch_tile_count(s, c, rp, q);       // the totals end up in the host's memory or stay on the device
     });
     if (rc) return rc;
     if (prof) GSR_HIP_TRY(hipEventRecord(ev.e[3], st));
@@ -725,8 +730,6 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
     if (mode == Mode::kBins) return GSR_OK;
     if (prof) GSR_HIP_TRY(hipEventRecord(ev.e[4], st));
 
-    RasterParams rp{};
-    if ((rc = raster_params(ctx, ws, job, i0, n_img, &rp)) != GSR_OK) return rc;
     if (graph) {
         key.push_back((uint64_t)(uintptr_t)rp.counter);
         key.push_back((uint64_t)rp.count_work);

@@ -235,8 +235,10 @@ hipError_t launch_compose(const SceneDev& s, const ChunkDev& c, hipStream_t stre
 hipError_t launch_project(const SceneDev& s, const ChunkDev& c, int ts, float cutoff, int img_per_thread,
                           hipStream_t stream);
 hipError_t launch_depth_sort(const SceneDev& s, const ChunkDev& c, hipStream_t stream);
-// Tile and tile-row histograms, ranges, image bases (before the host reads the totals).
-hipError_t launch_tile_count(const SceneDev& s, const ChunkDev& c, hipStream_t stream);
+// Tile and tile-row histograms, ranges, image bases (before the host reads the
+// totals), and the order of the tiles where p asks for one.
+struct RasterParams;
+hipError_t launch_tile_count(const SceneDev& s, const ChunkDev& c, const RasterParams& p, hipStream_t stream);
 // LiDAR: projection into the ray grid (keys = centre distance, conservative
 // angular tile rectangles, 64-byte whitening and cone records) and per-ray compositing.
 hipError_t launch_project_lidar(const SceneDev& s, const ChunkDev& c, int ts, int ipt, hipStream_t stream);
@@ -260,7 +262,14 @@ struct RasterParams {
     int n_segs;
     RasterSeg segs[kMaxSegs];
     uint32_t n_blocks;
+    uint32_t* order;         // heavy-first order of each XCD's part (launch_tile_order), or null: as they come
 };
+// Launches of more than kOrderTilesMin tiles (up to that all are resident at
+// once: five workgroups per CU) and at most kOrderTilesMax take their tiles
+// heavy first.  Above, the longest tile is a small part of the launch, and the
+// ordering blocks would have more than eight tiles a thread.
+constexpr uint32_t kOrderTilesMin = 1280;
+constexpr uint32_t kOrderTilesMax = 65536;
 hipError_t launch_raster_lidar(const SceneDev& s, const ChunkDev& c, const RasterParams& p, hipStream_t stream);
 hipError_t launch_raster(const SceneDev& s, const ChunkDev& c, const RasterParams& p, hipStream_t stream);
 // Fallback compositing of a chunk whose lists overflowed (a persistent grid
@@ -323,6 +332,15 @@ __host__ __device__ inline void tile_of(const RasterParams& p, uint32_t x, uint3
     const uint32_t io = rel / seg.tiles_per_image;
     *image = (int)(seg.first_image + io);
     *tile = rel - io * seg.tiles_per_image;
+}
+
+// The tile of workgroup b of a launch of p.n_blocks workgroups, one per tile.
+__device__ __forceinline__ void tile_of_block(const RasterParams& p, uint32_t b, int* image, uint32_t* tile)
+{
+    const uint32_t x = b % (uint32_t)kXcds;
+    uint32_t k = b / (uint32_t)kXcds;
+    if (p.order) k = p.order[xcd_remap(b, p.n_blocks)];
+    tile_of(p, x, k, (uint32_t)kXcds, image, tile);
 }
 
 }  // namespace gsr

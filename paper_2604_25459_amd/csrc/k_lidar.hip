@@ -756,7 +756,7 @@ __global__ __launch_bounds__(TS * TS) void k_raster_lidar(SceneDev s, ChunkDev c
     __shared__ LidarLds<TS> lds;
     int i;
     uint32_t t;
-    tile_of(p, blockIdx.x % (uint32_t)kXcds, blockIdx.x / (uint32_t)kXcds, (uint32_t)kXcds, &i, &t);
+    tile_of_block(p, blockIdx.x, &i, &t);
     const ImageInfo im = c.img[i];
     const int tx = (int)(t % (uint32_t)im.tiles_x);
     const int ty = (int)(t / (uint32_t)im.tiles_x);

@@ -173,12 +173,11 @@ struct FilterLds {
     uint32_t wcount[kRowScan / Layout<TS>::kThreads][Layout<TS>::kWaves];
 };
 
-// Composites tile `k_tile` of part `part` of `parts` of the chunk.  FILTER: the
-// tile's list is filtered on the fly from the image's depth-ordered
+// Composites tile t of image i of the chunk.  FILTER: the tile's list is filtered on the fly from the image's depth-ordered
 // Gaussians (Q holds the ring); else it is read from the tile lists.
 template <int TS, int kBatch, bool COUNT, bool FILTER>
-__device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c, const RasterParams& p, uint32_t part,
-                                            uint32_t k_tile, uint32_t parts, RasterLds<TS, kBatch>& L_, FilterLds<TS>* Q)
+__device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c, const RasterParams& p, int i, uint32_t t,
+                                            RasterLds<TS, kBatch>& L_, FilterLds<TS>* Q)
 {
     using L = Layout<TS>;
     constexpr int NT = L::kThreads;
@@ -192,9 +191,6 @@ __device__ __forceinline__ void raster_tile(const SceneDev& s, const ChunkDev& c
     auto& sB = L_.b;
     auto& sC = L_.c;
 
-    int i;
-    uint32_t t;
-    tile_of(p, part, k_tile, parts, &i, &t);
     const ImageInfo im = c.img[i];
     const int tx = (int)(t % (uint32_t)im.tiles_x);
     const int ty = (int)(t / (uint32_t)im.tiles_x);
@@ -544,8 +540,10 @@ __global__ __launch_bounds__(Layout<TS>::kThreads) void k_raster(SceneDev s, Chu
 {
     __shared__ RasterLds<TS, kBatch> lds;
     if (*c.ovf) return;                 // no tile lists: the fallback composites this chunk
-    raster_tile<TS, kBatch, COUNT, false>(s, c, p, blockIdx.x % (uint32_t)kXcds, blockIdx.x / (uint32_t)kXcds,
-                                          (uint32_t)kXcds, lds, nullptr);
+    int i;
+    uint32_t t;
+    tile_of_block(p, blockIdx.x, &i, &t);
+    raster_tile<TS, kBatch, COUNT, false>(s, c, p, i, t, lds, nullptr);
 }
 
 // Persistent workgroups.  The tiles are split into one part per XCD that has
@@ -570,7 +568,10 @@ __global__ __launch_bounds__(Layout<TS>::kThreads) void k_raster_persistent(Scen
         const uint32_t k = next;
         __syncthreads();
         if (k >= count) break;
-        raster_tile<TS, kBatch, COUNT, false>(s, c, p, x, k, parts, lds, nullptr);
+        int i;
+        uint32_t t;
+        tile_of(p, x, k, parts, &i, &t);
+        raster_tile<TS, kBatch, COUNT, false>(s, c, p, i, t, lds, nullptr);
         __syncthreads();
     }
 }
@@ -598,7 +599,10 @@ __global__ __launch_bounds__(Layout<TS>::kThreads) void k_raster_fallback(SceneD
         const uint32_t k = next;
         __syncthreads();
         if (k >= count) break;
-        raster_tile<TS, kB, COUNT, true>(s, c, p, x, k, parts, lds, &ring);
+        int i;
+        uint32_t t;
+        tile_of(p, x, k, parts, &i, &t);
+        raster_tile<TS, kB, COUNT, true>(s, c, p, i, t, lds, &ring);
         __syncthreads();
     }
 }

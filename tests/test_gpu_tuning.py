@@ -402,3 +402,39 @@ def test_several_image_sizes_in_a_launch(envs, sides, persistent):
             assert torch.equal(a, b), (k, sides[k])
         assert float(one[2].amax()) > 0.1
     R.close()
+
+
+@pytest.mark.parametrize("n_img", [1281, 9001, 65536, 65543])
+def test_heavy_first_order_covers_every_tile(n_img):
+    """One-tile images, some with every Gaussian in view and most with few, in
+    launches just above the smallest that is ordered, in between, the largest
+    and above it: every image holds the bits of launches too small to be
+    ordered."""
+    torch = _torch()
+    from paper_2604_25459_amd import gsr
+    from tests.scenes import scene_from
+    rng = np.random.default_rng(n_img)
+    n = 200
+    scene = scene_from(rng.uniform([-0.3, -0.3, 1.0], [0.3, 0.3, 3.0], (n, 3)), np.exp(rng.normal(-3.5, 0.8, (n, 3))),
+                       rng.standard_normal((n, 4)), rng.uniform(0.02, 1.0, n), rng.uniform(0, 1, (n, 1, 3)), 0)
+    R = gsr.Renderer(0)
+    sid = R.add_synth_scene(scene)
+    cam = gsr.Camera(16, 16, 14.0, 14.0, 8.0, 8.0, 0.01, -1)
+    views = torch.eye(4, device="cuda")[:3].repeat(1, n_img, 1, 1)
+    views[0, :, 0, 3] = torch.from_numpy(rng.uniform(-3.0, 3.0, n_img).astype(np.float32)).cuda()
+    poses = torch.zeros(n_img, 0, 7, device="cuda")
+    rgb, depth, alpha = R.alloc_outputs([cam], n_img, True)
+    for t in (rgb, depth, alpha):
+        t.fill_(-7.0)
+    R.render_into(sid, [cam], views, poses, rgb, depth, alpha)
+    got = R.split([cam], n_img, rgb, depth, alpha)[0]
+    torch.cuda.synchronize()
+    for a in range(0, n_img, 1280):
+        b = min(n_img, a + 1280)
+        one = R.render(sid, [cam], views[:, a:b].contiguous(), poses[a:b], alpha=True)[0]
+        torch.cuda.synchronize()
+        for x, y in zip(got, one):
+            assert torch.equal(x[a:b], y), a
+    hit = (got[2].amax(dim=(1, 2)) > 0.1).float().mean()
+    assert 0.02 < float(hit) < 0.9
+    R.close()
