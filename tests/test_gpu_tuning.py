@@ -1,5 +1,6 @@
 """hipGraph replay and autotuned launch parameters change no pixel: every
 replay and every parameter set gives the bits of the eager default render."""
+import math
 import time
 
 import numpy as np
@@ -437,4 +438,33 @@ def test_heavy_first_order_covers_every_tile(n_img):
             assert torch.equal(x[a:b], y), a
     hit = (got[2].amax(dim=(1, 2)) > 0.1).float().mean()
     assert 0.02 < float(hit) < 0.9
+    R.close()
+
+
+@pytest.mark.parametrize("n", [1, 1023, 4096, 4097, 8192, 8193, 16384, 16385])
+@pytest.mark.parametrize("depths", ["near", "wide", "ties", "behind"])
+def test_depth_order_around_the_one_workgroup_sort(n, depths):
+    """Depth order and tile lists against the specification at the largest
+    counts of each one-workgroup sort and just above: depths of one digit's
+    span and of all four, equal depths, and nothing in view."""
+    _torch()
+    from oracle import bin_ref
+    from paper_2604_25459_amd import gsr
+    from tests.scenes import one_camera, scene_from
+    rng = np.random.default_rng(n)
+    z = {"near": rng.uniform(2.0, 2.0001, n), "wide": np.exp(rng.uniform(math.log(0.02), math.log(3.0e4), n)),
+         "ties": rng.integers(1, 4, n).astype(float), "behind": np.full(n, -1.0)}[depths]
+    means = np.stack([rng.uniform(-0.4, 0.4, n) * z, rng.uniform(-0.4, 0.4, n) * z, z], axis=1)
+    scene = scene_from(means, np.abs(z)[:, None] * rng.uniform(0.004, 0.02, (n, 3)), rng.standard_normal((n, 4)),
+                       rng.uniform(0.05, 0.99, n), rng.uniform(0, 1, (n, 1, 3)), 0)
+    batch = one_camera(70, 50, 60.0)
+    R = gsr.Renderer(0)
+    sid = R.add_synth_scene(scene)
+    cams, vm, poses = gsr.batch_tensors(batch)
+    got = R.debug_bins(sid, cams, vm, poses, 0)
+    ref = bin_ref(scene, batch, 0, 0, R.tile_size)
+    assert got["n_visible"] == int(ref.visible.sum()) and (got["n_visible"] > 0) == (depths != "behind")
+    np.testing.assert_array_equal(got["keys"], ref.keys)
+    np.testing.assert_array_equal(got["values"], ref.values)
+    np.testing.assert_array_equal(got["ranges"], ref.ranges)
     R.close()
