@@ -231,7 +231,10 @@ __device__ uint32_t scan_rows(uint32_t* H, int nb, int stride, int rows, uint32_
     uint32_t done = 0;
     for (int r0 = 0; r0 < rows; r0 += NT) {
         const int m = min(rows - r0, NT);               // rows of this round
-        const int segs = NT / m;                        // >= 1
+        // at least 16 blocks a segment: every thread adds up the segments before
+        // its own (170 of them for six rows and 64 blocks: k_tile_scan of one
+        // 128x96 image 13 -> 6.4 us, with the prefixes above read eight at a time)
+        const int segs = max(1, min(NT / m, nb / 16));
         const int sg = tid / m, r = tid - sg * m;
         const bool on = sg < segs;
         const int b0 = on ? (int)((int64_t)nb * sg / segs) : 0, b1 = on ? (int)((int64_t)nb * (sg + 1) / segs) : 0;
@@ -299,21 +302,24 @@ __global__ __launch_bounds__(NT) void k_tile_scan(ChunkDev c)
     const int32_t* hist = c.tile_hist + (size_t)i * (size_t)(c.tx_max + 1) * (c.ty_max + 1);
     for (int t = threadIdx.x; t < TY * P1; t += NT) gd[t] = hist[t];
     __syncthreads();
-    for (int y = threadIdx.x; y < TY; y += NT) {
+    // prefixes along the rows, then down the columns; eight reads at a time,
+    // their LDS latencies side by side
+    auto prefix = [&](int32_t* g, int count, int stride) {
         int32_t run = 0;
-        for (int x = 0; x < TX; ++x) {
-            run += gd[y * P1 + x];
-            gd[y * P1 + x] = run;
+        for (int k = 0; k < count; k += 8) {
+            int32_t v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = k + q < count ? g[(k + q) * stride] : 0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                run += v[q];
+                if (k + q < count) g[(k + q) * stride] = run;
+            }
         }
-    }
+    };
+    for (int y = threadIdx.x; y < TY; y += NT) prefix(gd + y * P1, TX, 1);
     __syncthreads();
-    for (int x = threadIdx.x; x < TX; x += NT) {
-        int32_t run = 0;
-        for (int y = 0; y < TY; ++y) {
-            run += gd[y * P1 + x];
-            gd[y * P1 + x] = run;
-        }
-    }
+    for (int x = threadIdx.x; x < TX; x += NT) prefix(gd + x, TY, P1);
     __syncthreads();
     uint32_t* range = c.tile_range + (size_t)i * c.t_max * 2;
     uint32_t P = 0;
@@ -412,7 +418,7 @@ __device__ __forceinline__ void order_tiles(const ChunkDev& c, const RasterParam
 // k_image_scan_order eight more, one per XCD, order its tiles meanwhile.
 __device__ __forceinline__ void image_scan(const ChunkDev& c)
 {
-    __shared__ uint64_t part[3][256];
+    __shared__ uint64_t part[3][4];
     const int tid = threadIdx.x;
     const int per = tid < 256 ? (c.n_img + 255) / 256 : 0;         // 256 threads scan
     uint64_t sp = 0, sr = 0, sv = 0;
@@ -424,27 +430,38 @@ __device__ __forceinline__ void image_scan(const ChunkDev& c)
             sv += c.n ? c.vis_count[i] : 0u;
         }
     }
-    if (tid < 256) {
-        part[0][tid] = sp;
-        part[1][tid] = sr;
-        part[2][tid] = sv;
+    // inclusive prefixes over the waves, then over the four waves' sums
+    uint64_t ip = sp, ir = sr, iv = sv;
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) {
+        const uint64_t a = __shfl_up(ip, m, 64), b = __shfl_up(ir, m, 64), v = __shfl_up(iv, m, 64);
+        if ((tid & 63) >= m) {
+            ip += a;
+            ir += b;
+            iv += v;
+        }
+    }
+    if (tid < 256 && (tid & 63) == 63) {
+        part[0][tid >> 6] = ip;
+        part[1][tid >> 6] = ir;
+        part[2][tid >> 6] = iv;
     }
     __syncthreads();
-    __shared__ uint64_t tot[3];
+    uint64_t tot[3] = {}, rp = ip - sp, rr = ir - sr;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        rp += k < (tid >> 6) ? part[0][k] : 0ull;
+        rr += k < (tid >> 6) ? part[1][k] : 0ull;
+#pragma unroll
+        for (int q = 0; q < 3; ++q) tot[q] += part[q][k];
+    }
     if (tid < 3) {
-        uint64_t run = 0;
-        for (int k = 0; k < 256; ++k) {
-            const uint64_t v = part[tid][k];
-            part[tid][k] = run;
-            run += v;
-        }
-        tot[tid] = run;
+        const uint64_t run = tid == 0 ? tot[0] : tid == 1 ? tot[1] : tot[2];
         if (tid == 0) c.pair_base[c.n_img] = run;
         else if (tid == 1) c.row_base[c.n_img] = run;
         else c.pair_base[c.n_img + 1] = run;
         atomicAdd(&c.acc[tid == 2 ? 0 : tid + 1], (unsigned long long)run);   // visible, pairs, row entries
     }
-    __syncthreads();
     if (tid == 0) {
         const uint32_t over = tot[0] > c.cap_pairs || tot[1] > c.cap_rows ? 1u : 0u;
         *c.ovf = over;
@@ -461,7 +478,6 @@ __device__ __forceinline__ void image_scan(const ChunkDev& c)
         }
     }
     if (c.fallback_counter && tid < kXcds) c.fallback_counter[tid] = 0u;
-    uint64_t rp = part[0][tid & 255], rr = part[1][tid & 255];
     for (int k = 0; k < per; ++k) {
         const int i = tid * per + k;
         if (i < c.n_img) {
