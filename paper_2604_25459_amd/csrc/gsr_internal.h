@@ -221,12 +221,15 @@ inline int tile_items_for(uint64_t n, uint64_t n_img, int tx_max, int ty_max)
 // its last ones, and short segments keep the launch from waiting for those (512
 // scans of 32 x 1024 rays, 1024 rows: 3.6 ms with 16 segments per row, 2.1 with
 // 128).  A launch that would stay below kLevel2FewWaves waves takes segments of
-// down to kRowSegEntriesFew entries: there the longest wave is what it waits for.
+// down to kRowSegEntriesFew entries: there the longest wave is what it waits for
+// (with 256 entries below 4096 waves and with 128 below 32768: one 128x96 image
+// 130.5 and 122.8 us, one 640x480 290 and 285, 64 rosette scans 1.85 and 1.71 ms;
+// 64 entries cost 37 images of 317x203 2 %).
 constexpr int kRowSegEntries = 512;
-constexpr int kRowSegEntriesFew = 256;
+constexpr int kRowSegEntriesFew = 128;
 constexpr int kLevel2Rows = 16384;
 constexpr int kLevel2Waves = 131072;
-constexpr int kLevel2FewWaves = 4096;
+constexpr int kLevel2FewWaves = 32768;
 constexpr int kMaxRowSegs = 128;
 
 // ------------------------------------------------------------ launchers
