@@ -937,17 +937,25 @@ __device__ __forceinline__ void line_finish(const LineLists<T>& L, uint32_t cur,
 // 128-byte line for each of up to 64 buckets.
 __host__ __device__ constexpr size_t line_lds_bytes(int buckets) { return 1024 + 128 * (size_t)buckets; }
 
-// Level 1, schedule 1.  Block (gx, i), wave wv: task gx * kWavesPerBlock + wv
+// Waves per workgroup of the schedule-1 kernels.  A workgroup keeps its LDS
+// (6 KB a wave at 40 buckets) until its longest wave ends, and the rows of an
+// image differ several times in length: with four waves k_rowtile_rank held
+// three waves per SIMD on average where LDS allows six.  2048 images of
+// 640x480: 71.5 ms with four, 69.5 with two, 69.0 with one, which costs small
+// launches 1 %.
+constexpr int kWavesRank = 2;
+
+// Level 1, schedule 1.  Block (gx, i), wave wv: task gx * kWavesRank + wv
 // over (block b of tile_items of image i's depth-ordered Gaussians, window of 64
 // tile rows); the block's rows start at its per-block row offsets.
-__global__ __launch_bounds__(64 * kWavesPerBlock) void k_row_rank(ChunkDev c, uint64_t n, int n_rw, int nb)
+__global__ __launch_bounds__(64 * kWavesRank) void k_row_rank(ChunkDev c, uint64_t n, int n_rw, int nb)
 {
     if (*c.ovf) return;                 // the chunk's lists do not fit: no lists (fallback raster)
     extern __shared__ uint4 lds4[];
     const int wv = (int)(threadIdx.x >> 6), lane = __lane_id();
     uint4* mine = lds4 + (size_t)wv * (line_lds_bytes(nb) / 16);
     const uint32_t L = xcd_remap(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y);
-    const int i = (int)(L / gridDim.x), task = (int)(L - (uint32_t)i * gridDim.x) * kWavesPerBlock + wv;
+    const int i = (int)(L / gridDim.x), task = (int)(L - (uint32_t)i * gridDim.x) * kWavesRank + wv;
     const int b = task / n_rw, rw = task - b * n_rw;
     const uint32_t V = c.n ? c.vis_count[i] : 0u;
     const uint32_t j0 = (uint32_t)b * (uint32_t)c.tile_items;
@@ -1005,9 +1013,9 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_row_rank(ChunkDev c, ui
     line_finish(lists, cur, first);
 }
 
-// Level 2, schedule 1.  Block (gx, i), wave wv: task gx * kWavesPerBlock + wv
+// Level 2, schedule 1.  Block (gx, i), wave wv: task gx * kWavesRank + wv
 // over ((tile row * n_seg + segment) * n_cc + window of 64 tile columns).
-__global__ __launch_bounds__(64 * kWavesPerBlock) void k_rowtile_rank(ChunkDev c, int n_seg, int n_cc,
+__global__ __launch_bounds__(64 * kWavesRank) void k_rowtile_rank(ChunkDev c, int n_seg, int n_cc,
                                                                       const uint32_t* __restrict__ seg_off, int nb)
 {
     if (*c.ovf) return;                 // the chunk's lists do not fit: no lists (fallback raster)
@@ -1015,7 +1023,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void k_rowtile_rank(ChunkDev c
     const int wv = (int)(threadIdx.x >> 6), lane = __lane_id();
     uint4* mine = lds4 + (size_t)wv * (line_lds_bytes(nb) / 16);
     const uint32_t L = xcd_remap(blockIdx.x + blockIdx.y * gridDim.x, gridDim.x * gridDim.y);
-    const int i = (int)(L / gridDim.x), task = (int)(L - (uint32_t)i * gridDim.x) * kWavesPerBlock + wv;
+    const int i = (int)(L / gridDim.x), task = (int)(L - (uint32_t)i * gridDim.x) * kWavesRank + wv;
     const int cc = task % n_cc, ys = task / n_cc;
     const int y = ys / n_seg, sg = ys - y * n_seg;
     const ImageInfo im = c.img[i];
@@ -1109,9 +1117,9 @@ hipError_t launch_tile_scatter(const SceneDev& s, const ChunkDev& c, int schedul
     const uint64_t n = (uint64_t)s.n;
     if (schedule == 1) {
         const int n_rw = (c.ty_max + 63) / 64, nb = std::min(c.ty_max, 64);
-        const unsigned rb = (unsigned)((c.tile_blocks * n_rw + kWavesPerBlock - 1) / kWavesPerBlock);
-        hipLaunchKernelGGL(k_row_rank, dim3(rb, (unsigned)c.n_img), dim3(64 * kWavesPerBlock),
-                           kWavesPerBlock * line_lds_bytes(nb), stream, c, n, n_rw, nb);
+        const unsigned rb = (unsigned)((c.tile_blocks * n_rw + kWavesRank - 1) / kWavesRank);
+        hipLaunchKernelGGL(k_row_rank, dim3(rb, (unsigned)c.n_img), dim3(64 * kWavesRank),
+                           kWavesRank * line_lds_bytes(nb), stream, c, n, n_rw, nb);
     } else {
         const unsigned rb = (unsigned)((c.tile_blocks + kWavesPerBlock - 1) / kWavesPerBlock);
         hipLaunchKernelGGL(k_row_scatter, dim3(rb, (unsigned)c.n_img), dim3(64 * kWavesPerBlock),
@@ -1126,10 +1134,10 @@ hipError_t launch_tile_scatter(const SceneDev& s, const ChunkDev& c, int schedul
     }
     if (schedule == 1) {
         const int n_cc = (c.tx_max + 63) / 64;
-        const unsigned tb = (unsigned)((c.ty_max * n_seg * n_cc + kWavesPerBlock - 1) / kWavesPerBlock);
+        const unsigned tb = (unsigned)((c.ty_max * n_seg * n_cc + kWavesRank - 1) / kWavesRank);
         const int nb = std::min(c.tx_max, 64);
-        hipLaunchKernelGGL(k_rowtile_rank, dim3(tb, (unsigned)c.n_img), dim3(64 * kWavesPerBlock),
-                           kWavesPerBlock * line_lds_bytes(nb), stream, c, n_seg, n_cc, (const uint32_t*)seg_off, nb);
+        hipLaunchKernelGGL(k_rowtile_rank, dim3(tb, (unsigned)c.n_img), dim3(64 * kWavesRank),
+                           kWavesRank * line_lds_bytes(nb), stream, c, n_seg, n_cc, (const uint32_t*)seg_off, nb);
     } else {
         const unsigned tb = (unsigned)((c.ty_max * n_seg + kWavesPerBlock - 1) / kWavesPerBlock);
         hipLaunchKernelGGL(k_rowtile_scatter, dim3(tb, (unsigned)c.n_img), dim3(64 * kWavesPerBlock),
