@@ -468,3 +468,37 @@ def test_depth_order_around_the_one_workgroup_sort(n, depths):
     np.testing.assert_array_equal(got["values"], ref.values)
     np.testing.assert_array_equal(got["ranges"], ref.ranges)
     R.close()
+
+
+@pytest.mark.parametrize("n", [1 << 23, (1 << 23) + 1])
+def test_depth_order_with_ids_of_23_bits_and_more(n):
+    """The most Gaussians whose ids share a word with the last digit, and one
+    more: all but 20,000 lie behind the camera, so that the lists are those of
+    the 20,000 alone, under their ids."""
+    _torch()
+    from paper_2604_25459_amd import gsr
+    from tests.scenes import one_camera, scene_from
+    rng = np.random.default_rng(23)
+    m = 20_000
+    z = rng.uniform(1.0, 9.0, m)
+    z[::7] = 4.0                                          # ties
+    means = np.stack([rng.uniform(-0.4, 0.4, m) * z, rng.uniform(-0.4, 0.4, m) * z, z], axis=1)
+    quats, opac, sh = rng.standard_normal((m, 4)), rng.uniform(0.05, 0.99, m), rng.uniform(0, 1, (m, 1, 3))
+    ids = np.sort(rng.choice(n, m, replace=False))
+    ids[-1] = n - 1
+    batch = one_camera(70, 50, 60.0)
+    cams, vm, poses = gsr.batch_tensors(batch)
+    R = gsr.Renderer(0)
+    sid = R.add_synth_scene(scene_from(means, np.full((m, 3), 0.01), quats, opac, sh, 0))
+    few = R.debug_bins(sid, cams, vm, poses, 0)
+    R.remove_scene(sid)
+    all_means = np.full((n, 3), -1.0)
+    all_quats, all_opac, all_sh = np.ones((n, 4)), np.full(n, 0.5), np.zeros((n, 1, 3))
+    all_means[ids], all_quats[ids], all_opac[ids], all_sh[ids] = means, quats, opac, sh
+    sid = R.add_synth_scene(scene_from(all_means, np.full((n, 3), 0.01), all_quats, all_opac, all_sh, 0))
+    got = R.debug_bins(sid, cams, vm, poses, 0)
+    assert got["n_visible"] == few["n_visible"] > 10_000
+    np.testing.assert_array_equal(got["keys"], few["keys"])
+    np.testing.assert_array_equal(got["values"], ids[few["values"].astype(np.int64)])
+    np.testing.assert_array_equal(got["ranges"], few["ranges"])
+    R.close()
