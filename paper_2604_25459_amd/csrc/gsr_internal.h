@@ -340,10 +340,14 @@ __host__ __device__ inline void tile_of(const RasterParams& p, uint32_t x, uint3
 // The tile of workgroup b of a launch of p.n_blocks workgroups, one per tile.
 __device__ __forceinline__ void tile_of_block(const RasterParams& p, uint32_t b, int* image, uint32_t* tile)
 {
-    const uint32_t x = b % (uint32_t)kXcds;
-    uint32_t k = b / (uint32_t)kXcds;
-    if (p.order) k = p.order[xcd_remap(b, p.n_blocks)];
-    tile_of(p, x, k, (uint32_t)kXcds, image, tile);
+    if (p.order) {
+        // (at most 65,536 tiles: both fit 16 bits)
+        const uint32_t v = p.order[xcd_remap(b, p.n_blocks)];
+        *image = (int)(v >> 16);
+        *tile = v & 0xFFFFu;
+        return;
+    }
+    tile_of(p, b % (uint32_t)kXcds, b / (uint32_t)kXcds, (uint32_t)kXcds, image, tile);
 }
 
 }  // namespace gsr

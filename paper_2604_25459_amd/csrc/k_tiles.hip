@@ -351,25 +351,70 @@ __global__ __launch_bounds__(NT) void k_tile_scan(ChunkDev c)
 // 6.1 ms, 64 rosette scans 2.15 -> 1.85 ms, 512 scans of 32 x 1024 (65,536
 // tiles) 17.3 -> 17.0 ms; camera launches of 9,620 tiles 503 -> 474 us, of
 // 32,768 tiles 3.26 -> 3.20 ms, of 19,200 unchanged within 0.5 %.
+// In a launch of 16 to 1,024 images of one size the images are first dealt to
+// the XCDs by their list entries, longest first, in rounds there and back: by
+// image order alone XCDs ended between 614 and 711 us in a launch of 64 images
+// of 320x240, between 219 and 279 in one of 37 of 317x203 (474 -> 450 us in
+// all; 64 rosette scans 1.72 -> 1.61 ms, 512 heightmaps 6.08 -> 5.96, 512 scans
+// 16.85 -> 16.54, 512 images of 128x128 3.15 -> 3.08, the 64 1.21 -> 1.19).
 constexpr int kOrderItems = (int)(kOrderTilesMax / kXcds / 1024);
 constexpr int kOrderClasses = 5;
+constexpr int kOrderImages = 1024;
 
 __device__ __forceinline__ void order_tiles(const ChunkDev& c, const RasterParams& p, uint32_t x)
 {
     __shared__ uint32_t cnt[kOrderClasses * kOrderItems * 16];
     __shared__ uint32_t wsum[16];
+    __shared__ uint32_t work[kOrderImages];
+    __shared__ uint16_t ranked[kOrderImages];
     const int tid = threadIdx.x, w = tid >> 6, lane = __lane_id();
     const uint32_t n = p.n_blocks / kXcds + (x < p.n_blocks % kXcds ? 1u : 0u);
     const uint32_t first = xcd_remap(x, p.n_blocks);
-    uint32_t len[kOrderItems], sum = 0;
+    // images of one size, from the longest lists to the shortest (ties by index)
+    const bool deal = p.n_segs == 1 && c.n_img >= 2 * kXcds && c.n_img <= kOrderImages;
+    if (deal) {
+        const uint32_t mine = tid < c.n_img ? c.pair_count[tid] : 0u;
+        if (tid < kOrderImages) work[tid] = mine;
+        __syncthreads();
+        if (tid < c.n_img) {
+            int r = 0;
+#pragma unroll 8
+            for (int k = 0; k < c.n_img; ++k) r += work[k] > mine || (work[k] == mine && k < tid) ? 1 : 0;
+            ranked[r] = (uint16_t)tid;
+        }
+        __syncthreads();
+    }
+    const uint32_t per_image = p.segs[0].tiles_per_image, rounds = (uint32_t)c.n_img / kXcds;
+    auto tile_at = [&](uint32_t k, uint32_t* i, uint32_t* t) {
+        if (deal) {
+            // whole images in rounds over the XCDs, there and back; the tiles
+            // of what is left of them in ranges
+            uint32_t rank = k / per_image;
+            *t = k - rank * per_image;
+            if (rank < rounds) {
+                rank = kXcds * rank + (rank & 1u ? kXcds - 1u - x : x);
+            } else {
+                const uint32_t rest = (uint32_t)(c.n_img % kXcds) * per_image;
+                const uint32_t rel = rest / kXcds * x + min(x, rest % kXcds) + (k - rounds * per_image);
+                rank = kXcds * rounds + rel / per_image;
+                *t = rel % per_image;
+            }
+            *i = ranked[rank];
+        } else {
+            int im;
+            tile_of(p, x, k, (uint32_t)kXcds, &im, t);
+            *i = (uint32_t)im;
+        }
+    };
+    uint32_t len[kOrderItems], at[kOrderItems], sum = 0;
 #pragma unroll
     for (int j = 0; j < kOrderItems; ++j) {
         const uint32_t k = (uint32_t)(1024 * j + tid);
         len[j] = 0u;
         if (k < n) {
-            int i;
-            uint32_t t;
-            tile_of(p, x, k, (uint32_t)kXcds, &i, &t);
+            uint32_t i, t;
+            tile_at(k, &i, &t);
+            at[j] = i << 16 | t;
             const uint32_t* R = c.tile_range + ((size_t)i * c.t_max + t) * 2;
             len[j] = R[1] - R[0];
         }
@@ -408,7 +453,7 @@ __device__ __forceinline__ void order_tiles(const ChunkDev& c, const RasterParam
 #pragma unroll
     for (int j = 0; j < kOrderItems; ++j) {
         const uint32_t k = (uint32_t)(1024 * j + tid);
-        if (k < n) p.order[first + cnt[(cls[j] * kOrderItems + j) * 16 + w] + below[j]] = k;
+        if (k < n) p.order[first + cnt[(cls[j] * kOrderItems + j) * 16 + w] + below[j]] = at[j];
     }
 }
 
