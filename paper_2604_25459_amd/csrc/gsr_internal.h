@@ -196,12 +196,14 @@ constexpr int kSortItems = kSortBlock * kSortIpt;   // 4096 items per block
 // Tile pass geometry: k_tile_hist counts kTileGauss depth-ordered Gaussians per
 // block; level 1 places `tile_items` of them per wave (tile_items_for).
 constexpr int kTileGauss = 4096;
-constexpr int kTileItemsMin = 256;
-constexpr int kLevel1Waves = 8192;
+constexpr int kTileItemsMin = 128;
+constexpr int kLevel1Waves = 16384;
 // Items per level-1 wave: a wave walks its items in dependent groups of 64, so
 // a launch of few images is cut into more, shorter waves until it has about
 // kLevel1Waves of them (a single 640x480 image of 300k Gaussians: one wave per
-// 4096 items took 201 us with 74 waves on the chip, 256 items 29 us).  Large
+// 4096 items took 201 us with 74 waves on the chip, 256 items 29 us; 128
+// instead of 256 as the least takes 5 us more off its 283 us, twice the waves
+// 1 % off 64 images of 320x240 and 1.6 % off 64 rosette scans).  Large
 // launches keep 4096: every block starts and ends its row lists with partial
 // lines, and the scan of block offsets grows with the blocks.  The rows counted
 // per block also have to fit the LDS of k_tile_hist beside its tile counts.
