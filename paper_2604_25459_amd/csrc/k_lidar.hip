@@ -107,10 +107,13 @@ __device__ __forceinline__ void columns_between(float a, float b, int n, int* k0
 // (64 bytes each) are written to LDS and stored back lane-contiguously, so
 // each store instruction writes 1 KB of consecutive records.  The image
 // descriptions come in as a restrict argument (uniform reads become scalar
-// loads).
+// loads).  Six waves per SIMD (80 registers; left alone the compiler takes 84,
+// which makes five): 512 heightmaps 6.00 -> 5.92 ms, 64 rosette scans 1.61 ->
+// 1.56, 512 scans of 32 x 1024 16.69 -> 16.56.  (The camera projection, at 125
+// registers and four waves, spills at five: 256 image pairs 20.6 -> 22.2 ms.)
 template <int ST>
-__global__ __launch_bounds__(256) void k_project_lidar(SceneDev s, ChunkDev c, const ImageInfo* __restrict__ imgs,
-                                                       int ts, int ipt)
+__global__ __launch_bounds__(256, 6) void k_project_lidar(SceneDev s, ChunkDev c, const ImageInfo* __restrict__ imgs,
+                                                          int ts, int ipt)
 {
     __shared__ float4 stage[4][kLidarRec * 64];
     // the elevation table of the current angular image (up to kLdsBeams beams;
