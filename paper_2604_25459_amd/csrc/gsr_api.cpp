@@ -589,6 +589,10 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
             key.push_back(((uint64_t)job.imgs[i0 + k].width << 32) | (uint64_t)job.imgs[i0 + k].height);
     }
 
+    // whether lists of every Gaussian in every tile and tile row would fit: then
+    // no fallback is launched (one 128x96 image of 4,096 Gaussians: 118.6 -> 117.2 us)
+    const uint64_t entries = (uint64_t)n_img * (uint64_t)s.n;
+    const bool may_overflow = entries * (uint64_t)c.t_max > c.cap_pairs || entries * (uint64_t)c.ty_max > c.cap_rows;
     RasterParams rp{};
     if (mode == Mode::kRender) {
         const int r = raster_params(ctx, ws, job, i0, n_img, &rp);
@@ -619,7 +623,7 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
             if (e == hipSuccess) e = launch_tile_count(s, c, rp, q);
             if (e == hipSuccess) e = launch_tile_scatter(s, c, tu.bin, n_seg, seg_off, q);
             if (e == hipSuccess) e = launch_raster(s, c, rp, q);
-            if (e == hipSuccess) e = launch_raster_fallback(s, c, rp, q);
+            if (e == hipSuccess && may_overflow) e = launch_raster_fallback(s, c, rp, q);
             return e;
         });
     }
@@ -741,7 +745,7 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
         rc = run_stage(ws, graph, chunk_idx, 4, sc->uid, key, st, [&](hipStream_t q) {
             hipError_t e = launch_raster(s, c, rp, q);
             // asynchronous lists: the fallback composites the chunk if its lists overflowed (else it exits at once)
-            if (e == hipSuccess && async_lists) e = launch_raster_fallback(s, c, rp, q);
+            if (e == hipSuccess && async_lists && may_overflow) e = launch_raster_fallback(s, c, rp, q);
             return e;
         });
     }
