@@ -151,7 +151,7 @@ struct RasterLds {
     uint32_t live[2][Layout<TS>::kWaves];
 };
 
-// Launches of at most this many tiles (with the default batch) use the direct
+// Launches of at most kDirectTiles tiles (with the default batch) use the direct
 // kernel: no staging, no barrier; each wave reads its 64 candidates, a lane
 // each, into registers one batch ahead and their ids two ahead, and stops as
 // soon as its own pixels have.  There the time is a few long lists' latency
@@ -164,7 +164,26 @@ struct RasterLds {
 // (19,200), 1.28 and 1.25 ms; 512 of 128x128 (32,768), 3.25 and 3.24; 256
 // pairs of 128x128 and 640x480 (323,584), 22.6 and 23.5; 2048 of 640x480, 71
 // to 72 both.
+// Where the images are so small that several share an XCD's workgroups, and
+// their records its 4 MB of L2, the fourfold reads leave it: 200 images of
+// 128x128 of 140k Gaussians (12,800 tiles) 1.64 ms staged, 1.77 direct, 380 of
+// them 3.00 and 3.28, but 300 of 128x96 of 30k 812 and 801 us.  Direct then needs
+// a launch that is resident at once, or records within kDirectBytes.
 constexpr uint32_t kDirectTiles = 24576;
+constexpr uint32_t kResidentTiles = 2048;              // eight workgroups per CU
+constexpr uint64_t kDirectBytes = 8ull << 20;
+
+bool direct_pays(const SceneDev& s, const RasterParams& p)
+{
+    if (p.persistent || p.n_blocks > kDirectTiles) return false;
+    if (p.n_blocks <= kResidentTiles) return true;
+    constexpr uint64_t per_xcd = kResidentTiles / kXcds;
+    for (int k = 0; k < p.n_segs; ++k) {
+        const uint64_t tiles = p.segs[k].tiles_per_image;
+        if (tiles < per_xcd && (uint64_t)s.n * 48u * per_xcd / tiles > kDirectBytes) return false;
+    }
+    return true;
+}
 
 // Ring of the fallback lists: filtered ids and per-wave counts of one round.
 template <int TS>
@@ -640,7 +659,7 @@ hipError_t launch_ts(const SceneDev& s, const ChunkDev& c, const RasterParams& p
 template <int TS>
 hipError_t launch_batch(const SceneDev& s, const ChunkDev& c, const RasterParams& p, hipStream_t stream)
 {
-    if (p.batch == 64 && !p.persistent && p.n_blocks <= kDirectTiles) return launch_ts<TS, 0>(s, c, p, stream);
+    if (p.batch == 64 && direct_pays(s, p)) return launch_ts<TS, 0>(s, c, p, stream);
     if (p.batch == 64) return launch_ts<TS, 64>(s, c, p, stream);
     if (p.batch == 128) return launch_ts<TS, 128>(s, c, p, stream);
     if constexpr (TS != 8)

@@ -536,3 +536,34 @@ def test_images_dealt_over_the_xcds_cover_every_tile(n_img, side):
         for x, y in zip(got, one):
             assert torch.equal(x[a:b], y), a
     R.close()
+
+
+def test_images_equal_on_both_sides_of_the_direct_bytes_line():
+    """One-tile images of the most Gaussians whose records count as staying in
+    an XCD's L2 and of one more, which lies behind every camera: the same bits
+    from the direct and the staged rasteriser, just above and at the largest
+    launch that is resident at once."""
+    torch = _torch()
+    from paper_2604_25459_amd import gsr
+    from tests.scenes import scene_from
+    rng = np.random.default_rng(78)
+    n = 682                                               # 256 images of 48 bytes each: 8 MB
+    means = rng.uniform([-0.3, -0.3, 1.0], [0.3, 0.3, 3.0], (n, 3))
+    scales, quats = np.exp(rng.normal(-3.0, 0.8, (n, 3))), rng.standard_normal((n, 4))
+    opac, sh = rng.uniform(0.02, 1.0, n), rng.uniform(0, 1, (n, 1, 3))
+    R = gsr.Renderer(0)
+    few = R.add_synth_scene(scene_from(means, scales, quats, opac, sh, 0))
+    more = R.add_synth_scene(scene_from(*[np.concatenate([a, b]) for a, b in (
+        (means, [[0.0, 0.0, -2.0]]), (scales, scales[:1]), (quats, quats[:1]), (opac, opac[:1]), (sh, sh[:1]))], 0))
+    cam = gsr.Camera(16, 16, 14.0, 14.0, 8.0, 8.0, 0.01, -1)
+    for n_img in (2048, 2049):
+        views = torch.eye(4, device="cuda")[:3].repeat(1, n_img, 1, 1)
+        views[0, :, 0, 3] = torch.linspace(-0.4, 0.4, n_img, device="cuda")
+        poses = torch.zeros(n_img, 0, 7, device="cuda")
+        a = [t.clone() for t in R.render(few, [cam], views, poses, alpha=True)[0]]
+        b = R.render(more, [cam], views, poses, alpha=True)[0]
+        torch.cuda.synchronize()
+        for x, y in zip(a, b):
+            assert torch.equal(x, y), n_img
+        assert float(a[2].amax()) > 0.5
+    R.close()
