@@ -390,10 +390,21 @@ struct LidarLds {
     uint8_t surv[TS * TS / 64][64];             // and their places in the batch
 };
 
-// m = 2 m + (f > 0 ? 0 : 1), in two instructions
-__device__ __forceinline__ void shift_in(uint32_t& m, float f)
+// m = 2 m + (f > 0 ? 0 : 1) for f0, then for f1.  A vector instruction that
+// reads a mask which a vector instruction has written must follow it by two wait
+// states on this GPU, and the compiler inserts none inside inline assembly: the
+// two compares and one s_nop stand between each compare and its add.
+__device__ __forceinline__ void shift_in(uint32_t& m, float f0, float f1)
 {
-    asm("v_cmp_nlt_f32 vcc, 0, %1\n\tv_addc_co_u32 %0, vcc, %0, %0, vcc" : "+v"(m) : "v"(f) : "vcc");
+    uint64_t c1;
+    asm("v_cmp_nlt_f32 vcc, 0, %2\n\t"
+        "v_cmp_nlt_f32 %1, 0, %3\n\t"
+        "s_nop 0\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, vcc\n\t"
+        "v_addc_co_u32 %0, vcc, %0, %0, %1"
+        : "+v"(m), "=&s"(c1)
+        : "v"(f0), "v"(f1)
+        : "vcc");
 }
 
 template <int TS, bool GRID>
@@ -703,8 +714,7 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
                     const float4 q0 = qp[0], q1 = qp[1], q2 = qp[2];
                     const float fa = fmaf(q0.x, uu, fmaf(q0.y, uv, fmaf(q0.z, vv, fmaf(q0.w, ru, fmaf(q1.x, rv, q1.y)))));
                     const float fb = fmaf(q1.z, uu, fmaf(q1.w, uv, fmaf(q2.x, vv, fmaf(q2.y, ru, fmaf(q2.z, rv, q2.w)))));
-                    shift_in(mask, fb);
-                    shift_in(mask, fa);
+                    shift_in(mask, fb, fa);
                 }
                 // (an odd count's last pair holds one of an earlier group)
                 mask &= some == 32u ? 0xFFFFFFFFu : (1u << some) - 1u;
