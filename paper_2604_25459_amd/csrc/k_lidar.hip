@@ -385,8 +385,9 @@ struct LidarLds {
     float4 sr[kLidarStage][TS * TS];
     uint32_t live_w[2][TS * TS / 64];     // per wave: live rays left after a batch (by batch parity)
     uint8_t pick[TS * TS / 64][TS * TS];        // per wave: the batch's candidates that the first step keeps
-    float quad[TS * TS / 64][64 * 6];           // those the second step keeps: their quadratics less the bound,
-                                                // a11, 2 a12, a22, 2 b1, 2 b2, f0 - bound
+    // those the second step keeps: their quadratics less the bound, a11, 2 a12,
+    // a22, 2 b1, 2 b2, f0 - bound; the third step reads them 16 bytes at a time
+    alignas(16) float quad[TS * TS / 64][64 * 6];
     uint8_t surv[TS * TS / 64][64];             // and their places in the batch
 };
 
