@@ -297,6 +297,12 @@ __host__ __device__ inline uint32_t select_bit(uint64_t m, uint32_t k)
     return (uint32_t)__builtin_ctzll(m);
 }
 
+// Index of the lowest set bit of m, 31 for m = 0.
+__host__ __device__ constexpr uint32_t lowest_bit(uint32_t m)
+{
+    return (uint32_t)__builtin_ctz(m | 0x80000000u);
+}
+
 // Workgroups of a launch are handed to the chip's 8 XCDs round-robin by
 // linear id, and each XCD has its own L2.  xcd_remap renumbers linear id b of
 // a G-workgroup launch so that each XCD runs one contiguous range of logical

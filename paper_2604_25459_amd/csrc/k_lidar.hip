@@ -515,6 +515,7 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
     uint8_t* const pick = L_.pick[tid >> 6];
     float* const quad = L_.quad[tid >> 6];
     uint8_t* const surv = L_.surv[tid >> 6];
+    surv[lane] = 0;                     // every slot holds a place of the batch, also beyond the survivors so far
     float T = 1.0f, Rg = 0.0f;
     // returns at t* <= reach are not taken: the sensor's near range, infinity once the ray has stopped
     float reach = inside ? im.near_plane : INFINITY;
@@ -723,9 +724,10 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
                 // two at a time: both are evaluated (independent dependency
                 // chains the wave interleaves), then composited in list order
                 auto next = [&]() {             // place of the lowest of the mask in the batch
-                    const uint32_t j = (s0 + (uint32_t)__builtin_ctz(mask)) & 63u;
+                    // (an empty mask gives some place of the batch: it is read and not used)
+                    const uint32_t j = s0 + lowest_bit(mask);
                     mask &= mask - 1u;
-                    return (int)surv[j] & (NT - 1);
+                    return (int)surv[j];
                 };
                 bool a_on = mask != 0u;
                 int ja = next();

@@ -27,3 +27,20 @@ using Lds = gsr::LidarLds<{ts}>;
 static_assert(offsetof(Lds, quad) % 16 == 0 && sizeof(Lds::quad[0]) % 16 == 0, "misaligned");
 """, tmp_path)
     assert rc == 0, err
+
+
+def test_lowest_bit_is_defined_for_every_mask(tmp_path):
+    """Undefined results are no constant expressions: the mask without a bit,
+    which every ray's walk ends with, has to have a value too."""
+    rc, err = _syntax("""
+#include "gsr_internal.h"
+constexpr bool every_bit()
+{
+    for (uint32_t k = 0; k < 32; ++k)
+        if (gsr::lowest_bit(1u << k) != k || gsr::lowest_bit(0xFFFFFFFFu << k) != k) return false;
+    return true;
+}
+static_assert(every_bit(), "lowest set bit");
+static_assert(gsr::lowest_bit(0u) == 31u, "an empty mask");
+""", tmp_path)
+    assert rc == 0, err
