@@ -682,8 +682,10 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
         const uint64_t lists = ((total * 4 + 255) & ~255ull) + ((row_total * 8 + 255) & ~255ull);
         while (ws.fixed && n_seg > 1 && lists + n_rows * (uint64_t)n_seg * (uint64_t)c.tx_max * 4 > ws.list_bytes)
             n_seg /= 2;
-        if ((int)ws.nseg_hint.size() <= chunk_idx) ws.nseg_hint.resize((size_t)chunk_idx + 1, 1);
-        ws.nseg_hint[chunk_idx] = n_seg;
+        if (job.plans) {
+            if ((int)ws.nseg_hint.size() <= chunk_idx) ws.nseg_hint.resize((size_t)chunk_idx + 1, 1);
+            ws.nseg_hint[chunk_idx] = n_seg;
+        }
     }
     // everything enqueued before ev_total has completed, including earlier chunks: growing is safe
     auto grow = [&](DevBuf& b, uint64_t entries, size_t entry_bytes, const char* what) -> int {
@@ -811,6 +813,9 @@ int render_job(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job_i
                 async = false;
             }
     }
+    // a waiting render of camera images plans for later ones of its shape; others
+    // (LiDAR, plain, debug) leave the plan that is there as it is
+    job.plans = !async && !plain && !job.lidar && job.mode == Mode::kRender && !job.stop;
     // synchronous renders may reallocate buffers: earlier work on this workspace must be finished
     if (ws.used && !async) {
         GSR_HIP_TRY(hipEventSynchronize(ws.ev_done));
@@ -893,7 +898,7 @@ int render_job(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job_i
     GSR_HIP_TRY(hipEventRecord(ws.ev_done, st));
     ws.used = true;
     ws.last_stream = st;
-    if (!async && !plain && !job.lidar && job.mode == Mode::kRender && !job.stop) {
+    if (job.plans) {
         // this render sized the list buffers of its shape: later ones may go asynchronously
         ws.plan_key = shape;
         if (two) ws.twin->plan_key = shape;

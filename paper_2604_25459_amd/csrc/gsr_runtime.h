@@ -156,6 +156,8 @@ struct RenderJob {
     int64_t chunk_bytes = 0;           // working-memory budget of one chunk (0: the context's option)
     Mode mode = Mode::kRender;         // kBins: every chunk stops after its tile lists (no raster)
     DebugStop* stop = nullptr;         // optional debug stop (see DebugStop)
+    bool plans = false;                // its chunks' segment counts are kept for asynchronous renders of its shape
+                                       // (Workspace::nseg_hint; set by render_job)
 };
 
 // Validated per-request image list of a render descriptor (camera-slot-major).

@@ -567,3 +567,40 @@ def test_images_equal_on_both_sides_of_the_direct_bytes_line():
             assert torch.equal(x, y), n_img
         assert float(a[2].amax()) > 0.5
     R.close()
+
+
+@pytest.mark.parametrize("between", ["lidar", "plain", "bins"])
+def test_asynchronous_renders_keep_their_plan_between_others(between):
+    """A render of a planned shape, after a LiDAR scan, a plain render or a
+    readback of tile lists on the same stream, which cut their tile-row lists
+    into other numbers of segments: enqueued as planned, same images."""
+    torch = _torch()
+    from paper_2604_25459_amd import gsr
+    scene = synth.make_scene(71, 40_000, 0, 0, sh_degree=0, half_box=2.0)
+    rng = np.random.default_rng(71)
+    cams = [synth.pinhole(640, 480, 60.0)]
+    batch = synth.Batch(cams=cams, viewmats=synth.orbit_viewmats(rng, 1, 3.0, 5.0)[None],
+                        poses=np.zeros((1, 0, 7), np.float32))
+    tall = synth.Batch(cams=[synth.pinhole(32, 16, 20.0)], viewmats=batch.viewmats, poses=batch.poses)
+    lid = synth.rotating_lidar(32, 1024, -20, 20)
+    lid_vm = torch.from_numpy(synth.sensor_viewmats(rng, 1, 0.5, 1.5, 0.1)[None]).cuda()
+    R = gsr.Renderer(0)
+    sid = R.add_synth_scene(scene)
+    cams, vm, poses = gsr.batch_tensors(batch)
+    few = gsr.batch_tensors(tall)
+    ref = [t.clone() for t in R.render(sid, cams, vm, poses, alpha=True)[0]]       # plans
+    scan = None
+    for k in range(3):
+        got = R.render(sid, cams, vm, poses, alpha=True)[0]
+        torch.cuda.synchronize()
+        for a, b in zip(ref, got):
+            assert torch.equal(a, b), k
+        if between == "lidar":
+            out = [t.clone() for t in R.render_lidar(sid, [lid], lid_vm, poses)[0]]
+            assert scan is None or all(torch.equal(a, b) for a, b in zip(scan, out))
+            scan = out
+        elif between == "plain":
+            R.render(sid, *few, plain=True)
+        else:
+            R.debug_bins(sid, *few, 0)
+    R.close()
