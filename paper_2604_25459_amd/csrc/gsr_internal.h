@@ -234,6 +234,12 @@ constexpr int kLevel2Waves = 131072;
 constexpr int kLevel2FewWaves = 32768;
 constexpr int kMaxRowSegs = 128;
 
+// LDS of k_tile_scan for an image's tile differences ([tiles_y][tiles_x + 1]
+// words) of a chunk's largest image.  Not tx_max x ty_max: those may come from
+// different images, and a wide and a tall one of 200 tiles each would take more
+// than the 160 KB there are.  An image has at most 15,000 tiles, 1,024 rows.
+constexpr size_t tile_scan_lds(int t_max, int ty_max) { return ((size_t)t_max + (size_t)ty_max) * 4; }
+
 // ------------------------------------------------------------ launchers
 // All launchers enqueue on `stream` and return hipGetLastError().
 hipError_t launch_compose(const SceneDev& s, const ChunkDev& c, hipStream_t stream);

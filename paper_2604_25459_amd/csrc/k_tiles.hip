@@ -1145,7 +1145,7 @@ hipError_t launch_tile_count(const SceneDev& s, const ChunkDev& c, const RasterP
         hipLaunchKernelGGL(k_tile_hist, dim3((unsigned)((n + kTileGauss - 1) / kTileGauss), (unsigned)c.n_img),
                            dim3(256), lds, stream, c, n);
     }
-    const size_t scan_lds = (size_t)(c.tx_max + 1) * c.ty_max * 4;
+    const size_t scan_lds = tile_scan_lds(c.t_max, c.ty_max);
     if (c.n_img < 128)
         hipLaunchKernelGGL(k_tile_scan<1024>, dim3((unsigned)c.n_img), dim3(1024), scan_lds, stream, c);
     else

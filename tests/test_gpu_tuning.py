@@ -604,3 +604,31 @@ def test_asynchronous_renders_keep_their_plan_between_others(between):
         else:
             R.debug_bins(sid, *few, 0)
     R.close()
+
+
+@pytest.mark.parametrize("sides,n", [(((3200, 1000), (1000, 3200)), 0), (((3200, 1000), (1000, 3200)), 300),
+                                     (((8192, 16), (16, 8192)), 0)])
+def test_wide_and_tall_images_in_a_launch(sides, n):
+    """A wide and a tall image in one launch, whose sides together span many
+    more tiles than either has: the bits of a launch of each, with Gaussians and
+    of an empty scene (which has no limit on the product of the sides)."""
+    torch = _torch()
+    from paper_2604_25459_amd import gsr
+    from tests.scenes import scene_from
+    rng = np.random.default_rng(n)
+    scene = scene_from(rng.uniform([-1.5, -1.5, 1.0], [1.5, 1.5, 3.0], (n, 3)), np.exp(rng.normal(-3.0, 0.8, (n, 3))),
+                       rng.standard_normal((n, 4)), rng.uniform(0.02, 1.0, n), rng.uniform(0, 1, (n, 1, 3)), 0)
+    R = gsr.Renderer(0)
+    sid = R.add_synth_scene(scene)
+    cams = [gsr.Camera(w, h, 1000.0, 1000.0, w / 2, h / 2, 0.01, -1) for w, h in sides]
+    views = torch.eye(4, device="cuda")[:3].repeat(2, 1, 1, 1)
+    poses = torch.zeros(1, 0, 7, device="cuda")
+    got = R.render(sid, cams, views, poses, bg=(0.1, 0.2, 0.3), alpha=True)
+    torch.cuda.synchronize()
+    for k, cam in enumerate(cams):
+        one = R.render(sid, [cam], views[k:k + 1].contiguous(), poses, bg=(0.1, 0.2, 0.3), alpha=True)[0]
+        torch.cuda.synchronize()
+        for a, b in zip(got[k], one):
+            assert torch.equal(a, b), (k, sides[k])
+        assert (float(one[2].amax()) > 0.5) == (n > 0)
+    R.close()
