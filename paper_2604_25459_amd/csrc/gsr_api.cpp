@@ -315,14 +315,18 @@ WorkspaceSizes workspace_sizes(const SceneRes* sc, const ChunkPlan& p, size_t n_
 
 hipError_t alloc_totals(Workspace& ws)
 {
-    if (ws.h_total) return hipSuccess;
-    hipError_t e = hipHostMalloc((void**)&ws.h_total, 64, hipHostMallocDefault);
-    if (e != hipSuccess) {
-        ws.h_total = nullptr;
+    if (ws.d_total) return hipSuccess;
+    void *h = nullptr, *d = nullptr;
+    hipError_t e = hipHostMalloc(&h, 64, hipHostMallocDefault);
+    if (e != hipSuccess) return e;
+    if ((e = hipHostGetDevicePointer(&d, h, 0)) != hipSuccess) {
+        (void)hipHostFree(h);
         return e;
     }
-    std::memset(ws.h_total, 0, 64);
-    return hipHostGetDevicePointer((void**)&ws.d_total, ws.h_total, 0);
+    std::memset(h, 0, 64);
+    ws.h_total = static_cast<uint64_t*>(h);
+    ws.d_total = static_cast<uint64_t*>(d);
+    return hipSuccess;
 }
 
 hipError_t ensure_workspace(Workspace& ws, const SceneRes* sc, const ChunkPlan& p, size_t n_images_total,

@@ -69,3 +69,51 @@ constexpr bool all()
 static_assert(all() && fits(200, 1, 1, 200) && fits(200, 63, 63, 200), "k_tile_scan");
 """, tmp_path)
     assert rc == 0, err
+
+
+def _run(text, tmp_path):
+    """Builds `text` as a host program (what it does not call may stay
+    undefined) and returns its exit status and output."""
+    src, obj, exe = (str(tmp_path / f) for f in ("t.hip", "t.o", "t"))
+    with open(src, "w") as f:
+        f.write(text)
+    subprocess.run([build.HIPCC, *build.FLAGS, "--offload-host-only", "-c", src, "-o", obj], check=True,
+                   capture_output=True)
+    subprocess.run([build.HIPCC, "-o", exe, obj, "-Wl,--unresolved-symbols=ignore-all"], check=True, capture_output=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    return r.returncode, r.stdout
+
+
+def test_totals_without_a_device_address_are_not_taken_as_allocated(tmp_path):
+    """The device address of a working set's pinned totals is refused twice and
+    then given: every call reports what it got, and none leaves the kernels an
+    address that is not one."""
+    rc, out = _run("""
+#include <stdio.h>
+#include <stdlib.h>
+#include <hip/hip_runtime.h>
+static int refuse = 2, held = 0;
+static hipError_t fake_alloc(void** p, size_t n, unsigned) { *p = malloc(n); ++held; return hipSuccess; }
+static hipError_t fake_free(void* p) { free(p); --held; return hipSuccess; }
+static hipError_t fake_address(void** d, void* h, unsigned)
+{
+    if (refuse-- > 0) return hipErrorInvalidValue;
+    *d = h;
+    return hipSuccess;
+}
+#define hipHostMalloc(p, n, f) fake_alloc(p, n, f)
+#define hipHostFree(p) fake_free(p)
+#define hipHostGetDevicePointer(d, h, f) fake_address(d, h, f)
+#include "gsr_api.cpp"
+int main()
+{
+    gsr::Workspace* ws = new gsr::Workspace();      // not destroyed: no device
+    for (int k = 0; k < 4; ++k) {
+        const hipError_t e = gsr::alloc_totals(*ws);
+        if ((e == hipSuccess) != (k >= 2) || (e == hipSuccess) != (ws->d_total != nullptr)) return printf("call %d\\n", k), 1;
+        if (held != (k >= 2 ? 1 : 0)) return printf("held %d after call %d\\n", held, k), 1;
+    }
+    return 0;
+}
+""", tmp_path)
+    assert rc == 0, out
