@@ -365,6 +365,12 @@ int gsr_render_lidar(gsr_ctx* ctx, const gsr_lidar_desc* desc, void* stream);
 int gsr_debug_bins(gsr_ctx* ctx, const gsr_render_desc* desc, int image, gsr_bins_out* out);
 int gsr_debug_project(gsr_ctx* ctx, const gsr_render_desc* desc, int image, gsr_proj_out* out);
 
+/* The projections' reciprocal (GSR_ROOT_RCP) or square root (GSR_ROOT_SQRT) of
+ * the `count` binary32 values whose bit patterns are first_bits,
+ * first_bits + 1, ..., into host memory `out` [count].  Synchronous. */
+enum { GSR_ROOT_RCP = 0, GSR_ROOT_SQRT = 1 };
+int gsr_debug_roots(gsr_ctx* ctx, int root, uint32_t first_bits, uint32_t count, float* out);
+
 /* ---- serving ---------------------------------------------------------
  * A server renders requests from several producers (e.g. RL workers) as they
  * arrive, with continuous batching: worker threads, each with its own device

@@ -1702,6 +1702,22 @@ GSR_EXPORT int gsr_debug_project(gsr_ctx* ctx, const gsr_render_desc* d, int ima
     return rc;
 }
 
+GSR_EXPORT int gsr_debug_roots(gsr_ctx* ctx, int root, uint32_t first_bits, uint32_t count, float* out)
+{
+    if (!ctx || (!out && count > 0)) return fail(GSR_E_INVALID, "ctx/out is NULL");
+    if (root != GSR_ROOT_RCP && root != GSR_ROOT_SQRT) return fail(GSR_E_INVALID, "unknown root");
+    if (count > (1u << 24)) return fail(GSR_E_INVALID, "more than 2^24 values");
+    if (count == 0) return GSR_OK;
+    if (ctx->poisoned) return fail(GSR_E_DEVICE, "context poisoned by an earlier device fault");
+    GSR_HIP_TRY(hipSetDevice(ctx->device));
+    DevBuf d;
+    hipError_t e = d.ensure((size_t)count * 4);
+    if (e == hipSuccess) e = launch_debug_roots(root, first_bits, count, d.as<float>(), nullptr);
+    if (e == hipSuccess) e = hipMemcpy(out, d.p, (size_t)count * 4, hipMemcpyDeviceToHost);
+    d.release();
+    return e == hipSuccess ? GSR_OK : hip_fail(e, "gsr_debug_roots");
+}
+
 // ============================================================== autotuning
 
 namespace {

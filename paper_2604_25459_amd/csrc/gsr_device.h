@@ -36,10 +36,10 @@ __device__ __forceinline__ uint16_t encode(float f)
 
 // Correctly rounded square root and reciprocal, one Newton step after the
 // hardware approximation (the residual is exact in a fused multiply-add): the
-// bits of sqrtf(x) and 1.0f / x for every x in [2^-100, 2^127) and for every
-// normal x up to 2^126 (checked over all mantissas), without their handling of
-// the ends of the range: five and three instructions instead of about fifteen
-// and ten.  sqrt_rn(inf) is NaN.
+// bits of sqrtf(x) for every finite x >= 2^-100 and of 1.0f / x for every
+// normal x up to 2^126 (tests/test_gpu_roots.py: all mantissas, every exponent),
+// without their handling of the ends of the range: five and three instructions
+// instead of about fifteen and ten.  sqrt_rn(inf) is NaN.
 __device__ __forceinline__ float sqrt_rn(float x)
 {
     const float r = __builtin_amdgcn_rsqf(x);

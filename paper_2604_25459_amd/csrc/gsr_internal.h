@@ -296,6 +296,8 @@ hipError_t launch_scene_convert(int storage, int64_t n, int64_t n_pad, int degre
 // Debug: 64-bit keys and Gaussian indices of one image from its sorted pairs.
 hipError_t launch_debug_keys(const ChunkDev& c, int image, uint64_t n, const uint32_t* pairs, uint64_t n_pairs,
                              uint64_t* keys_out, uint32_t* ids_out, hipStream_t stream);
+// Debug: the projections' reciprocal or square root (GSR_ROOT_*) of the values with the bits first, first + 1, ...
+hipError_t launch_debug_roots(int root, uint32_t first, uint32_t count, float* out, hipStream_t stream);
 // Index of the k-th set bit of m (k < popcount(m)).
 __host__ __device__ inline uint32_t select_bit(uint64_t m, uint32_t k)
 {

@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256) void k_project(SceneDev s, ChunkDev c, const I
         const float det = (((w0 * w0 + w1 * w1) + w2 * w2) + 0.3f * (n1 + n2)) + 0.09f;
         const float m = 0.5f * (ca + cc);
         const float h = 0.5f * (ca - cc);
-        // arguments of at least 0.1: a finite one takes no part of sqrtf's range handling, and an infinite
+        // arguments of at least 0.1: sqrt_rn has the bits of sqrtf for the finite ones, and an infinite
         // one leaves r NaN or infinite (culled) or loses against r below, as with sqrtf
         const float lam = m + sqrt_rn(fmaxf(0.1f, h * h + cb * cb));
         const float r = ceilf(cutoff * sqrt_rn(lam));
@@ -393,7 +393,22 @@ __global__ __launch_bounds__(256) void k_scene_convert(int64_t n, int64_t n_pad,
     }
 }
 
+__global__ __launch_bounds__(256) void k_debug_roots(int root, uint32_t first, uint32_t count, float* __restrict__ out)
+{
+    const uint32_t k = blockIdx.x * 256u + threadIdx.x;
+    if (k >= count) return;
+    const float x = __uint_as_float(first + k);
+    out[k] = root == GSR_ROOT_SQRT ? sqrt_rn(x) : rcp_rn(x);
+}
+
 }  // namespace
+
+hipError_t launch_debug_roots(int root, uint32_t first, uint32_t count, float* out, hipStream_t stream)
+{
+    if (count == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_debug_roots, dim3((count + 255u) / 256u), dim3(256), 0, stream, root, first, count, out);
+    return hipGetLastError();
+}
 
 hipError_t launch_compose(const SceneDev& s, const ChunkDev& c, hipStream_t stream)
 {

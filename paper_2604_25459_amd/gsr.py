@@ -123,6 +123,7 @@ SIGNATURES = {
     "gsr_render_lidar": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p]),
     "gsr_debug_bins": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int, C.c_void_p]),
     "gsr_debug_project": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int, C.c_void_p]),
+    "gsr_debug_roots": (C.c_int, [C.c_void_p, C.c_int, C.c_uint32, C.c_uint32, C.c_void_p]),
     "gsr_stage_times": (C.c_int, [C.c_void_p, C.c_void_p, C.c_int, C.c_int]),
     "gsr_autotune": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p]),
     "gsr_tuning_get": (C.c_int, [C.c_void_p, C.c_void_p, C.c_void_p]),
@@ -484,6 +485,13 @@ class Renderer:
         o = ProjOut(n=n, zkey=z.ctypes.data, rect=rect.ctypes.data, rec=rec.ctypes.data)
         _check(load().gsr_debug_project(self._h, C.byref(d), int(image), C.byref(o)))
         return dict(zkey=z, rect=rect, rec=rec)
+
+    def debug_roots(self, root: int, first_bits: int, count: int) -> np.ndarray:
+        """The projections' reciprocal (0) or square root (1) of the binary32 values with the bit patterns
+        first_bits .. first_bits + count - 1."""
+        out = np.empty(count, np.float32)
+        _check(load().gsr_debug_roots(self._h, int(root), int(first_bits), int(count), out.ctypes.data))
+        return out
 
 
 class Server:
