@@ -673,15 +673,7 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
         total = ws.h_total[0];
         row_total = ws.h_total[1];
         *pairs_total = total;
-        // segments per tile-row list (see kLevel2Rows)
-        const uint64_t per_row = n_rows ? row_total / n_rows : 0;
-        uint64_t by_len = std::max<uint64_t>(1, per_row / kRowSegEntries), waves = (uint64_t)kLevel2Waves;
-        if (n_rows * by_len < (uint64_t)kLevel2FewWaves) {
-            by_len = std::max<uint64_t>(1, per_row / kRowSegEntriesFew);
-            waves = (uint64_t)kLevel2FewWaves;
-        }
-        const uint64_t by_waves = n_rows == 0 || n_rows >= (uint64_t)kLevel2Rows ? 1 : (waves + n_rows - 1) / n_rows;
-        n_seg = (int)std::min<uint64_t>(kMaxRowSegs, std::min(by_len, by_waves));
+        n_seg = row_segments(n_rows, row_total, c.tx_max);
         // a fixed list region: no segments where their offsets would not fit beside the lists
         const uint64_t lists = ((total * 4 + 255) & ~255ull) + ((row_total * 8 + 255) & ~255ull);
         while (ws.fixed && n_seg > 1 && lists + n_rows * (uint64_t)n_seg * (uint64_t)c.tx_max * 4 > ws.list_bytes)

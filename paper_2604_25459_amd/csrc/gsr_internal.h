@@ -11,6 +11,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "gsr.h"
 
 namespace gsr {
@@ -233,6 +235,22 @@ constexpr int kLevel2Rows = 16384;
 constexpr int kLevel2Waves = 131072;
 constexpr int kLevel2FewWaves = 32768;
 constexpr int kMaxRowSegs = 128;
+// Segments per tile-row list of a launch with n_rows tile rows of row_total
+// entries in all, at most tx_max tiles each.  A segment also has at least as
+// many entries as its row has tiles: its offsets (a word per tile) then take at
+// most half the memory of its entries (two words each), whatever the images' width.
+constexpr int row_segments(uint64_t n_rows, uint64_t row_total, int tx_max)
+{
+    if (n_rows == 0 || n_rows >= (uint64_t)kLevel2Rows) return 1;
+    const uint64_t per_row = row_total / n_rows, tx = (uint64_t)tx_max;
+    uint64_t segs = per_row / std::max<uint64_t>(kRowSegEntries, tx), waves = kLevel2Waves;
+    if (n_rows * std::max<uint64_t>(segs, 1) < (uint64_t)kLevel2FewWaves) {
+        segs = per_row / std::max<uint64_t>(kRowSegEntriesFew, tx);
+        waves = kLevel2FewWaves;
+    }
+    segs = std::min(segs, (waves + n_rows - 1) / n_rows);
+    return (int)std::max<uint64_t>(1, std::min<uint64_t>(kMaxRowSegs, segs));
+}
 
 // LDS of k_tile_scan for an image's tile differences ([tiles_y][tiles_x + 1]
 // words) of a chunk's largest image.  Not tx_max x ty_max: those may come from

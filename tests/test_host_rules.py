@@ -117,3 +117,29 @@ int main()
 }
 """, tmp_path)
     assert rc == 0, out
+
+
+def test_segment_offsets_stay_within_half_of_the_row_lists(tmp_path):
+    """Level-2 segments over launches of every row count, list length and
+    width: their offsets take at most half the bytes of the row lists that they
+    divide, and images of up to 128 tile columns keep the numbers of segments
+    that the launch's waves ask for."""
+    rc, out = _run("""
+#include <stdio.h>
+#include "gsr_internal.h"
+int main()
+{
+    long many = 0;
+    for (uint64_t rows = 1; rows <= 40000; rows = rows * 5 / 4 + 1)
+        for (uint64_t per = 0; per <= 4000000; per = per * 3 / 2 + 1)
+            for (int tx = 1; tx <= 1024; tx = tx * 2 + (tx > 100)) {
+                const int s = gsr::row_segments(rows, rows * per, tx), narrow = gsr::row_segments(rows, rows * per, 1);
+                const bool ok = s >= 1 && s <= gsr::kMaxRowSegs && s <= narrow && (tx > 128 || s == narrow) &&
+                                (s == 1 || (uint64_t)s * tx * 4 * rows <= rows * per * 8 / 2);
+                if (!ok) return printf("rows %lu entries %lu tx %d: %d segments\\n", rows, per, tx, s), 1;
+                many += s > 1;
+            }
+    return many < 1000;
+}
+""", tmp_path)
+    assert rc == 0, out
