@@ -232,6 +232,12 @@ size_t per_image_bytes(const SceneRes* sc, int t_max, int ty_max, int sort_block
     return b;
 }
 
+// Row counts of one image's tile-pass blocks (Workspace::row_hist).
+size_t row_count_bytes(int64_t n, int tile_items, int ty_max)
+{
+    return (size_t)tile_blocks_of(n, tile_items) * (size_t)ty_max * 4;
+}
+
 }  // namespace
 
 size_t image_bytes_estimate(const SceneRes* sc, int width, int height, int ts)
@@ -239,8 +245,15 @@ size_t image_bytes_estimate(const SceneRes* sc, int width, int height, int ts)
     const int tx = (width + ts - 1) / ts, ty = (height + ts - 1) / ts;
     const int64_t n = sc->dev.n;
     const int sb = (int)std::max<int64_t>(1, (n + kSortItems - 1) / kSortItems);
-    const int tb = (int)std::max<int64_t>(1, (n + kTileGauss - 1) / kTileGauss);
+    const int tb = tile_blocks_of(n, kTileGauss);
     return per_image_bytes(sc, tx * ty, ty, sb, tb);
+}
+
+size_t image_block_bytes(const SceneRes* sc, int width, int height, int ts, int n_images)
+{
+    const int tx = (width + ts - 1) / ts, ty = (height + ts - 1) / ts;
+    const int items = tile_items_for((uint64_t)sc->dev.n, (uint64_t)n_images, tx, ty);
+    return row_count_bytes(sc->dev.n, items, ty) - row_count_bytes(sc->dev.n, kTileGauss, ty);
 }
 
 ChunkPlan plan_chunks(const gsr_ctx* ctx, const SceneRes* sc, const std::vector<ImageInfo>& imgs, bool plain,
@@ -256,12 +269,11 @@ ChunkPlan plan_chunks(const gsr_ctx* ctx, const SceneRes* sc, const std::vector<
     }
     const int64_t n = sc->dev.n;
     p.sort_blocks = (int)std::max<int64_t>(1, (n + kSortItems - 1) / kSortItems);
-    p.tile_blocks = (int)std::max<int64_t>(1, (n + kTileGauss - 1) / kTileGauss);
+    const size_t per = per_image_bytes(sc, p.t_max, p.ty_max, p.sort_blocks, tile_blocks_of(n, kTileGauss), rec_bytes);
+    size_t cap = budget;
     if (plain) {
         p.chunk = 1;
     } else {
-        const size_t per = per_image_bytes(sc, p.t_max, p.ty_max, p.sort_blocks, p.tile_blocks, rec_bytes);
-        size_t cap = budget;
         if (per * imgs.size() > cap) {
             // a job larger than one chunk: keep a chunk's working set (two with the
             // second stream) within 40 % of the device memory free now
@@ -276,8 +288,13 @@ ChunkPlan plan_chunks(const gsr_ctx* ctx, const SceneRes* sc, const std::vector<
         c = (imgs.size() + n_chunks - 1) / n_chunks;
         p.chunk = (int)std::min<size_t>(c, imgs.size());
     }
+    // The estimate counts the row counts of kTileGauss Gaussians per block; smaller
+    // blocks are taken as far as theirs fit the budget too.
     p.tile_items = tile_items_for((uint64_t)n, (uint64_t)p.chunk, p.tx_max, p.ty_max);
-    p.tile_blocks = (int)std::max<int64_t>(1, (n + p.tile_items - 1) / p.tile_items);
+    const size_t counted = per - row_count_bytes(n, kTileGauss, p.ty_max);
+    while (p.tile_items < kTileGauss && (counted + row_count_bytes(n, p.tile_items, p.ty_max)) * (size_t)p.chunk > cap)
+        p.tile_items *= 2;
+    p.tile_blocks = tile_blocks_of(n, p.tile_items);
     return p;
 }
 

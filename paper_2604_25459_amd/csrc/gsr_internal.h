@@ -217,6 +217,10 @@ inline int tile_items_for(uint64_t n, uint64_t n_img, int tx_max, int ty_max)
         items /= 2;
     return items;
 }
+inline int tile_blocks_of(int64_t n, int tile_items)
+{
+    return (int)std::max<int64_t>(1, (n + tile_items - 1) / tile_items);
+}
 // Level 2 runs one wave per (image, tile row, segment).  A launch that has
 // kLevel2Rows tile rows takes each as one segment: an extra segment costs a
 // count pass over its entries.  Fewer rows are cut into kLevel2Waves segments of

@@ -61,11 +61,11 @@ size_t chunk_fixed_bytes(const SceneRes* sc, const ChunkPlan& plan)
     return b;
 }
 
-// The plan with the fewest tile-pass blocks (the smallest block counts).
-ChunkPlan coarse_blocks(const SceneRes* sc, ChunkPlan plan)
+// The plan with tile-pass blocks of tile_items Gaussians (kTileGauss: the smallest block counts).
+ChunkPlan with_blocks(const SceneRes* sc, ChunkPlan plan, int tile_items)
 {
-    plan.tile_items = kTileGauss;
-    plan.tile_blocks = (int)std::max<int64_t>(1, (sc->dev.n + kTileGauss - 1) / kTileGauss);
+    plan.tile_items = tile_items;
+    plan.tile_blocks = tile_blocks_of(sc->dev.n, tile_items);
     return plan;
 }
 
@@ -150,8 +150,10 @@ int render_noalloc(gsr_ctx* ctx, NoallocDev& nd, SceneRes* sc, const gsr_render_
     // share the dead buffers' place: a record's 48 bytes less theirs)
     ChunkPlan plan = plan_chunks(ctx, sc, job.imgs, false, 0, 48 - kSortedBytes, (int64_t)budget);
     int chunk = std::max(1, std::min(plan.chunk, n_img));
+    // blocks as the launch wants them: what they take is checked below, not estimated
+    plan = with_blocks(sc, plan, tile_items_for((uint64_t)sc->dev.n, (uint64_t)plan.chunk, plan.tx_max, plan.ty_max));
     plan.chunk = 1;
-    const ChunkPlan coarse = coarse_blocks(sc, plan);
+    const ChunkPlan coarse = with_blocks(sc, plan, kTileGauss);
     const size_t one = chunk_fixed_bytes(sc, coarse);
     if (one + kAlign > budget) {
         char msg[256];

@@ -166,6 +166,8 @@ std::vector<ImageInfo> images_of(const gsr_render_desc* d, int ts, int n_bodies)
 void fill_images(const gsr_render_desc* d, int ts, int n_bodies, ImageInfo* out);
 int validate_desc(const gsr_ctx* ctx, const gsr_render_desc* d, const SceneRes* sc, bool need_outputs);
 size_t image_bytes_estimate(const SceneRes* sc, int width, int height, int ts);
+// What smaller tile-pass blocks add to that per image in launches of n_images and more.
+size_t image_block_bytes(const SceneRes* sc, int width, int height, int ts, int n_images);
 ChunkPlan plan_chunks(const gsr_ctx* ctx, const SceneRes* sc, const std::vector<ImageInfo>& imgs, bool plain,
                       int chunk_images = 0, size_t rec_bytes = 48, int64_t chunk_bytes = 0);
 // Shape-class key of a render descriptor (scene, envs, camera sizes).

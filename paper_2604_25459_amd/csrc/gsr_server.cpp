@@ -238,7 +238,7 @@ GSR_EXPORT int gsr_submit(gsr_server* srv, const gsr_render_desc* d, uint64_t* t
     int64_t all = 0;
     for (const gsr_camera& c : r->cams) {
         const int64_t one = (int64_t)image_bytes_estimate(sc, c.width, c.height, ctx->opt.tile_size);
-        all += one * d->n_envs;
+        all += (one + (int64_t)image_block_bytes(sc, c.width, c.height, ctx->opt.tile_size, r->n_images)) * d->n_envs;
         r->image_bytes = std::max(r->image_bytes, one);
     }
     // a render holds one memory chunk of images at a time (at least one

@@ -143,3 +143,52 @@ int main()
 }
 """, tmp_path)
     assert rc == 0, out
+
+
+def test_tile_pass_blocks_stay_within_the_memory_budget(tmp_path):
+    """Chunk plans over scenes, image sides and budgets: smaller tile-pass
+    blocks are planned only as far as their row counts fit the chunk's budget
+    beside what the estimate counts, all of them where there is room, and a
+    served request is charged for the blocks of any launch that it ends up in."""
+    rc, out = _run("""
+#include <stdio.h>
+#include "gsr_api.cpp"
+using namespace gsr;
+int main()
+{
+    gsr_ctx* ctx = new gsr_ctx();           // neither is destroyed: no device
+    SceneRes* sc = new SceneRes();
+    const int sides[][2] = {{640, 480}, {128, 96}, {1920, 1080}, {112, 8192}, {8192, 112}};
+    long refined = 0, bounded = 0;
+    for (const long n : {1l, 5000l, 300000l, 3000000l})
+        for (const auto& wh : sides)
+            for (const int images : {1, 7, 64}) {
+                sc->dev.n = n;
+                std::vector<ImageInfo> imgs((size_t)images);
+                for (ImageInfo& im : imgs) {
+                    im.tiles_x = (wh[0] + 15) / 16;
+                    im.tiles_y = (wh[1] + 15) / 16;
+                }
+                const size_t one = image_bytes_estimate(sc, wh[0], wh[1], 16), all = one * (size_t)images;
+                const size_t coarse = (size_t)tile_blocks_of(n, kTileGauss) * (size_t)imgs[0].tiles_y * 4 * (size_t)images;
+                const int want = tile_items_for((uint64_t)n, (uint64_t)images, imgs[0].tiles_x, imgs[0].tiles_y);
+                for (const size_t spare : {(size_t)0, (size_t)4096, all / 256, all}) {
+                    const ChunkPlan p = plan_chunks(ctx, sc, imgs, false, 0, 48, (int64_t)(all + spare));
+                    const size_t rows = (size_t)p.tile_blocks * (size_t)p.ty_max * 4 * (size_t)p.chunk;
+                    if (p.chunk != images || p.tile_blocks != tile_blocks_of(n, p.tile_items)) return printf("plan\\n"), 1;
+                    if (rows > coarse + spare) return printf("n %ld side %d: %zu over\\n", n, wh[0], rows - coarse - spare), 1;
+                    if (spare == all && p.tile_items != want) return printf("n %ld side %d: %d items\\n", n, wh[0], p.tile_items), 1;
+                    refined += p.tile_items < kTileGauss;
+                    bounded += p.tile_items > want;
+                }
+                // charged by the request's own images: a larger launch has no smaller blocks
+                for (const int with : {images, 3 * images + 1}) {
+                    const int items = tile_items_for((uint64_t)n, (uint64_t)with, imgs[0].tiles_x, imgs[0].tiles_y);
+                    const size_t rows = (size_t)tile_blocks_of(n, items) * (size_t)imgs[0].tiles_y * 4;
+                    if (rows > coarse / (size_t)images + image_block_bytes(sc, wh[0], wh[1], 16, images)) return printf("charge\\n"), 1;
+                }
+            }
+    return !(refined > 20 && bounded > 20);
+}
+""", tmp_path)
+    assert rc == 0, out
