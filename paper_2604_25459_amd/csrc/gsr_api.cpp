@@ -533,7 +533,6 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
 {
     ChunkDev c = chunk_view(ws, sc, plan, i0, n_img, job.imgs);
     c.err = ctx->d_err;
-    c.ovf_count = ctx->d_err + 1;
     c.acc = reinterpret_cast<unsigned long long*>(ctx->d_err + 16);
     c.ovf = ws.ovf.as<uint32_t>();
     c.host_totals = async_lists ? nullptr : ws.d_total;

@@ -173,7 +173,6 @@ struct ChunkDev {
     // filters each tile's list from the depth-ordered Gaussians instead.
     uint64_t cap_pairs, cap_rows;
     uint32_t* ovf;             // device word of the workspace: 1 = this chunk's lists do not fit
-    uint32_t* ovf_count;       // device counter of the context: overflowed chunks so far
     // pinned host memory of the workspace, written by k_image_scan: the chunk's
     // totals and the consistency bits (pairs, row entries, visible Gaussians,
     // bits; null where the host does not wait for them), and a word set to 1

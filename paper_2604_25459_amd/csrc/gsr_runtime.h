@@ -222,8 +222,7 @@ struct gsr_ctx {
     double raster_launches = 0, renders = 0;
     std::atomic<bool> poisoned{false};
     uint32_t* d_err = nullptr;                        // device words: [0] consistency bits (ChunkDev::err), read
-                                                      // at every synchronous chunk; [1] overflowed chunks
-                                                      // (ChunkDev::ovf_count); from byte 64, three u64
+                                                      // at every synchronous chunk; from byte 64, three u64
                                                       // accumulators (ChunkDev::acc)
     uint64_t list_cap = 0;                            // tests: list capacity (entries) of asynchronous chunks
     unsigned long long acc_base[3] = {0, 0, 0};       // accumulator values at the last stage-timer reset

@@ -510,10 +510,7 @@ __device__ __forceinline__ void image_scan(const ChunkDev& c)
     if (tid == 0) {
         const uint32_t over = tot[0] > c.cap_pairs || tot[1] > c.cap_rows ? 1u : 0u;
         *c.ovf = over;
-        if (over) {
-            atomicAdd(c.ovf_count, 1u);
-            __hip_atomic_store(c.host_ovf, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-        }
+        if (over) __hip_atomic_store(c.host_ovf, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         // the totals go straight to the host's memory: four small copies and the gaps between them otherwise
         if (c.host_totals) {
             const uint64_t bits = *c.err;
