@@ -320,7 +320,7 @@ WorkspaceSizes workspace_sizes(const SceneRes* sc, const ChunkPlan& p, size_t n_
     add(&Workspace::vis_count, I * 4);
     add(&Workspace::tile_hist, I * (size_t)(p.tx_max + 1) * (p.ty_max + 1) * 4);
     add(&Workspace::tile_range, I * (size_t)p.t_max * 8);
-    add(&Workspace::pair_count, I * 4);
+    add(&Workspace::pair_count, I * 8);        // pairs, longest list
     add(&Workspace::pair_base, (I + 2) * 8);
     add(&Workspace::row_hist, I * p.tile_blocks * (size_t)p.ty_max * 4);
     add(&Workspace::row_range, I * (size_t)p.ty_max * 8);
@@ -535,6 +535,7 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
     c.err = ctx->d_err;
     c.acc = reinterpret_cast<unsigned long long*>(ctx->d_err + 16);
     c.ovf = ws.ovf.as<uint32_t>();
+    c.longest = job.lidar ? c.pair_count + plan.chunk : nullptr;
     c.host_totals = async_lists ? nullptr : ws.d_total;
     c.host_ovf = reinterpret_cast<uint32_t*>(ws.d_total + 5);
     c.fallback_counter = async_lists ? ws.counter2.as<uint32_t>() : nullptr;
@@ -753,6 +754,8 @@ int run_chunk(gsr_ctx* ctx, Workspace& ws, SceneRes* sc, const RenderJob& job, c
         key.push_back((uint64_t)rp.count_work);
     }
     if (job.lidar) {
+        rp.entries = total;
+        rp.longest = ws.h_total[4];
         rc = run_stage(ws, graph, chunk_idx, 4, sc->uid, key, st,
                        [&](hipStream_t q) { return launch_raster_lidar(s, c, rp, q); });
     } else {

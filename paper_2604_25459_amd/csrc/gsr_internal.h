@@ -152,6 +152,7 @@ struct ChunkDev {
     int32_t* tile_hist;       // [n_img][(tx_max + 1) (ty_max + 1)] 2D difference array of tile counts
     uint32_t* tile_range;      // [n_img][t_max][2] local [start, end)
     uint32_t* pair_count;      // [n_img] P_i
+    uint32_t* longest;         // [n_img] entries of the image's longest tile list (LiDAR; else null)
     uint64_t* pair_base;       // [n_img + 2] exclusive prefix of P_i, total pairs, total visible
     uint32_t* pairs;           // [total pairs] Gaussian id per (tile, depth)-sorted entry
     int ty_max;                // largest tile-row count of an image in the chunk
@@ -175,8 +176,8 @@ struct ChunkDev {
     uint32_t* ovf;             // device word of the workspace: 1 = this chunk's lists do not fit
     // pinned host memory of the workspace, written by k_image_scan: the chunk's
     // totals and the consistency bits (pairs, row entries, visible Gaussians,
-    // bits; null where the host does not wait for them), and a word set to 1
-    // when a chunk overflowed
+    // bits, longest tile list; null where the host does not wait for them), and a
+    // word set to 1 when a chunk overflowed
     uint64_t* host_totals;
     uint32_t* host_ovf;
     uint32_t* fallback_counter;   // kXcds tile counters of the fallback rasteriser, zeroed by k_image_scan (or null)
@@ -294,6 +295,8 @@ struct RasterParams {
     int n_segs;
     RasterSeg segs[kMaxSegs];
     uint32_t n_blocks;
+    uint64_t entries;        // LiDAR: of the chunk's tile lists, and of the longest of them
+    uint64_t longest;
     uint32_t* order;         // heavy-first order of each XCD's part (launch_tile_order), or null: as they come
 };
 // Launches of more than kOrderTilesMin tiles (up to that all are resident at
@@ -302,6 +305,23 @@ struct RasterParams {
 // ordering blocks would have more than eight tiles a thread.
 constexpr uint32_t kOrderTilesMin = 1280;
 constexpr uint32_t kOrderTilesMax = 65536;
+// Launches whose tiles hold at most kShortList entries on average: their time is
+// what a tile sets up.  Their images are not dealt out by list entries (a ranking
+// that takes 0.04 us an image), and LiDAR launches of more tiles than are resident
+// at once take a kernel of fewer culling steps, unless some list is long
+// (kShortLongest).  With the dealing and the full kernel, and without: 512 scans of
+// 32 x 1024 rays over 500, 2,000, 4,000 and 8,000 Gaussians 509, 579, 614 and 737
+// us and 345, 430, 496 and 684, the last of about 90 entries a tile; 1,024 of
+// 16 x 360 over 2,000 and 8,000 438 and 667, and 364 and 666; 1,000 images of 64x64
+// over 2,000 299 and 261.  40 heightmaps of 16 tiles, resident at once, lose 4 %
+// with the smaller kernel, and one list of 4,000 entries takes it 0.2 ms longer;
+// with lines at 256 and 1,024 entries the times above differ by less than 1 %.
+constexpr uint64_t kShortList = 96;
+constexpr uint64_t kShortLongest = 512;
+__host__ __device__ inline bool short_lists(uint64_t entries, uint32_t n_blocks)
+{
+    return entries <= kShortList * n_blocks;
+}
 hipError_t launch_raster_lidar(const SceneDev& s, const ChunkDev& c, const RasterParams& p, hipStream_t stream);
 hipError_t launch_raster(const SceneDev& s, const ChunkDev& c, const RasterParams& p, hipStream_t stream);
 // Fallback compositing of a chunk whose lists overflowed (a persistent grid

@@ -78,8 +78,8 @@ struct Workspace {
     DevBuf img, xform, keyz, rect, srect, rec, sk0, sk1, sv0, sv1, sort_hist, kmm, vis_count, tile_hist, tile_range,
         pair_count, pair_base, pairs, row_hist, row_range, row_count, row_base, rows, debug, vmask, stage_elev, seg_off;
     uint64_t* h_total = nullptr;   // pinned: [0] pairs, [1] row entries, [2] visible Gaussians of the current chunk,
-                                   // [3] the context's device consistency bits, [5] low word: 1 = a chunk overflowed
-                                   // (written by k_image_scan)
+                                   // [3] the context's device consistency bits, [4] entries of the longest tile list
+                                   // (LiDAR), [5] low word: 1 = a chunk overflowed (written by k_image_scan)
     uint64_t* d_total = nullptr;   // device address of h_total
     ImageInfo* h_img = nullptr;    // pinned staging for image descriptions
     size_t h_img_cap = 0;

@@ -31,6 +31,7 @@
 #include "gsr_wave.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace gsr {
 namespace {
@@ -391,6 +392,16 @@ struct LidarLds {
     uint8_t surv[TS * TS / 64][64];             // and their places in the batch
 };
 
+// Launches of short lists (kShortList) take the first step only, and a wave's rays
+// walk its survivors together: what a tile costs there is what it sets up, and how
+// many others its CU holds beside it (7 workgroups of 48 registers and 20 KB a
+// tile, 5 of 93 and 27 KB with all three steps).
+template <int TS>
+struct LidarShortLds {
+    float4 sr[kLidarStage][TS * TS];
+    uint32_t live_w[2][TS * TS / 64];
+};
+
 // m = 2 m + (f > 0 ? 0 : 1) for f0, then for f1.  A vector instruction that
 // reads a mask which a vector instruction has written must follow it by two wait
 // states on this GPU, and the compiler inserts none inside inline assembly: the
@@ -408,9 +419,9 @@ __device__ __forceinline__ void shift_in(uint32_t& m, float f0, float f1)
         : "vcc");
 }
 
-template <int TS, bool GRID>
+template <int TS, bool GRID, bool SHORT, class Lds>
 __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c, int i, const ImageInfo& im, int tx,
-                                           int ty, uint32_t t, LidarLds<TS>& L_)
+                                           int ty, uint32_t t, Lds& L_)
 {
     constexpr int NT = TS * TS;
     constexpr int kLBatch = NT;
@@ -491,7 +502,7 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
     // them have stopped; the second step needs rays within about 45 degrees of
     // the axis
     float u0, u1, v0, v1;
-    const bool tight = GRID || (cull && cb > 0.75f);
+    const bool tight = !SHORT && (GRID || (cull && cb > 0.75f));
     auto live_rect = [&](bool on) {
         float r[4] = {on ? ru : 3.0e38f, on ? -ru : 3.0e38f, on ? rv : 3.0e38f, on ? -rv : 3.0e38f};
 #pragma unroll
@@ -511,11 +522,15 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
     const float um = fmaxf(fabsf(bx0), fabsf(bx1)), vm = fmaxf(fabsf(by0), fabsf(by1));     // grid: largest |u|, |v|
     bool live = inside;
     uint32_t rect_rays = (uint32_t)__popcll(__ballot(live));
-    live_rect(live);
-    uint8_t* const pick = L_.pick[tid >> 6];
-    float* const quad = L_.quad[tid >> 6];
-    uint8_t* const surv = L_.surv[tid >> 6];
-    surv[lane] = 0;                     // every slot holds a place of the batch, also beyond the survivors so far
+    uint8_t *pick = nullptr, *surv = nullptr;
+    float* quad = nullptr;
+    if constexpr (!SHORT) {
+        live_rect(live);
+        pick = L_.pick[tid >> 6];
+        quad = L_.quad[tid >> 6];
+        surv = L_.surv[tid >> 6];
+        surv[lane] = 0;                 // every slot holds a place of the batch, also beyond the survivors so far
+    }
     float T = 1.0f, Rg = 0.0f;
     // returns at t* <= reach are not taken: the sensor's near range, infinity once the ray has stopped
     float reach = inside ? im.near_plane : INFINITY;
@@ -570,34 +585,6 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
         }
         __syncthreads();
         const int cnt = (int)min((uint32_t)kLBatch, end - b0);
-        uint32_t n_pick = 0;
-        for (int sub = 0; sub < cnt && wave_live; sub += 64) {
-            const int jl = sub + lane;
-            bool keep = false;
-            if (jl < cnt) {
-                const float4 cn = sr[4][jl];
-                if (GRID) {
-                    // distance from the footprint centre to the origin rectangle, against the disc radius
-                    const float ex = fmaxf(0.0f, fmaxf(bx0 - cn.x, cn.x - bx1));
-                    const float ey = fmaxf(0.0f, fmaxf(by0 - cn.y, cn.y - by1));
-                    keep = ex * ex + ey * ey <= cn.z * cn.z * 1.0001f;
-                } else if (!cull || cn.w < -1.5f) {
-                    keep = true;
-                } else {
-                    const float sa = __builtin_amdgcn_sqrtf(fmaxf(0.0f, fmaf(-cn.w, cn.w, 1.0f)));
-                    keep = fmaf(cn.z, w[2], fmaf(cn.y, w[1], cn.x * w[0])) >= fmaf(cn.w, cb, -sa * sb) - 2e-6f;
-                }
-            }
-            const uint64_t kept = __ballot(keep);
-            if (keep) pick[n_pick + lanes_below(kept)] = (uint8_t)jl;
-            n_pick += (uint32_t)__popcll(kept);
-        }
-        wave_lds_sync();
-        const uint64_t live_m = __ballot(live);
-        if (tight && 4u * (uint32_t)__popcll(live_m) <= 3u * rect_rays) {
-            rect_rays = (uint32_t)__popcll(live_m);
-            live_rect(live);
-        }
         auto eval = [&](int j, float* ts_out, float* la_out) {
             const float4 m0 = sr[0][j], m1 = sr[1][j], m2 = sr[2][j], m3 = sr[3][j];
             float tstar, px, py, pz;
@@ -644,6 +631,52 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
                 reach = stop ? INFINITY : reach;
             }
         };
+        uint32_t n_pick = 0;
+        for (int sub = 0; sub < cnt && wave_live; sub += 64) {
+            const int jl = sub + lane;
+            bool keep = false;
+            if (jl < cnt) {
+                const float4 cn = sr[4][jl];
+                if (GRID) {
+                    // distance from the footprint centre to the origin rectangle, against the disc radius
+                    const float ex = fmaxf(0.0f, fmaxf(bx0 - cn.x, cn.x - bx1));
+                    const float ey = fmaxf(0.0f, fmaxf(by0 - cn.y, cn.y - by1));
+                    keep = ex * ex + ey * ey <= cn.z * cn.z * 1.0001f;
+                } else if (!cull || cn.w < -1.5f) {
+                    keep = true;
+                } else {
+                    const float sa = __builtin_amdgcn_sqrtf(fmaxf(0.0f, fmaf(-cn.w, cn.w, 1.0f)));
+                    keep = fmaf(cn.z, w[2], fmaf(cn.y, w[1], cn.x * w[0])) >= fmaf(cn.w, cb, -sa * sb) - 2e-6f;
+                }
+            }
+            const uint64_t kept = __ballot(keep);
+            if constexpr (SHORT) {
+                for (uint64_t m = kept; m != 0ull;) {
+                    const int j0 = sub + __builtin_ctzll(m);
+                    m &= m - 1;
+                    const bool two = m != 0ull;
+                    const int j1 = two ? sub + __builtin_ctzll(m) : j0;
+                    m &= m - 1;         // (zero stays zero)
+                    float t0, l0, t1, l1;
+                    eval(j0, &t0, &l0);
+                    eval(j1, &t1, &l1);
+                    l1 = two ? l1 : -INFINITY;
+                    asm volatile("" : "+v"(t0), "+v"(l0), "+v"(t1), "+v"(l1));      // two independent chains, as below
+                    take(t0, l0);
+                    take(t1, l1);
+                }
+                wave_live = __ballot(reach < INFINITY) != 0ull;
+            } else {
+                if (keep) pick[n_pick + lanes_below(kept)] = (uint8_t)jl;
+                n_pick += (uint32_t)__popcll(kept);
+            }
+        }
+        wave_lds_sync();
+        const uint64_t live_m = __ballot(live);
+        if (tight && 4u * (uint32_t)__popcll(live_m) <= 3u * rect_rays) {
+            rect_rays = (uint32_t)__popcll(live_m);
+            live_rect(live);
+        }
         for (uint32_t p0 = 0; p0 < n_pick && wave_live; p0 += 64) {
             const bool have = p0 + (uint32_t)lane < n_pick;
             const int jp = have ? (int)pick[p0 + (uint32_t)lane] : 0;
@@ -766,18 +799,18 @@ __device__ __forceinline__ void lidar_tile(const SceneDev& s, const ChunkDev& c,
     }
 }
 
-template <int TS>
+template <int TS, bool SHORT>
 __global__ __launch_bounds__(TS * TS) void k_raster_lidar(SceneDev s, ChunkDev c, RasterParams p)
 {
-    __shared__ LidarLds<TS> lds;
+    __shared__ std::conditional_t<SHORT, LidarShortLds<TS>, LidarLds<TS>> lds;
     int i;
     uint32_t t;
     tile_of_block(p, blockIdx.x, &i, &t);
     const ImageInfo im = c.img[i];
     const int tx = (int)(t % (uint32_t)im.tiles_x);
     const int ty = (int)(t / (uint32_t)im.tiles_x);
-    if (im.kind == 2) lidar_tile<TS, true>(s, c, i, im, tx, ty, t, lds);     // workgroup-uniform
-    else lidar_tile<TS, false>(s, c, i, im, tx, ty, t, lds);
+    if (im.kind == 2) lidar_tile<TS, true, SHORT>(s, c, i, im, tx, ty, t, lds);     // workgroup-uniform
+    else lidar_tile<TS, false, SHORT>(s, c, i, im, tx, ty, t, lds);
 }
 
 template <int ST>
@@ -785,6 +818,13 @@ hipError_t project_lidar_st(const SceneDev& s, const ChunkDev& c, int ts, int ip
 {
     const dim3 grid((unsigned)((s.n + 255) / 256), (unsigned)((c.n_img + ipt - 1) / ipt));
     hipLaunchKernelGGL((k_project_lidar<ST>), grid, dim3(256), 0, st, s, c, c.img, ts, ipt);
+    return hipGetLastError();
+}
+
+template <int TS, bool SHORT>
+hipError_t launch_lidar(const SceneDev& s, const ChunkDev& c, const RasterParams& p, hipStream_t stream)
+{
+    hipLaunchKernelGGL((k_raster_lidar<TS, SHORT>), dim3(p.n_blocks), dim3(TS * TS), 0, stream, s, c, p);
     return hipGetLastError();
 }
 
@@ -802,10 +842,10 @@ hipError_t launch_project_lidar(const SceneDev& s, const ChunkDev& c, int ts, in
 hipError_t launch_raster_lidar(const SceneDev& s, const ChunkDev& c, const RasterParams& p, hipStream_t stream)
 {
     if (p.n_blocks == 0) return hipSuccess;
-    if (p.ts == 8) hipLaunchKernelGGL((k_raster_lidar<8>), dim3(p.n_blocks), dim3(64), 0, stream, s, c, p);
-    else if (p.ts == 16) hipLaunchKernelGGL((k_raster_lidar<16>), dim3(p.n_blocks), dim3(256), 0, stream, s, c, p);
-    else return hipErrorInvalidValue;           // 32 x 32 ray tiles exceed the workgroup size
-    return hipGetLastError();
+    const bool few = p.n_blocks > kOrderTilesMin && short_lists(p.entries, p.n_blocks) && p.longest <= kShortLongest;
+    if (p.ts == 8) return few ? launch_lidar<8, true>(s, c, p, stream) : launch_lidar<8, false>(s, c, p, stream);
+    if (p.ts == 16) return few ? launch_lidar<16, true>(s, c, p, stream) : launch_lidar<16, false>(s, c, p, stream);
+    return hipErrorInvalidValue;                // 32 x 32 ray tiles exceed the workgroup size
 }
 
 }  // namespace gsr

@@ -322,7 +322,7 @@ __global__ __launch_bounds__(NT) void k_tile_scan(ChunkDev c)
     for (int x = threadIdx.x; x < TX; x += NT) prefix(gd + x, TY, P1);
     __syncthreads();
     uint32_t* range = c.tile_range + (size_t)i * c.t_max * 2;
-    uint32_t P = 0;
+    uint32_t P = 0, longest = 0;
     for (int t0 = 0; t0 < TX * TY; t0 += NT) {
         const int t = t0 + threadIdx.x;
         const uint32_t cnt = t < TX * TY ? (uint32_t)gd[(t / TX) * P1 + (t % TX)] : 0u;
@@ -333,6 +333,17 @@ __global__ __launch_bounds__(NT) void k_tile_scan(ChunkDev c)
             range[2 * t + 1] = start + cnt;
         }
         P += chunk_total;
+        longest = max(longest, cnt);
+    }
+    if (c.longest) {
+        longest = wave_last(wave_incl_max(longest));
+        if (__lane_id() == 0) part[threadIdx.x >> 6] = longest;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int k = 1; k < NT / 64; ++k) longest = max(longest, part[k]);
+            c.longest[i] = longest;
+        }
+        __syncthreads();
     }
     const uint32_t Rn = scan_rows<NT>(c.row_hist + (size_t)i * c.tile_blocks * c.ty_max, nb, c.ty_max, TY,
                                       c.row_range + (size_t)i * c.ty_max * 2, part, lds16);
@@ -370,8 +381,13 @@ __device__ __forceinline__ void order_tiles(const ChunkDev& c, const RasterParam
     const int tid = threadIdx.x, w = tid >> 6, lane = __lane_id();
     const uint32_t n = p.n_blocks / kXcds + (x < p.n_blocks % kXcds ? 1u : 0u);
     const uint32_t first = xcd_remap(x, p.n_blocks);
+    uint64_t entries = 0;
+    for (int k = lane; k < c.n_img; k += 64) entries += c.pair_count[k];
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) entries += __shfl_xor(entries, m, 64);
     // images of one size, from the longest lists to the shortest (ties by index)
-    const bool deal = p.n_segs == 1 && c.n_img >= 2 * kXcds && c.n_img <= kOrderImages;
+    const bool deal = p.n_segs == 1 && c.n_img >= 2 * kXcds && c.n_img <= kOrderImages &&
+                      !short_lists(entries, p.n_blocks);
     if (deal) {
         const uint32_t mine = tid < c.n_img ? c.pair_count[tid] : 0u;
         if (tid < kOrderImages) work[tid] = mine;
@@ -464,12 +480,15 @@ __device__ __forceinline__ void order_tiles(const ChunkDev& c, const RasterParam
 __device__ __forceinline__ void image_scan(const ChunkDev& c)
 {
     __shared__ uint64_t part[3][4];
+    __shared__ uint32_t most[4];
     const int tid = threadIdx.x;
     const int per = tid < 256 ? (c.n_img + 255) / 256 : 0;         // 256 threads scan
     uint64_t sp = 0, sr = 0, sv = 0;
+    uint32_t longest = 0;
     for (int k = 0; k < per; ++k) {
         const int i = tid * per + k;
         if (i < c.n_img) {
+            if (c.longest) longest = max(longest, c.longest[i]);
             sp += c.pair_count[i];
             sr += c.row_count[i];
             sv += c.n ? c.vis_count[i] : 0u;
@@ -486,7 +505,9 @@ __device__ __forceinline__ void image_scan(const ChunkDev& c)
             iv += v;
         }
     }
+    if (c.longest) longest = wave_last(wave_incl_max(longest));
     if (tid < 256 && (tid & 63) == 63) {
+        most[tid >> 6] = longest;
         part[0][tid >> 6] = ip;
         part[1][tid >> 6] = ir;
         part[2][tid >> 6] = iv;
@@ -513,10 +534,10 @@ __device__ __forceinline__ void image_scan(const ChunkDev& c)
         if (over) __hip_atomic_store(c.host_ovf, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         // the totals go straight to the host's memory: four small copies and the gaps between them otherwise
         if (c.host_totals) {
-            const uint64_t bits = *c.err;
+            const uint64_t v[5] = {tot[0], tot[1], tot[2], *c.err, max(max(most[0], most[1]), max(most[2], most[3]))};
 #pragma unroll
-            for (int k = 0; k < 4; ++k)
-                __hip_atomic_store(&c.host_totals[k], k < 3 ? tot[k] : bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+            for (int k = 0; k < 5; ++k)
+                __hip_atomic_store(&c.host_totals[k], v[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
         }
     }
     if (c.fallback_counter && tid < kXcds) c.fallback_counter[tid] = 0u;

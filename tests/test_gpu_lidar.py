@@ -445,3 +445,40 @@ def test_rounded_roots_and_reciprocals_match_the_specification(R):
     np.testing.assert_array_equal(got["rec"][vis][:, 7], ref["radius"][vis])
     np.testing.assert_array_equal(got["rec"][vis][:, 0], ref["u"][vis])
     R.remove_scene(sid)
+
+
+@pytest.mark.parametrize("ts", [8, 16])
+@pytest.mark.parametrize("kind", ["rotating", "grid", "rays"])
+def test_short_lists_give_the_bits_of_long_ones(kind, ts):
+    """Launches of many tiles with few entries each, which take the kernel of
+    one culling step, against launches of fewer sensors, which take the full
+    one: single entries, odd counts, and one tile of several batches."""
+    torch = _torch()
+    from paper_2604_25459_amd import gsr
+    rng = np.random.default_rng(ts)
+    n, near = 340, 250                                      # most of them in one direction
+    d = rng.standard_normal((n, 3))
+    means = d / np.linalg.norm(d, axis=1, keepdims=True) * rng.uniform(0.8, 3.0, (n, 1))
+    means[:near] = [0.9, 0.0, -0.9] + rng.uniform(-0.06, 0.06, (near, 3))
+    scene = scene_from(means, 0.03 * np.exp(0.6 * rng.standard_normal((n, 3))), quats=rng.standard_normal((n, 4)),
+                       opac=rng.uniform(0.02, 0.3, n), degree=0)
+    lid = {"rotating": synth.rotating_lidar(37, 301, -60, 40), "grid": synth.height_grid(61, 77, 0.05),
+           "rays": synth.rosette_lidar(37, 75, 60.0, s0=1.0)}[kind]
+    tiles = -(-lid.width // ts) * -(-lid.height // ts)
+    E, few = 1281 // tiles + 2, max(1, 1280 // tiles)
+    vm = synth.sensor_viewmats(rng, E, 0.0, 0.3, 0.1)[None]
+    R = gsr.Renderer(0, tile_size=ts)
+    sid = R.add_synth_scene(scene)
+    vm_t = torch.from_numpy(np.ascontiguousarray(vm)).cuda()
+    poses = torch.zeros(E, 0, 7, device="cuda")
+    rng_all, hit_all = (t.clone() for t in R.render_lidar(sid, [lid], vm_t, poses)[0])
+    for a in range(0, E, few):
+        b = min(E, a + few)
+        one = R.render_lidar(sid, [lid], vm_t[:, a:b].contiguous(), poses[a:b])[0]
+        torch.cuda.synchronize()
+        assert torch.equal(rng_all[a:b], one[0]) and torch.equal(hit_all[a:b], one[1]), a
+    assert float((hit_all > 0.05).float().mean()) > 0.01
+    ref = lidar_ref(scene, synth.LidarBatch(cams=[lid], viewmats=vm, poses=np.zeros((E, 0, 7), np.float32)), 0, E - 1)
+    batch = synth.LidarBatch(cams=[lid], viewmats=vm, poses=np.zeros((E, 0, 7), np.float32))
+    _compare(rng_all[E - 1].cpu().numpy(), hit_all[E - 1].cpu().numpy(), ref, kind, scene, batch, 0, E - 1, min_hits=1)
+    R.close()
