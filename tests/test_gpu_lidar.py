@@ -482,3 +482,26 @@ def test_short_lists_give_the_bits_of_long_ones(kind, ts):
     batch = synth.LidarBatch(cams=[lid], viewmats=vm, poses=np.zeros((E, 0, 7), np.float32))
     _compare(rng_all[E - 1].cpu().numpy(), hit_all[E - 1].cpu().numpy(), ref, kind, scene, batch, 0, E - 1, min_hits=1)
     R.close()
+
+
+@pytest.mark.parametrize("ts", [8, 16])
+@pytest.mark.parametrize("rows,cols", [(16, 24), (5, 40), (37, 17)])
+def test_waves_of_wide_rays_match_oracle(rows, cols, ts):
+    """Scans so coarse that a wave's rays spread over more than 45 degrees (or
+    the whole turn), which are culled by the first step at most."""
+    _torch()
+    from paper_2604_25459_amd import gsr
+    rng = np.random.default_rng(rows)
+    n, E = 900, 2
+    scene = scene_from(rng.uniform(-2.5, 2.5, (n, 3)), 0.06 * np.exp(0.6 * rng.standard_normal((n, 3))),
+                       quats=rng.standard_normal((n, 4)), opac=rng.uniform(0.05, 0.999, n), degree=0)
+    lid = synth.rotating_lidar(rows, cols, -70, 75)
+    batch = synth.LidarBatch(cams=[lid], viewmats=synth.sensor_viewmats(rng, E, 0.0, 0.8, 0.2)[None],
+                             poses=np.zeros((E, 0, 7), np.float32))
+    r = gsr.Renderer(0, tile_size=ts)
+    out = r.render_lidar(r.add_synth_scene(scene), [lid], *_tensors(batch))
+    for e in range(E):
+        ref = lidar_ref(scene, batch, 0, e)
+        _compare(out[0][0][e].cpu().numpy(), out[0][1][e].cpu().numpy(), ref, f"{rows}x{cols} ts {ts} env {e}", scene,
+                 batch, 0, e)
+    r.close()
