@@ -1,8 +1,7 @@
 // Batch LiDAR: ray casting of the resident, rigidly posed Gaussians for grids
 // of rays (rotating or solid-state sensors) and for listed rays
-// (non-repetitive scan patterns, sorted on the host into elevation bands of
-// azimuth-ordered rays), through the same sort and tile binning as the
-// cameras.
+// (non-repetitive scan patterns, ordered on the host into compact tiles), through
+// the same sort and tile binning as the cameras.
 //
 // Projection (one thread per Gaussian, a group of scans per thread):
 //   * pose into the sensor frame with the binary32 specification of the
@@ -11,9 +10,9 @@
 //     rounded), so the compositing order is (distance, index);
 //   * tile rectangle: rows and columns of rays whose direction lies in the
 //     cone of the sphere of radius sqrt(Qmax) * max scale around t (Qmax the
-//     opacity bucket bound of the camera path), widened by a relative 1e-4 and
-//     an absolute 2e-6 rad against the rounding of the trigonometric
-//     functions; a cone across the seam of a full turn takes the hull of its
+//     opacity bucket bound of the camera path), its sine widened by a relative
+//     2e-4 and 4e-6, its angles by kAngleSlack against the errors of their
+//     polynomials; a cone across the seam of a full turn takes the hull of its
 //     two column ranges, a sensor inside the sphere takes the whole grid;
 //   * record: whitening W = S^-1 R^T (R, S the Gaussian's rotation in the
 //     sensor frame and its scales), the centre t, log2 o, the cosine of the
@@ -395,7 +394,7 @@ struct LidarLds {
 // Launches of short lists (kShortList) take the first step only, and a wave's rays
 // walk its survivors together: what a tile costs there is what it sets up, and how
 // many others its CU holds beside it (7 workgroups of 48 registers and 20 KB a
-// tile, 5 of 93 and 27 KB with all three steps).
+// tile, 5 of 93 and 28 KB with all three steps).
 template <int TS>
 struct LidarShortLds {
     float4 sr[kLidarStage][TS * TS];

@@ -174,7 +174,13 @@ struct RasterLds {
 // their records its 4 MB of L2, the fourfold reads leave it: 200 images of
 // 128x128 of 140k Gaussians (12,800 tiles) 1.64 ms staged, 1.77 direct, 380 of
 // them 3.00 and 3.28, but 300 of 128x96 of 30k 812 and 801 us.  Direct then needs
-// a launch that is resident at once, or records within kDirectBytes.
+// a launch that is resident at once, or records within kDirectBytes.  From 256
+// tiles an image on it needs neither: 96 images of 256x256 of 180k, 300k and 1M
+// Gaussians 1.39, 1.56 and 3.55 ms staged (by 128), 1.31, 1.49 and 3.50 direct, 16
+// of 3M 2.05 and 2.03.  Of the launches that are resident at once those of few
+// tiles an image lose near the line (2,048 tiles: 2x2 an image of 30k Gaussians
+// 0.99 ms staged, 1.17 direct, 4x4 of 120k 0.86 and 0.89, 8x8 0.44 both; 1,000
+// tiles: 0.68 and 0.67, 0.60 and 0.59, 0.32 and 0.31).
 constexpr uint32_t kDirectTiles = 24576;
 constexpr uint32_t kResidentTiles = 2048;              // eight workgroups per CU
 constexpr uint64_t kDirectBytes = 8ull << 20;

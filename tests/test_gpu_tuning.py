@@ -632,3 +632,39 @@ def test_wide_and_tall_images_in_a_launch(sides, n):
             assert torch.equal(a, b), (k, sides[k])
         assert (float(one[2].amax()) > 0.5) == (n > 0)
     R.close()
+
+
+@pytest.mark.parametrize("n_img,side", [(15, 160), (16, 160), (17, 160), (39, 96), (1023, 32), (1024, 32), (1025, 32)])
+def test_images_of_long_lists_dealt_over_the_xcds_cover_every_tile(n_img, side):
+    """As above with lists of hundreds of entries on average, above the line
+    from which images are dealt out: whole rounds, every kind of remainder, the
+    most images and one more."""
+    torch = _torch()
+    from paper_2604_25459_amd import gsr
+    from tests.scenes import scene_from
+    rng = np.random.default_rng(n_img)
+    n = 400
+    scene = scene_from(rng.uniform([-0.6, -0.6, 1.0], [0.6, 0.6, 3.0], (n, 3)), np.exp(rng.normal(-0.5, 0.8, (n, 3))),
+                       rng.standard_normal((n, 4)), rng.uniform(0.02, 0.3, n), rng.uniform(0, 1, (n, 1, 3)), 0)
+    R = gsr.Renderer(0)
+    sid = R.add_synth_scene(scene)
+    cam = gsr.Camera(side, side, 0.9 * side, 0.9 * side, side / 2, side / 2, 0.01, -1)
+    views = torch.eye(4, device="cuda")[:3].repeat(1, n_img, 1, 1)
+    views[0, :, 0, 3] = torch.from_numpy(rng.uniform(-0.5, 0.5, n_img).astype(np.float32)).cuda()
+    poses = torch.zeros(n_img, 0, 7, device="cuda")
+    bins = R.debug_bins(sid, [cam], views, poses, 0)
+    assert bins["keys"].size > 96 * bins["ranges"].shape[0]
+    rgb, depth, alpha = R.alloc_outputs([cam], n_img, True)
+    for t in (rgb, depth, alpha):
+        t.fill_(-7.0)
+    R.render_into(sid, [cam], views, poses, rgb, depth, alpha)
+    got = R.split([cam], n_img, rgb, depth, alpha)[0]
+    torch.cuda.synchronize()
+    step = 1280 // ((side + 15) // 16) ** 2
+    for a in range(0, n_img, step):
+        b = min(n_img, a + step)
+        one = R.render(sid, [cam], views[:, a:b].contiguous(), poses[a:b], alpha=True)[0]
+        torch.cuda.synchronize()
+        for x, y in zip(got, one):
+            assert torch.equal(x[a:b], y), a
+    R.close()
