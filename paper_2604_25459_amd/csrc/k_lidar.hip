@@ -373,8 +373,8 @@ __device__ __forceinline__ void wave_range(float x, bool on, float* lo, float* h
 // ray, of which 64 are taken; the longest mask of each word adds up to 167, for
 // which the lanes evaluate together.  (A heightmap's wave: 2252, 1224, 87, 62
 // and 349; a rosette's: 336, 140, 83, 60 and 93.)  Before, each quarter of a
-// wave walked the survivors of its own rectangle, about 300 in a scan.  512
-// scans 17.5 -> 17.1 ms with the third step, 512 heightmaps of 64 x 64 rays
+// wave walked the survivors of its own rectangle, about 300 in a scan.  Times of
+// when each step came in: 512 scans 17.5 -> 17.1 ms with the third step, 512 heightmaps of 64 x 64 rays
 // 7.5 -> 7.1 ms, 64 rosette scans of 24,576 rays 2.55 -> 2.20 ms; without any
 // but the first 26.7, 16.2 and 10.3 ms.  Measured and no faster: waves without
 // shared staging (17.1, 7.7, 2.18 ms: four times the reads miss L2, 18.7 GB

@@ -357,17 +357,19 @@ __global__ __launch_bounds__(NT) void k_tile_scan(ChunkDev c)
 // against the part's mean (at least 8, 4, 2, 1.4 times it, the rest), as they
 // come within a class, which keeps the bulk of an image's tiles together in
 // that XCD's L2.  A launch ends with its last tile: where one is many times
-// the mean and comes late, the chip is idle around it.  512 heightmaps of
-// 64 x 64 rays (8,192 tiles of 0.29 ms on average, the longest 2.1 ms) 7.1 ->
-// 6.1 ms, 64 rosette scans 2.15 -> 1.85 ms, 512 scans of 32 x 1024 (65,536
-// tiles) 17.3 -> 17.0 ms; camera launches of 9,620 tiles 503 -> 474 us, of
-// 32,768 tiles 3.26 -> 3.20 ms, of 19,200 unchanged within 0.5 %.
-// In a launch of 16 to 1,024 images of one size the images are first dealt to
-// the XCDs by their list entries, longest first, in rounds there and back: by
-// image order alone XCDs ended between 614 and 711 us in a launch of 64 images
-// of 320x240, between 219 and 279 in one of 37 of 317x203 (474 -> 450 us in
-// all; 64 rosette scans 1.72 -> 1.61 ms, 512 heightmaps 6.08 -> 5.96, 512 scans
-// 16.85 -> 16.54, 512 images of 128x128 3.15 -> 3.08, the 64 1.21 -> 1.19).
+// the mean and comes late, the chip is idle around it.  (Each pair of times is
+// from when its rule came in.)  512 heightmaps of 64 x 64 rays (8,192 tiles of
+// 0.29 ms on average, the longest 2.1 ms) 7.1 -> 6.1 ms, 64 rosette scans 2.15 ->
+// 1.85 ms, 512 scans of 32 x 1024 (65,536 tiles) 17.3 -> 17.0 ms; camera launches
+// of 9,620 tiles 503 -> 474 us, of 32,768 tiles 3.26 -> 3.20 ms, of 19,200
+// unchanged within 0.5 %.
+// In a launch of 16 to 1,024 images of one size, unless its lists are short
+// (kShortList), the images are first dealt to the XCDs by their list entries,
+// longest first, in rounds there and back: by image order alone XCDs ended
+// between 614 and 711 us in a launch of 64 images of 320x240, between 219 and 279
+// in one of 37 of 317x203 (474 -> 450 us in all; 64 rosette scans 1.72 -> 1.61 ms,
+// 512 heightmaps 6.08 -> 5.96, 512 scans 16.85 -> 16.54, 512 images of 128x128
+// 3.15 -> 3.08, the 64 1.21 -> 1.19).
 constexpr int kOrderItems = (int)(kOrderTilesMax / kXcds / 1024);
 constexpr int kOrderClasses = 5;
 constexpr int kOrderImages = 1024;
