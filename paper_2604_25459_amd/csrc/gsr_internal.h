@@ -297,7 +297,7 @@ struct RasterParams {
     uint32_t n_blocks;
     uint64_t entries;        // LiDAR: of the chunk's tile lists, and of the longest of them
     uint64_t longest;
-    uint32_t* order;         // heavy-first order of each XCD's part (launch_tile_order), or null: as they come
+    uint32_t* order;         // heavy-first order of each XCD's part (k_image_scan_order), or null: as they come
 };
 // Launches of more than kOrderTilesMin tiles (up to that all are resident at
 // once: five workgroups per CU) and at most kOrderTilesMax take their tiles
